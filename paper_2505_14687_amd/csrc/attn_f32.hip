@@ -1,171 +1,443 @@
-// fp32 attention (grouped and dense): plain vector-ALU kernel, one query per lane.
+// fp32 attention (grouped and dense) on the fp32 matrix instructions, head_dim 64 or 128.
 //
-// Sec. 3.1 Eq. 1 restricted to the attendable KV groups of Sec. 3.2.  This is the precision
-// path (inputs, scores, softmax and accumulation all fp32); throughput is not its purpose.
-// One 64-lane wavefront owns up to 64 queries of one group; K/V rows of the attendable groups
-// are staged through LDS 32 tokens at a time and every lane reads them as broadcasts.
-// Group dims need not divide the grid (Eq. 2-4 are floor divisions): a group at the far border
-// is the part of its box that lies inside the grid, and its tokens are enumerated over that part.
+// Sec. 3.1 Eq. 1 restricted to the attendable KV groups of Sec. 3.2.  This is the precision path: inputs,
+// products, softmax and accumulation are all fp32 (v_mfma_f32_*_f32 multiplies and adds in fp32).
+// Group dims need not divide the grid (Eq. 2-4 are floor divisions): a group at the far border is the
+// part of its box that lies inside the grid, and its tokens are enumerated over that part only, so no
+// work is done for tokens that are not there.  Any group size.
+//
+// Both kernels form S^T = K Q^T and O^T += V^T P^T.  A lane then owns one query and the weights P^T come
+// out of the first product in the layout the second one takes them in: register r of the S^T accumulator
+// is the B operand of MFMA r of the second product, whose contraction index runs over the keys that
+// register holds across the lane groups.  The A operands are read as 16-byte pieces of K and V rows: one
+// piece feeds four MFMAs, with the head dims taken in the order in which the pieces hold them.
+//
+//   attn_f32_kernel        32 queries a wave, K and V shared through LDS: launches that fill the chip.
+//   attn_f32_split_kernel  16 queries a workgroup, the eight waves share its KEYS and merge at the end:
+//                          launches too small to give every SIMD a wave of its own, and groups of at most
+//                          16 tokens.
 #include "grat_common.h"
+#include "tile_order.h"
 
 namespace grat {
 
-constexpr int kF32Keys = 32;   // KV tokens staged per LDS tile
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-template <int D, bool DENSE>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnParams p) {
-    __shared__ float sK[kF32Keys][D];
-    __shared__ float sV[kF32Keys][D];
+#define LDS_PTR(T) __attribute__((address_space(3))) T*
 
-    const int lane = threadIdx.x;
-    const int tile = xcd_contiguous_tile(blockIdx.x, p.total_tiles);
-    if (tile >= p.total_tiles) return;
+// Weights are taken against a reference maximum that is refreshed only once a score exceeds it by this
+// much (base-2 exponent): any reference gives the same quotient O / l, and weights up to 2^16 leave fp32
+// all its relative accuracy.
+constexpr float kRefSlack = 16.f;
 
+// A group as the part of its box inside the grid.
+struct Box {
+    uint32_t origin;    // row of its first token
+    uint32_t tokens;    // tokens inside the grid
+    FastDiv f1, f2;     // extents along the last two axes
+};
+__device__ __forceinline__ Box group_box(const AttnParams& p, uint32_t gid) {
     const Geometry& geo = p.geo;
-    const int tiles_per_head = DENSE ? p.q_tiles : geo.num_groups * p.q_tiles;
-    const int bh = tile / tiles_per_head;
-    const int t_in_head = tile % tiles_per_head;
-    const int64_t head_off = (int64_t)(bh / p.heads) * p.stride_b + (int64_t)(bh % p.heads) * p.stride_h;
-    const float* Qh = (const float*)p.Q + head_off;
-    const float* Kh = (const float*)p.K + head_off;
-    const float* Vh = (const float*)p.V + head_off;
-    float* Oh = (float*)p.O + (int64_t)(bh / p.heads) * p.o_stride_b + (int64_t)(bh % p.heads) * p.o_stride_h;
+    uint32_t u, p0, p1, p2;
+    fdivmod(gid, p.fd_G2, u, p2);
+    fdivmod(u, p.fd_G1, p0, p1);
+    const bool last1 = (int)p1 == geo.G[1] - 1, last2 = (int)p2 == geo.G[2] - 1;
+    const uint32_t v0 = (int)p0 == geo.G[0] - 1 ? (uint32_t)p.last0 : (uint32_t)geo.g[0];
+    Box b;
+    b.f1.d = last1 ? p.fd_last1.d : p.fd_g1.d;
+    b.f1.m = last1 ? p.fd_last1.m : p.fd_g1.m;
+    b.f1.sh = last1 ? p.fd_last1.sh : p.fd_g1.sh;
+    b.f2.d = last2 ? p.fd_last2.d : p.fd_g2.d;
+    b.f2.m = last2 ? p.fd_last2.m : p.fd_g2.m;
+    b.f2.sh = last2 ? p.fd_last2.sh : p.fd_g2.sh;
+    b.origin = (p0 * geo.g[0] * geo.T[1] + p1 * geo.g[1]) * geo.T[2] + p2 * geo.g[2];
+    b.tokens = v0 * b.f1.d * b.f2.d;
+    return b;
+}
+// token row of the t-th token of a group (last axis fastest inside its box), t < b.tokens
+__device__ __forceinline__ uint32_t token_row(const AttnParams& p, const Box& b, uint32_t t) {
+    uint32_t u, c0, c1, c2;
+    fdivmod(t, b.f2, u, c2);
+    fdivmod(u, b.f1, c0, c1);
+    return b.origin + (c0 * p.geo.T[1] + c1) * p.geo.T[2] + c2;
+}
+// listed group i of query group gamma (caller-made lists are forced into range: a bad one gives wrong
+// numbers, never an access outside the tensors)
+__device__ __forceinline__ uint32_t list_entry(const AttnParams& p, int gamma, int i) {
+    return (uint32_t)min(max(p.kv_index[(int64_t)gamma * p.max_kv + i], 0), p.geo.num_groups - 1);
+}
 
-    const int T12 = geo.T[1] * geo.T[2];
-    const int G12 = geo.G[1] * geo.G[2];
+__device__ __forceinline__ float swap32(float x) { return __shfl_xor(x, 32); }
 
-    // A group as its first token row and the extents of its box inside the grid.
-    struct Box { int origin, v1, v2, tokens; };
-    auto group_box = [&](int gid) {
-        const int p0 = gid / G12, p1 = (gid / geo.G[2]) % geo.G[1], p2 = gid % geo.G[2];
-        const int v0 = min(geo.g[0], geo.T[0] - p0 * geo.g[0]);
-        Box b;
-        b.v1 = min(geo.g[1], geo.T[1] - p1 * geo.g[1]);
-        b.v2 = min(geo.g[2], geo.T[2] - p2 * geo.g[2]);
-        b.origin = p0 * geo.g[0] * T12 + p1 * geo.g[1] * geo.T[2] + p2 * geo.g[2];
-        b.tokens = v0 * b.v1 * b.v2;
-        return b;
-    };
-    // token row of the t-th token of a group (last axis fastest inside its box)
-    auto token_row = [&](const Box& b, int t) {
-        return b.origin + (t / (b.v1 * b.v2)) * T12 + ((t / b.v2) % b.v1) * geo.T[2] + t % b.v2;
-    };
+// ---- 32 queries a wave -------------------------------------------------------------------------
+// Bound: the fp32 matrix pipe.  A 32x32x2 MFMA holds it for 64 cycles and a 32-key tile takes a wave
+// D of them, against 32 * D * 8 bytes of K and V, so one 16-byte LDS read feeds four MFMAs (256 cycles)
+// and there is no pressure on LDS or memory: K and V have one tile buffer each (32 KiB together at
+// head_dim 128), V(t) is fetched while the waves form the scores of tile t, K(t+1) while they add tile t
+// to O, with a barrier between the two halves.  Two waves per SIMD, from different workgroups, cover
+// each other's softmax and barriers.  64x64 tokens in 16x16 groups, 24 heads x 128, criss-cross lists: 7 230 us
+// as one query per lane on the vector ALU (12.5 TFLOP/s: one wave per SIMD and a dependent multiply-add
+// chain per score), 702 us here (128 TFLOP/s; a large fp32 library product reaches 153 on the same card).
+template <int D, bool DENSE, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
+    constexpr int kKeys = 32, NB = D / 32, CPR = D / 4;   // O^T blocks of 32 head dims; 16-byte chunks in a row
+    constexpr int RPP = 64 / CPR;                         // rows in a 1-KiB load of one wave
+    constexpr int LPW = kKeys / RPP / NW;                 // such loads per wave and tile
+    __shared__ __attribute__((aligned(1024))) float sK[kKeys * D];
+    __shared__ __attribute__((aligned(1024))) float sV[kKeys * D];
 
-    int gamma = 0, q_row, n_lists, list_tokens;
-    bool q_valid;
-    if (DENSE) {
-        q_row = t_in_head * 64 + lane;
-        q_valid = q_row < p.n_tokens;
-        n_lists = 1;
-        list_tokens = p.n_tokens;
-    } else {
-        gamma = t_in_head / p.q_tiles;
-        const Box qb = group_box(gamma);
-        if ((t_in_head % p.q_tiles) * 64 >= qb.tokens) return;   // a border group with fewer query tiles
-        const int t = (t_in_head % p.q_tiles) * 64 + lane;
-        q_valid = t < qb.tokens;
-        q_row = token_row(qb, q_valid ? t : 0);
-        n_lists = min(max(p.kv_count[gamma], 0), p.max_kv);   // (forced into range: a bad list never reads outside the tensors)
-        list_tokens = 0;   // per listed group, below
-    }
-    if (!q_valid && DENSE) q_row = p.n_tokens - 1;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int qcol = lane & 31, half = lane >> 5;
+    int bh, qt, gamma = 0;
+    if (!pick_tile<DENSE>(p, bh, qt, gamma)) return;
 
-    float q[D], o[D];
+    const int b_idx = (int)fdiv((uint32_t)bh, p.fd_heads), h_idx = bh - b_idx * p.heads;
+    const int64_t head_off = (int64_t)b_idx * p.stride_b + (int64_t)h_idx * p.stride_h;
+    const uint8_t* Kh = (const uint8_t*)((const float*)p.K + head_off);
+    const uint8_t* Vh = (const uint8_t*)((const float*)p.V + head_off);
+    const uint64_t pitch = (uint64_t)(uint32_t)p.stride_n * 4u;
+
+    const int q_first = (qt * NW + wave) * 32;
+    Box qb{};
+    if (!DENSE) qb = group_box(p, (uint32_t)gamma);
+    const int q_tokens = DENSE ? p.n_tokens : (int)qb.tokens;
+    if (qt * NW * 32 >= q_tokens) return;    // a clipped group with fewer query tiles
+    const bool active = q_first < q_tokens;  // (a wave without queries still loads its share and meets the barriers)
+    const int q_t = min(q_first + qcol, q_tokens - 1);
+    const uint32_t q_row = DENSE ? (uint32_t)q_t : token_row(p, qb, (uint32_t)q_t);
+
+    // Q^T (B operand): q[4 * j + s] = dim 8 * j + 4 * half + s of this lane's query
+    float q[D / 2];
     {
-        const float4* src = (const float4*)(Qh + (int64_t)q_row * p.stride_n);
+        const float* src = (const float*)p.Q + head_off + (int64_t)q_row * p.stride_n + 4 * half;
 #pragma unroll
-        for (int c = 0; c < D / 4; ++c) {
-            const float4 v = src[c];
-            q[4 * c] = v.x; q[4 * c + 1] = v.y; q[4 * c + 2] = v.z; q[4 * c + 3] = v.w;
-        }
+        for (int j = 0; j < D / 8; ++j) {
+            const f32x4 v = *(const f32x4*)(src + 8 * j);
 #pragma unroll
-        for (int c = 0; c < D; ++c) o[c] = 0.f;
-    }
-    float m = -INFINITY, l = 0.f;
-
-    for (int li = 0; li < n_lists; ++li) {
-        Box kb{0, 1, 1, 0};
-        if (!DENSE) {
-            kb = group_box(min(max(p.kv_index[(int64_t)gamma * p.max_kv + li], 0), p.geo.num_groups - 1));
-            list_tokens = kb.tokens;
-        }
-        for (int t0 = 0; t0 < list_tokens; t0 += kF32Keys) {
-            const int n_valid = min(kF32Keys, list_tokens - t0);
-            __syncthreads();
-            // stage K and V rows: D/4 float4 per row, 64 lanes
-            for (int c = lane; c < kF32Keys * (D / 4); c += 64) {
-                const int kk = c / (D / 4), col = c % (D / 4);
-                if (kk < n_valid) {
-                    const int row = DENSE ? t0 + kk : token_row(kb, t0 + kk);
-                    const int64_t off = (int64_t)row * p.stride_n + 4 * col;
-                    *(float4*)&sK[kk][4 * col] = *(const float4*)(Kh + off);
-                    *(float4*)&sV[kk][4 * col] = *(const float4*)(Vh + off);
-                }
-            }
-            __syncthreads();
-
-            float s[kF32Keys];
-            float tile_max = -INFINITY;
-#pragma unroll
-            for (int kk = 0; kk < kF32Keys; ++kk) {
-                float acc = 0.f;
-                if (kk < n_valid) {
-#pragma unroll
-                    for (int c = 0; c < D; c += 4) {
-                        const float4 kv = *(const float4*)&sK[kk][c];
-                        acc = fmaf(q[c], kv.x, acc);
-                        acc = fmaf(q[c + 1], kv.y, acc);
-                        acc = fmaf(q[c + 2], kv.z, acc);
-                        acc = fmaf(q[c + 3], kv.w, acc);
-                    }
-                    acc *= p.scale_log2;
-                    tile_max = fmaxf(tile_max, acc);
-                } else {
-                    acc = -INFINITY;
-                }
-                s[kk] = acc;
-            }
-            const float m_new = fmaxf(m, tile_max);
-            const float alpha = exp2f(m - m_new);   // first tile: exp2(-inf) = 0
-            l *= alpha;
-#pragma unroll
-            for (int c = 0; c < D; ++c) o[c] *= alpha;
-#pragma unroll
-            for (int kk = 0; kk < kF32Keys; ++kk) {
-                if (kk < n_valid) {
-                    const float w = exp2f(s[kk] - m_new);
-                    l += w;
-#pragma unroll
-                    for (int c = 0; c < D; c += 4) {
-                        const float4 vv = *(const float4*)&sV[kk][c];
-                        o[c] = fmaf(w, vv.x, o[c]);
-                        o[c + 1] = fmaf(w, vv.y, o[c + 1]);
-                        o[c + 2] = fmaf(w, vv.z, o[c + 2]);
-                        o[c + 3] = fmaf(w, vv.w, o[c + 3]);
-                    }
-                }
-            }
-            m = m_new;
+            for (int s = 0; s < 4; ++s) q[4 * j + s] = v[s];
         }
     }
 
-    if (q_valid) {
-        const float inv = 1.f / l;
-        float4* dst = (float4*)(Oh + (int64_t)q_row * p.o_stride_n);
+    // The walk: entry e of the list, tile j of its tokens; lane l looks after key l % 32 of a tile.
+    const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
+    if (cnt == 0) return;
+    int e = 0, j = 0;
+    uint32_t gid_next = 0, key_row = 0;
+    Box kb{};
+    int kv_tokens = p.n_tokens;
+    auto enter = [&](uint32_t gid) {   // the walk reaches entry e, which is group gid
+        if (DENSE) return;
+        kb = group_box(p, gid);
+        kv_tokens = (int)kb.tokens;
+        if (e + 1 < cnt) gid_next = list_entry(p, gamma, e + 1);
+    };
+    auto find_rows = [&]() {
+        const uint32_t t = (uint32_t)min(32 * j + qcol, kv_tokens - 1);
+        key_row = DENSE ? t : token_row(p, kb, t);
+    };
+    // direct-to-LDS loads as inline assembly: the compiler would wait for a load it can see ahead of every
+    // later LDS read; completion is waited for explicitly before the barrier that publishes the tile
+    auto issue = [&](const uint8_t* head, float* tile, bool swizzle) {
 #pragma unroll
-        for (int c = 0; c < D / 4; ++c)
-            dst[c] = make_float4(o[4 * c] * inv, o[4 * c + 1] * inv, o[4 * c + 2] * inv, o[4 * c + 3] * inv);
+        for (int k = 0; k < LPW; ++k) {
+            const int piece = wave * LPW + k, row = RPP * piece + lane / CPR, pos = lane % CPR;
+            const uint32_t src_row = (uint32_t)__shfl((int)key_row, row);
+            const uint8_t* src = head + src_row * pitch + 16 * (swizzle ? pos ^ (row & 15) : pos);
+            const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(LDS_PTR(uint8_t))((uint8_t*)tile + piece * 1024));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(dst), "v"(src) : "memory", "m0");
+        }
+    };
+    auto landed = [&]() {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+
+    f32x16 o[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+    float m_ref = -INFINITY, l = 0.f;   // l: this lane's share of the sum (its 16 keys of every tile)
+    const float c = p.scale_log2;
+
+    enter(DENSE ? 0u : list_entry(p, gamma, 0));
+    find_rows();
+    issue(Kh, sK, true);
+    for (;;) {
+        const int n_valid = min(kKeys, kv_tokens - kKeys * j);
+        landed();   // K(t) is there, and everyone has finished with V(t-1)
+        issue(Vh, sV, false);
+        f32x16 S;
+        if (active) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) S[r] = 0.f;
+#pragma unroll
+            for (int jj = 0; jj < D / 8; ++jj) {
+                const f32x4 kf = *(const f32x4*)&sK[qcol * D + 4 * ((2 * jj + half) ^ (qcol & 15))];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) S = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[s], q[4 * jj + s], S, 0, 0, 0);
+            }
+            if (n_valid < kKeys) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (8 * (r >> 2) + 4 * half + (r & 3) >= n_valid) S[r] = -INFINITY;
+            }
+            float mx = S[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S[r]);
+            mx = fmaxf(mx, swap32(mx)) * c;
+            if (__builtin_amdgcn_ballot_w64(mx > m_ref + kRefSlack) != 0) {
+                const float m_new = fmaxf(m_ref, mx), alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+                m_ref = m_new;
+                l *= alpha;
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -m_ref));
+                l += S[r];
+            }
+        }
+        landed();   // V(t) is there, and everyone has finished with K(t)
+        bool more = true;
+        if (kKeys * (j + 1) < kv_tokens) {
+            ++j;
+        } else {
+            j = 0;
+            more = ++e < cnt;
+            if (more) enter(gid_next);
+        }
+        if (more) {
+            find_rows();
+            issue(Kh, sK, true);
+        }
+        if (active) {
+            // A operand: rows 4*qcol .. (NB dims of the row's piece): block b holds head dims NB * i + b
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float* src = &sV[(8 * (r >> 2) + 4 * half + (r & 3)) * D + NB * qcol];
+                float v[NB];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) v[b] = src[b];
+#pragma unroll
+                for (int b = 0; b < NB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[b], S[r], o[b], 0, 0, 0);
+            }
+        }
+        if (!more) break;
+    }
+
+    if (q_first + qcol < q_tokens) {
+        const float inv = 1.f / (l + swap32(l));
+        float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h + (int64_t)q_row * p.o_stride_n;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float* d = dst + NB * (8 * (r >> 2) + 4 * half + (r & 3));
+#pragma unroll
+            for (int b = 0; b < NB; ++b) d[b] = o[b][r] * inv;
+        }
     }
 }
 
-hipError_t launch_attn_f32(const AttnParams& p, int head_dim, bool dense, hipStream_t stream) {
-    const dim3 grid(xcd_padded_blocks(p.total_tiles)), block(64);
+// ---- 16 queries a workgroup, keys split over its waves -------------------------------------------
+// Bound: latency.  A small launch cannot give each of the 1 024 SIMDs 32 queries, and one wave's walk over
+// a list is a serial chain of 64-cycle MFMAs; so the tile is 16 queries (16x16x4 MFMAs: the same rate,
+// half the chain), wave w takes every eighth block of 16 keys, straight from memory into registers (nobody
+// else reads it), one block ahead, and the eight partial results are merged through LDS.  Blocks are cut
+// from the listed groups laid end to end, each padded to a multiple of 16 tokens - groups of fewer than
+// 16 tokens are not padded but packed, several to a block.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
+// with the list building: 390 us with one query per lane (32 waves in all), 28 us here, most of it host time.
+template <int D, bool DENSE>
+__global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
+    constexpr int NW = 8, NP = D / 64;   // 64-dim parts of a V row
+    __shared__ __attribute__((aligned(16))) float s_o[NW][16][D];
+    __shared__ float s_m[NW][16], s_l[NW][16];
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, quarter = lane >> 4;
+    int bh, qt, gamma = 0;
+    if (!pick_tile<DENSE>(p, bh, qt, gamma)) return;
+
+    const int b_idx = (int)fdiv((uint32_t)bh, p.fd_heads), h_idx = bh - b_idx * p.heads;
+    const int64_t head_off = (int64_t)b_idx * p.stride_b + (int64_t)h_idx * p.stride_h;
+    const float* Kh = (const float*)p.K + head_off;
+    const float* Vh = (const float*)p.V + head_off;
+    Box qb{};
+    if (!DENSE) qb = group_box(p, (uint32_t)gamma);
+    const int q_tokens = DENSE ? p.n_tokens : (int)qb.tokens;
+    if (qt * 16 >= q_tokens) return;
+    auto query_row = [&](int i) {
+        const uint32_t t = (uint32_t)min(qt * 16 + i, q_tokens - 1);
+        return DENSE ? t : token_row(p, qb, t);
+    };
+
+    const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
+    if (cnt == 0) return;
+    const int n_blocks = DENSE ? (p.n_tokens + 15) / 16 : (int)(((int64_t)cnt * p.pad_tokens + 15) / 16);
+    // block b: lane looks after key `col` of it.  The group it belongs to is read one block before its rows
+    // are needed, its K and V one block before they are multiplied.
+    auto entry_of = [&](int b, uint32_t& t) -> int {
+        uint32_t e;
+        fdivmod((uint32_t)(16 * b + col), p.fd_pad_tokens, e, t);
+        return (int)e;
+    };
+    auto read_gid = [&](int b) -> uint32_t {
+        if (DENSE) return 0;
+        uint32_t t;
+        return list_entry(p, gamma, min(entry_of(min(b, n_blocks - 1), t), cnt - 1));
+    };
+    struct Block {
+        f32x4 k[D / 16], v[4][NP];
+        uint64_t valid;   // bit l: lane l's key exists
+    };
+    auto fetch = [&](Block& x, int b, uint32_t gid) {
+        uint32_t row;
+        bool ok;
+        if (DENSE) {
+            row = (uint32_t)min(16 * b + col, p.n_tokens - 1);
+            ok = 16 * b + col < p.n_tokens;
+        } else {
+            uint32_t t;
+            const int e = entry_of(b, t);
+            const Box kb = group_box(p, gid);
+            ok = e < cnt && t < kb.tokens;
+            row = token_row(p, kb, ok ? t : 0u);
+        }
+        x.valid = __builtin_amdgcn_ballot_w64(ok);
+        const float* src = Kh + (int64_t)row * p.stride_n + 4 * quarter;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) x.k[j] = *(const f32x4*)(src + 16 * j);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t vrow = (uint32_t)__shfl((int)row, 4 * quarter + r);
+#pragma unroll
+            for (int n = 0; n < NP; ++n) x.v[r][n] = *(const f32x4*)(Vh + (int64_t)vrow * p.stride_n + 64 * n + 4 * col);
+        }
+    };
+
+    uint32_t gid0 = read_gid(wave), gid1 = read_gid(wave + NW);
+    // Q^T (B operand): q[j][s] = dim 16 * j + 4 * quarter + s of query `col`
+    f32x4 q[D / 16];
+    {
+        const float* src = (const float*)p.Q + head_off + (int64_t)query_row(col) * p.stride_n + 4 * quarter;
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) q[j] = *(const f32x4*)(src + 16 * j);
+    }
+    f32x4 o[4 * NP];   // o[4 * n + s]: head dims 64 * n + 4 * i + s, i = 4 * quarter + register
+#pragma unroll
+    for (int b = 0; b < 4 * NP; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_ref = -INFINITY, l = 0.f;
+    const float c = p.scale_log2;
+
+    auto add_block = [&](const Block& x) {
+        if (x.valid == 0) return;   // padding of a clipped group
+        f32x4 S = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) S = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[j][s], q[j][s], S, 0, 0, 0);
+        // lane holds keys 4 * quarter + r of its query
+        const uint32_t mine = (uint32_t)x.valid >> (4 * quarter);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (!(mine >> r & 1u)) S[r] = -INFINITY;
+        float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32)) * c;
+        if (__builtin_amdgcn_ballot_w64(mx > m_ref + kRefSlack) != 0) {
+            const float m_new = fmaxf(m_ref, mx), alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
+            m_ref = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int b = 0; b < 4 * NP; ++b) o[b] *= alpha;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -m_ref));
+            l += S[r];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int n = 0; n < NP; ++n)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    o[4 * n + s] = __builtin_amdgcn_mfma_f32_16x16x4f32(x.v[r][n][s], S[r], o[4 * n + s], 0, 0, 0);
+    };
+
+    Block x0, x1;
+    int b = wave;
+    if (b < n_blocks) fetch(x0, b, gid0);
+    while (b < n_blocks) {
+        gid0 = read_gid(b + 2 * NW);
+        if (b + NW < n_blocks) fetch(x1, b + NW, gid1);
+        add_block(x0);
+        b += NW;
+        if (b >= n_blocks) break;
+        gid1 = read_gid(b + 2 * NW);
+        if (b + NW < n_blocks) fetch(x0, b + NW, gid0);
+        add_block(x1);
+        b += NW;
+    }
+
+    // merge: every wave leaves its reference, sum and O; a thread then adds up one query's share of dims
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (quarter == 0) {
+        s_m[wave][col] = m_ref;
+        s_l[wave][col] = l;
+    }
+#pragma unroll
+    for (int n = 0; n < NP; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            *(f32x4*)&s_o[wave][col][64 * n + 4 * (4 * quarter + r)] =
+                f32x4{o[4 * n][r], o[4 * n + 1][r], o[4 * n + 2][r], o[4 * n + 3][r]};
+    __syncthreads();
+    constexpr int DPT = 16 * D / 512;   // head dims per thread: 2 or 4
+    const int qi = threadIdx.x / 32, d0 = (threadIdx.x % 32) * DPT;
+    float M = s_m[0][qi];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w][qi]);
+    float sum = 0.f, acc[DPT];
+#pragma unroll
+    for (int d = 0; d < DPT; ++d) acc[d] = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float f = __builtin_amdgcn_exp2f(s_m[w][qi] - M);   // (a wave without keys: exp2(-inf) = 0)
+        sum = fmaf(f, s_l[w][qi], sum);
+#pragma unroll
+        for (int d = 0; d < DPT; ++d) acc[d] = fmaf(f, s_o[w][qi][d0 + d], acc[d]);
+    }
+    if (qt * 16 + qi < q_tokens) {
+        const float inv = 1.f / sum;
+        float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h +
+                     (int64_t)query_row(qi) * p.o_stride_n + d0;
+#pragma unroll
+        for (int d = 0; d < DPT; ++d) dst[d] = acc[d] * inv;
+    }
+}
+
+template <int D, bool DENSE>
+static void launch_d(const AttnParams& p, int rows, hipStream_t stream) {
+    const dim3 grid(tile_blocks<DENSE>(p));
+    if (rows == 16) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE>), grid, dim3(512), 0, stream, p);
+    else if (rows == 32) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 1>), grid, dim3(64), 0, stream, p);
+    else if (rows == 64) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 2>), grid, dim3(128), 0, stream, p);
+    else hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 4>), grid, dim3(256), 0, stream, p);
+}
+
+// rows: query rows per workgroup, 16, 32, 64 or 128 (f32_tile_rows), for which p's tile counts were made
+hipError_t launch_attn_f32(const AttnParams& p, int rows, int head_dim, bool dense, hipStream_t stream) {
     if (head_dim == 64) {
-        if (dense) hipLaunchKernelGGL((attn_f32_kernel<64, true>), grid, block, 0, stream, p);
-        else       hipLaunchKernelGGL((attn_f32_kernel<64, false>), grid, block, 0, stream, p);
+        if (dense) launch_d<64, true>(p, rows, stream);
+        else launch_d<64, false>(p, rows, stream);
     } else {
-        if (dense) hipLaunchKernelGGL((attn_f32_kernel<128, true>), grid, block, 0, stream, p);
-        else       hipLaunchKernelGGL((attn_f32_kernel<128, false>), grid, block, 0, stream, p);
+        if (dense) launch_d<128, true>(p, rows, stream);
+        else launch_d<128, false>(p, rows, stream);
     }
     return hipGetLastError();
 }

@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "grat_common.h"
+#include "tile_order.h"
 
 namespace grat {
 
@@ -201,7 +202,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         } else {
             const uint32_t u_group = fdiv((uint32_t)t_in_head, p.fd_q_tiles);
             qt = t_in_head - (int)u_group * p.q_tiles;
-            gamma = strip_order_group_fast(u_group, geo.G[0] * geo.G[1], geo.G[2], p);
+            gamma = strip_order_group(u_group, geo.G[0] * geo.G[1], geo.G[2], p);
         }
         const int n_g = geo.group_tokens;
         const int T12 = geo.T[1] * geo.T[2];
@@ -734,44 +735,9 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     }
 }
 
-// The kernel: picks this workgroup's query tile and runs it.  Workgroups are dealt round-robin to the
-// 8 XCDs; block b runs on XCD b % 8 as that XCD's (b / 8)-th workgroup.  The XCDs walk the heads
-// TOGETHER: within a head every XCD owns one eighth of the head's tile order (a compact range of
-// query groups; which eighth rotates from head to head, so that the short lists of border groups are
-// spread evenly), so at any time the whole chip reads the K/V of one or two heads (which the memory-side
-// cache holds) and every XCD's L2 sees a compact patch of neighbouring groups.  In joint mode the
-// long-running dense tiles over the prompt rows get the lowest block indices, dealt round-robin over
-// the XCDs, and the grouped tiles follow.
-template <bool DENSE>
-__device__ __forceinline__ bool head_sync_tile(const AttnParams& p, int xcd, int idx, int& bh, int& t_in_head) {
-    const int per = DENSE ? p.per_xcd_dense : p.per_xcd;
-    const int tph = DENSE ? p.q_tiles_dense : p.geo.num_groups * p.q_tiles;
-    bh = (int)fdiv((uint32_t)idx, DENSE ? p.fd_per_xcd_dense : p.fd_per_xcd);
-    t_in_head = ((xcd + bh) % kNumXcd) * per + (idx - bh * per);   // (rotated per head: border groups have shorter lists)
-    return t_in_head < tph && bh < p.batch * p.heads;
-}
-// Small launches (p.longest_first; at most 64 groups): the hardware hands out workgroups in block order
-// and a launch of only a few rounds of workgroups ends when its last long one does, so the groups with
-// the longest lists go first and the short ones fill the tail.  Block b is query tile b % q_tiles of
-// (batch, head) (b / q_tiles) % (batch * heads) of the group whose list is the (b / (q_tiles * batch *
-// heads))-th longest (ties: lower id first); lane j ranks group j against the others, every wave for
-// itself.
-__device__ __forceinline__ bool longest_first_tile(const AttnParams& p, int b, int& bh, int& qt, int& gamma) {
-    const int G = p.geo.num_groups;
-    const int rank = (int)fdiv((uint32_t)b, p.fd_tiles_per_rank), rem = b - rank * p.batch * p.heads * p.q_tiles;
-    if (rank >= G) return false;
-    bh = (int)fdiv((uint32_t)rem, p.fd_q_tiles);
-    qt = rem - bh * p.q_tiles;
-    const int lane = threadIdx.x & 63;
-    const int key = lane < G ? min(max(p.kv_count[lane], 0), p.max_kv) * 64 + (63 - lane) : -1;
-    int r = 0;
-#pragma unroll
-    for (int k = 0; k < 64; ++k) r += __builtin_amdgcn_readlane(key, k) > key ? 1 : 0;
-    const uint64_t m = __ballot(lane < G && r == rank);   // (the keys differ, so exactly one lane)
-    gamma = __builtin_amdgcn_readfirstlane(__ffsll((long long)m) - 1);
-    return true;
-}
-
+// The kernel: picks this workgroup's query tile (tile_order.h) and runs it.  In joint mode the long-running
+// dense tiles over the prompt rows get the lowest block indices, dealt round-robin over the XCDs, and the
+// grouped tiles follow.
 template <int NWAVES, int BN, int MODE, bool F16, int D>
 __global__ __launch_bounds__(NWAVES * 64, 2) void attn_mfma_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t sK[2][BN * kRowBytes];
@@ -807,8 +773,7 @@ template <int NWAVES, int BN, bool F16, int D>
 inline hipError_t launch_one(const AttnParams& p, int mode, hipStream_t stream) {
     const dim3 block(NWAVES * 64);
     const size_t dyn = mode == kDense ? 0 : sizeof(int32_t) * (mode == kRagged ? 2 : 1) * ((size_t)p.geo.group_tokens + p.max_kv);
-    const int bh = p.batch * p.heads;
-    const int grouped_blocks = kNumXcd * p.per_xcd * bh, dense_blocks = kNumXcd * p.per_xcd_dense * bh;
+    const int grouped_blocks = tile_blocks<false>(p), dense_blocks = tile_blocks<true>(p);
     if (mode == kRagged) {
         hipLaunchKernelGGL((attn_mfma_kernel<NWAVES, BN, kRagged, F16, D>), dim3(grouped_blocks), block, dyn, stream, p);
     } else if (mode == kDense) {

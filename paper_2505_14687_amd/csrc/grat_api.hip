@@ -180,6 +180,23 @@ static void fill_fastdivs(AttnParams& p) {
     p.fd_g2 = make_fastdiv((uint32_t)geo.g[2]);
     p.fd_G1 = make_fastdiv((uint32_t)geo.G[1]);
     p.fd_G2 = make_fastdiv((uint32_t)geo.G[2]);
+    p.last0 = geo.T[0] - (geo.G[0] - 1) * geo.g[0];
+    p.fd_last1 = make_fastdiv((uint32_t)(geo.T[1] - (geo.G[1] - 1) * geo.g[1]));
+    p.fd_last2 = make_fastdiv((uint32_t)(geo.T[2] - (geo.G[2] - 1) * geo.g[2]));
+    p.pad_tokens = geo.group_tokens < 16 ? geo.group_tokens : (geo.group_tokens + 15) / 16 * 16;
+    p.fd_pad_tokens = make_fastdiv((uint32_t)p.pad_tokens);
+}
+
+// Query rows per workgroup of the fp32 path: 16 selects the kernel that splits the keys over a workgroup's
+// waves, 32 / 64 / 128 the one whose waves own 32 queries each.  `rows` = query rows of a group (or of the
+// sequence), `problems` = groups x heads x batch, `keys` = an upper bound of a list's keys.
+static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys) {
+    const int64_t waves = problems * ((rows + 31) / 32);   // of the 32-query kernel; the chip has 1 024 SIMDs
+    if (keys < kMaxElems - 65536 && (rows <= 16 || waves < 1024)) return 16;
+    const int64_t need = (rows + 31) / 32 * 32;
+    for (int bm = 128; bm > 32; bm /= 2)
+        if ((rows + bm - 1) / bm * bm == need || rows >= 1024) return bm;   // (no wave without queries)
+    return 32;
 }
 
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
@@ -244,14 +261,13 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
         // walk (measured: +5 % at 64x64 tokens, nothing either way from 128x128 tokens on).
         if (bm == 256 && (int64_t)batch * heads * geo.num_groups < 2 * 256) bm = 128;
     } else {
-        bm = 64;
+        bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, (int64_t)max_kv * (n_g + 15));
     }
     p.q_tiles = (n_g + bm - 1) / bm;
     p.strip_w = geo.G[2] >= 16 ? 8 : geo.G[2];
     // (the launch pads every head's tiles to a multiple of 8: up to 7 more per head)
     const int64_t total = (int64_t)batch * heads * geo.num_groups * p.q_tiles;
     if ((int64_t)batch * heads * ((int64_t)geo.num_groups * p.q_tiles + 8) >= kMaxElems - 8) return GRAT_ERR_UNSUPPORTED;
-    p.total_tiles = (int32_t)total;
 
     int mode = ragged ? kRagged : kGrouped;
     // the clipped-box tests of the bf16 kernel pack box coordinates into 12 + 10 + 10 bits
@@ -270,12 +286,12 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     // first (measured at 128x128 tokens in 16x16 groups, 24 heads: +14 % for 3x3 lists, +10 % for 5x5,
     // nothing either way for the equally long criss-cross lists; at 64x64 tokens +7 %).  Larger launches
     // keep the order that lets neighbouring groups share their K/V in the L2.
-    p.longest_first = is16(dtype) && geo.num_groups <= 64 && total <= 16 * 256;
+    p.longest_first = geo.num_groups <= 64 && total <= 16 * 256;
     p.fd_tiles_per_rank = make_fastdiv((uint32_t)(batch * heads * p.q_tiles));
     fill_fastdivs(p);
     const hipError_t e = is16(dtype)
                              ? launch_attn_bf16(p, mode, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
-                             : launch_attn_f32(p, head_dim, false, (hipStream_t)hip_stream);
+                             : launch_attn_f32(p, bm, head_dim, false, (hipStream_t)hip_stream);
     return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
 }
 
@@ -344,19 +360,17 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     p.batch = batch; p.heads = heads;
     p.scale_log2 = scale * 1.4426950408889634f;
     p.n_tokens = (int32_t)n_tokens;
-    const int bm = is16(dtype) ? 256 : 64;
+    const int bm = is16(dtype) ? 256 : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens);
     p.q_tiles = (int32_t)((n_tokens + bm - 1) / bm);
     p.q_tiles_dense = p.q_tiles;
     p.n_dense_rows = (int32_t)n_tokens;
     p.dense_row0 = 0;
-    const int64_t total = (int64_t)batch * heads * p.q_tiles;
     if ((int64_t)batch * heads * ((int64_t)p.q_tiles + 8) >= kMaxElems - 8) return GRAT_ERR_UNSUPPORTED;
-    p.total_tiles = (int32_t)total;
 
     fill_fastdivs(p);
     const hipError_t e = is16(dtype)
                              ? launch_attn_bf16(p, kDense, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
-                             : launch_attn_f32(p, head_dim, true, (hipStream_t)hip_stream);
+                             : launch_attn_f32(p, bm, head_dim, true, (hipStream_t)hip_stream);
     return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
 }
 

@@ -35,7 +35,6 @@ struct AttnParams {
     int32_t max_kv;
     int32_t n_tokens;          // dense tiles: number of KV rows (the whole sequence)
     int32_t q_tiles;           // query tiles per group
-    int32_t total_tiles;       // batch * heads * groups * q_tiles (grouped) or batch * heads * q_tiles_dense (dense)
     int32_t strip_w;           // grouped bf16 path: query groups are walked in column strips this wide
     // dense tiles (dense entry point, and the prompt rows of a joint sequence)
     int32_t q_tiles_dense;     // query tiles per head
@@ -56,6 +55,11 @@ struct AttnParams {
     FastDiv fd_strip, fd_strip_w, fd_strip_tail;   // strip order: by rows * strip_w, strip_w, width of the last strip
     int32_t strip_full;               // full strips: cols / strip_w
     FastDiv fd_g1, fd_g2, fd_G1, fd_G2;            // token in group -> box coordinates, group id -> group coordinates
+    // fp32 kernels: extents of the last group along each axis (it may be cut by the grid's border)
+    int32_t last0;
+    FastDiv fd_last1, fd_last2;
+    int32_t pad_tokens;               // tokens a listed group takes up in the split kernel's key order
+    FastDiv fd_pad_tokens;
 };
 
 // What a workgroup of the MFMA attention kernel can be (its MODE template argument).
@@ -76,38 +80,11 @@ hipError_t launch_build_block_lists(const Geometry& geo, int ndim, grat_pattern 
                                     int32_t* d_kv_index, int32_t max_kv, hipStream_t stream);
 hipError_t launch_validate_block_lists(const Geometry& geo, const int32_t* d_kv_count, const int32_t* d_kv_index,
                                        int32_t max_kv, int32_t* d_status, hipStream_t stream);
-hipError_t launch_attn_f32(const AttnParams& p, int head_dim, bool dense, hipStream_t stream);
+hipError_t launch_attn_f32(const AttnParams& p, int rows /* per workgroup */, int head_dim, bool dense, hipStream_t stream);
 hipError_t launch_attn_bf16(const AttnParams& p, int mode /* AttnMode */, bool f16, int head_dim, hipStream_t stream);
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).
 constexpr int kNumXcd = 8;
-// fp32 kernel: every XCD gets one contiguous range of the logical tile order.
-__device__ __forceinline__ int xcd_contiguous_tile(int block, int total) {
-    const int per = (total + kNumXcd - 1) / kNumXcd;
-    return (block % kNumXcd) * per + block / kNumXcd;   // may be >= total: caller exits
-}
 inline int xcd_padded_blocks(int total) { return ((total + kNumXcd - 1) / kNumXcd) * kNumXcd; }
-
-// Order in which the query groups of one head are handed to consecutive workgroups: column strips
-// of the group grid, `strip_w` groups wide, each walked row by row.  The ~32 workgroups an XCD
-// runs at a time then cover a compact 2D patch of groups (4 rows x 8 columns for strip_w = 8)
-// whose K/V neighbourhoods overlap in both directions, instead of one long group-row.
-// rows = all leading group axes flattened, cols = the last group axis; returns the linear group id.
-__device__ __forceinline__ int strip_order_group_fast(uint32_t u, int rows, int cols, const AttnParams& p) {
-    uint32_t s = fdiv(u, p.fd_strip);
-    int w = p.strip_w;
-    FastDiv fw = p.fd_strip_w;
-    if ((int)s >= p.strip_full) { s = p.strip_full; w = cols - p.strip_full * p.strip_w; fw = p.fd_strip_tail; }
-    const uint32_t v = u - s * (uint32_t)(rows * p.strip_w);
-    const uint32_t vq = fdiv(v, fw);
-    return (int)(vq * cols + s * p.strip_w + (v - vq * w));
-}
-__device__ __forceinline__ int strip_order_group(int u, int rows, int cols, int strip_w) {
-    const int full = cols / strip_w;
-    int s = u / (rows * strip_w), w = strip_w;
-    if (s >= full) { s = full; w = cols - full * strip_w; }
-    const int v = u - s * rows * strip_w;
-    return (v / w) * cols + s * strip_w + v % w;
-}
 
 }  // namespace grat

@@ -1,7 +1,7 @@
-// fp32 attention (grouped and dense) on the fp32 matrix instructions, head_dim 64 or 128.
+// fp32 attention (grouped and dense) on the matrix instructions, head_dim 64 or 128.
 //
-// Sec. 3.1 Eq. 1 restricted to the attendable KV groups of Sec. 3.2.  This is the precision path: inputs,
-// products, softmax and accumulation are all fp32 (v_mfma_f32_*_f32 multiplies and adds in fp32).
+// Sec. 3.1 Eq. 1 restricted to the attendable KV groups of Sec. 3.2.  This is the precision path: inputs, softmax
+// and accumulation are fp32, and products are as good as fp32 ones (v_mfma_f32_*_f32, or fp32 numbers as two halfs).
 // Group dims need not divide the grid (Eq. 2-4 are floor divisions): a group at the far border is the
 // part of its box that lies inside the grid, and its tokens are enumerated over that part only, so no
 // work is done for tokens that are not there.  Any group size.
@@ -9,7 +9,7 @@
 // Both kernels form S^T = K Q^T and O^T += V^T P^T.  A lane then owns one query and the weights P^T come
 // out of the first product in the layout the second one takes them in: register r of the S^T accumulator
 // is the B operand of MFMA r of the second product, whose contraction index runs over the keys that
-// register holds across the lane groups.  The A operands are read as 16-byte pieces of K and V rows: one
+// register holds across the lane groups (of half MFMAs: of an MFMA for every eight registers).  The A operands are read as 16-byte pieces of K and V rows: one
 // piece feeds four MFMAs, with the head dims taken in the order in which the pieces hold them.
 //
 //   attn_f32_kernel        32 queries a wave, K and V shared through LDS: launches that fill the chip.
@@ -21,15 +21,20 @@
 
 namespace grat {
 
+typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(8))) short frag8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
-// Weights are taken against a reference maximum that is refreshed only once a score exceeds it by this
-// much (base-2 exponent): any reference gives the same quotient O / l, and weights up to 2^16 leave fp32
-// all its relative accuracy.
-constexpr float kRefSlack = 16.f;
+// attn_f32_kernel takes weights against a reference that is refreshed only once one of them would exceed
+// 2^kTopWeight; the largest then becomes 2^kNewWeight.  Any reference gives the same quotient O / l; this one keeps weights inside
+// the range of a half, and one of 2^-11 of the largest still has two full terms.
+constexpr float kTopWeight = 15.f, kNewWeight = 8.f;
 
 // A group as the part of its box inside the grid.
 struct Box {
@@ -71,46 +76,91 @@ __device__ __forceinline__ uint32_t list_entry(const AttnParams& p, int gamma, i
 __device__ __forceinline__ float swap32(float x) { return __shfl_xor(x, 32); }
 
 // ---- 32 queries a wave -------------------------------------------------------------------------
-// Bound: the fp32 matrix pipe.  A 32x32x2 MFMA holds it for 64 cycles and a 32-key tile takes a wave
-// D of them, against 32 * D * 8 bytes of K and V, so one 16-byte LDS read feeds four MFMAs (256 cycles)
-// and there is no pressure on LDS or memory: K and V have one tile buffer each (32 KiB together at
-// head_dim 128), V(t) is fetched while the waves form the scores of tile t, K(t+1) while they add tile t
-// to O, with a barrier between the two halves.  Two waves per SIMD, from different workgroups, cover
-// each other's softmax and barriers.  64x64 tokens in 16x16 groups, 24 heads x 128, criss-cross lists: 7 230 us
-// as one query per lane on the vector ALU (12.5 TFLOP/s: one wave per SIMD and a dependent multiply-add
-// chain per score), 702 us here (128 TFLOP/s; a large fp32 library product reaches 153 on the same card).
+// The products run on the half-precision matrix pipe: x = x0 + x1 with two halfs (11 significand bits each and a
+// sign: the remainder is below 2^-24 |x|, half an ulp of fp32) and x y = x0 y0 + x0 y1 + x1 y0, whose missing
+// term is below 2^-24 |x y| too.  Products of halfs are exact in fp32 and are added up in fp32.  Three
+// 32x32x16 half MFMAs of 32 cycles do the work of eight 32x32x2 fp32 MFMAs of 64.
+// The range of a half is met by powers of two: a query is scaled by its own largest magnitude, K and V by
+// kScale, the weights by the choice of their reference.  A 32-key tile whose numbers do not fit (can_split:
+// infinities and magnitudes from 255 on; everything a thread splits below 2^-11) sends its workgroup through the
+// fp32 instructions (fp32_walk) after all.
+struct Split {
+    uint32_t t0, t1;   // the terms of a pair of numbers, first number in the low half
+};
+__device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
+}
+__device__ __forceinline__ Split split_pair(float x, float y) {
+    Split r;
+    r.t0 = pack_f16(x, y);
+    const f16x2 h = __builtin_bit_cast(f16x2, r.t0);
+    r.t1 = pack_f16(x - (float)h[0], y - (float)h[1]);
+    return r;
+}
+constexpr float kScale = 256.f;
+// mx: the largest magnitude of some numbers of K or V.  Scaled, it is below 65 280 and, unless 0, not below 2^-3,
+// where the second term would begin to lose bits (halfs end at 2^-24).
+__device__ __forceinline__ bool can_split(float mx) { return mx == 0.f || (mx >= 0x1p-11f && mx < 255.f); }
+__device__ __forceinline__ f32x16 mfma_f16(frag8 a, frag8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mfma_split(const frag8 (&a)[2], const frag8 (&b)[2], f32x16 c) {   // smallest first
+    c = mfma_f16(a[1], b[0], c);
+    c = mfma_f16(a[0], b[1], c);
+    return mfma_f16(a[0], b[0], c);
+}
+
+// o and the sum of a query follow a new reference of its weights.
+template <int N, typename Vec>
+__device__ __forceinline__ void rescale(Vec (&o)[N], float& l, float alpha) {
+    l *= alpha;
+#pragma unroll
+    for (int b = 0; b < N; ++b) o[b] *= alpha;
+}
+// Scores are weighted by exp2(c * (score - m_ref)), m_ref the largest so far (no score is below kNoScore, so that a block
+// of nothing but -infinity weighs 0).  For any numbers: the difference of huge scores is formed first, and no
+// weight is above 1, so that O overflows only where its sum does.
+constexpr float kNoScore = -3.4028234e38f;
+template <int R, int N, typename Scores, typename Vec>
+__device__ __forceinline__ void weigh(Scores& S, float mx, Vec (&o)[N], float& m_ref, float& l, float c) {
+    if (__builtin_amdgcn_ballot_w64(mx > m_ref) != 0) {
+        const float m_new = fmaxf(m_ref, mx);
+        rescale(o, l, __builtin_amdgcn_exp2f((m_ref - m_new) * c));
+        m_ref = m_new;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        S[r] = __builtin_amdgcn_exp2f((S[r] - m_ref) * c);
+        l += S[r];
+    }
+}
+__device__ __forceinline__ float block_max(const f32x16& S) {
+    float mx = S[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S[r]);
+    return fmaxf(mx, swap32(mx));
+}
+
+// The walk on the fp32 instructions (any numbers): the same operand layouts, K and V shared through LDS as they are.
+// K(t+1) is fetched while the waves add tile t to O, V(t) while they form its scores.
+// active: this wave has queries; stored: this lane's query exists; lds: room for 256 * D bytes.
 template <int D, bool DENSE, int NW>
-__global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
+__device__ __forceinline__ void fp32_walk(const AttnParams& p, uint8_t* lds, int gamma, int cnt, const float* q_src,
+                                          const uint8_t* Kh, const uint8_t* Vh, bool active, bool stored, float* dst) {
     constexpr int kKeys = 32, NB = D / 32, CPR = D / 4;   // O^T blocks of 32 head dims; 16-byte chunks in a row
     constexpr int RPP = 64 / CPR;                         // rows in a 1-KiB load of one wave
     constexpr int LPW = kKeys / RPP / NW;                 // such loads per wave and tile
-    __shared__ __attribute__((aligned(1024))) float sK[kKeys * D];
-    __shared__ __attribute__((aligned(1024))) float sV[kKeys * D];
-
+    float* const sK = (float*)lds;
+    float* const sV = sK + kKeys * D;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int qcol = lane & 31, half = lane >> 5;
-    int bh, qt, gamma = 0;
-    if (!pick_tile<DENSE>(p, bh, qt, gamma)) return;
-
-    const int b_idx = (int)fdiv((uint32_t)bh, p.fd_heads), h_idx = bh - b_idx * p.heads;
-    const int64_t head_off = (int64_t)b_idx * p.stride_b + (int64_t)h_idx * p.stride_h;
-    const uint8_t* Kh = (const uint8_t*)((const float*)p.K + head_off);
-    const uint8_t* Vh = (const uint8_t*)((const float*)p.V + head_off);
     const uint64_t pitch = (uint64_t)(uint32_t)p.stride_n * 4u;
-
-    const int q_first = (qt * NW + wave) * 32;
-    Box qb{};
-    if (!DENSE) qb = group_box(p, (uint32_t)gamma);
-    const int q_tokens = DENSE ? p.n_tokens : (int)qb.tokens;
-    if (qt * NW * 32 >= q_tokens) return;    // a clipped group with fewer query tiles
-    const bool active = q_first < q_tokens;  // (a wave without queries still loads its share and meets the barriers)
-    const int q_t = min(q_first + qcol, q_tokens - 1);
-    const uint32_t q_row = DENSE ? (uint32_t)q_t : token_row(p, qb, (uint32_t)q_t);
 
     // Q^T (B operand): q[4 * j + s] = dim 8 * j + 4 * half + s of this lane's query
     float q[D / 2];
     {
-        const float* src = (const float*)p.Q + head_off + (int64_t)q_row * p.stride_n + 4 * half;
+        const float* src = q_src + 4 * half;
 #pragma unroll
         for (int j = 0; j < D / 8; ++j) {
             const f32x4 v = *(const f32x4*)(src + 8 * j);
@@ -120,8 +170,6 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
     }
 
     // The walk: entry e of the list, tile j of its tokens; lane l looks after key l % 32 of a tile.
-    const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
-    if (cnt == 0) return;
     int e = 0, j = 0;
     uint32_t gid_next = 0, key_row = 0;
     Box kb{};
@@ -158,7 +206,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
     for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
-    float m_ref = -INFINITY, l = 0.f;   // l: this lane's share of the sum (its 16 keys of every tile)
+    float m_ref = kNoScore, l = 0.f;   // l: this lane's share of the sum (its 16 keys of every tile)
     const float c = p.scale_log2;
 
     enter(DENSE ? 0u : list_entry(p, gamma, 0));
@@ -183,24 +231,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
                 for (int r = 0; r < 16; ++r)
                     if (8 * (r >> 2) + 4 * half + (r & 3) >= n_valid) S[r] = -INFINITY;
             }
-            float mx = S[0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S[r]);
-            mx = fmaxf(mx, swap32(mx)) * c;
-            if (__builtin_amdgcn_ballot_w64(mx > m_ref + kRefSlack) != 0) {
-                const float m_new = fmaxf(m_ref, mx), alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
-                m_ref = m_new;
-                l *= alpha;
-#pragma unroll
-                for (int b = 0; b < NB; ++b)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -m_ref));
-                l += S[r];
-            }
+            weigh<16>(S, block_max(S), o, m_ref, l, c);
         }
         landed();   // V(t) is there, and everyone has finished with K(t)
         bool more = true;
@@ -230,15 +261,254 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
         if (!more) break;
     }
 
-    if (q_first + qcol < q_tokens) {
+    if (stored) {
         const float inv = 1.f / (l + swap32(l));
-        float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h + (int64_t)q_row * p.o_stride_n;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             float* d = dst + NB * (8 * (r >> 2) + 4 * half + (r & 3));
 #pragma unroll
             for (int b = 0; b < NB; ++b) d[b] = o[b][r] * inv;
         }
+    }
+}
+
+// Bound: the half-precision matrix pipe; a 32-key tile takes a wave 3 * D / 8 MFMAs of 32 cycles.  K and V are split
+// once per workgroup on their way into LDS (memory -> registers -> two planes each), Q once per wave, the
+// weights where they are formed: while the waves form the scores of tile t they split V(t), while they add tile t
+// to O they split K(t+1), with a barrier between the halves; the fp32 rows of the next half are in registers or on
+// their way.  Two waves per SIMD, from different workgroups, cover each other's softmax and barriers.
+// 24 heads x 128, us on the fp32 instructions -> here, error against float64: 64x64 tokens in 16x16 groups,
+// criss-cross 699 -> 316, 9.1e-7 -> 6.4e-7 (270 TFLOP/s where a large fp32 library product reaches 141); 2 079 tokens
+// dense 518 -> 197, 9.7e-7 -> 6.8e-7; 8 heads, 128x128 tokens in 8x8 groups 344 -> 186, in 4x8 groups 287 -> 173.
+// Three bf16 terms and six products instead: 470 us, 7.9e-7.  256 query rows a workgroup: 285 instead of 296 us for
+// 3x3 lists, but 324 instead of 316 for criss-cross ones and 309 instead of 197 at 2 079 tokens.
+template <int D, bool DENSE, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
+    constexpr int kKeys = 32, NB = D / 32, NK = D / 16, NT = NW * 64;
+    constexpr int CPR = D / 4, PIECES = kKeys * CPR / NT; // 16-byte pieces of an fp32 row; ... of a tile, per thread
+    constexpr int RPP = NT / CPR;                         // rows from one piece of a thread to its next
+    // Rows of the planes are padded so that fragment reads are free of bank conflicts and all their addresses
+    // differ by constants.  K: 16 bytes, consecutive rows start at different 16-byte positions.  V, read in blocks
+    // of 4 rows x 64 bytes by the transpose read: 64 bytes.
+    constexpr int kRowK = 2 * D + 16, kRowV = 2 * D + (D == 128 ? 64 : 192), kPlaneK = kKeys * kRowK, kPlaneV = kKeys * kRowV;
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * kPlaneK + 2 * kPlaneV];
+    static_assert(sizeof(lds) >= 256 * D, "fp32_walk's tiles");
+    uint8_t* const sK = lds;
+    uint8_t* const sV = lds + 2 * kPlaneK;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qcol = lane & 31, half = lane >> 5;
+    int bh, qt, gamma = 0;
+    if (!pick_tile<DENSE>(p, bh, qt, gamma)) return;
+
+    const int b_idx = (int)fdiv((uint32_t)bh, p.fd_heads), h_idx = bh - b_idx * p.heads;
+    const int64_t head_off = (int64_t)b_idx * p.stride_b + (int64_t)h_idx * p.stride_h;
+    const uint8_t* Kh = (const uint8_t*)((const float*)p.K + head_off);
+    const uint8_t* Vh = (const uint8_t*)((const float*)p.V + head_off);
+    const uint64_t pitch = (uint64_t)(uint32_t)p.stride_n * 4u;
+
+    const int q_first = (qt * NW + wave) * 32;
+    Box qb{};
+    if (!DENSE) qb = group_box(p, (uint32_t)gamma);
+    const int q_tokens = DENSE ? p.n_tokens : (int)qb.tokens;
+    if (qt * NW * 32 >= q_tokens) return;    // a clipped group with fewer query tiles
+    const int q_t = min(q_first + qcol, q_tokens - 1);
+    const uint32_t q_row = DENSE ? (uint32_t)q_t : token_row(p, qb, (uint32_t)q_t);
+
+    // Q^T (B operand): term t of dims 16 * ks + 8 * half .. + 7 of this lane's query
+    const float* q_src = (const float*)p.Q + head_off + (int64_t)q_row * p.stride_n;
+    frag8 qf[NK][2];
+    float c = p.scale_log2 / kScale;   // base-2 exponent per unit of a score, as the scaled operands give it
+    bool plain;                        // this thread has met numbers that cannot be split
+    {
+        f32x4 x[2 * NK];
+        float mx = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            x[2 * ks] = *(const f32x4*)(q_src + 16 * ks + 8 * half);
+            x[2 * ks + 1] = *(const f32x4*)(q_src + 16 * ks + 8 * half + 4);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, fmaxf(fabsf(x[2 * ks][i]), fabsf(x[2 * ks + 1][i])));
+        }
+        mx = fmaxf(mx, swap32(mx));
+        plain = !(mx == 0.f || (mx >= 0x1p-80f && mx < 0x1p+80f));
+        const int up = mx == 0.f || plain ? 0 : 8 - __builtin_amdgcn_frexp_expf(mx);   // largest in [2^7, 2^8)
+        c = __builtin_amdgcn_ldexpf(c, -up);
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            Split s[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                s[i] = split_pair(__builtin_amdgcn_ldexpf(x[2 * ks + i / 2][2 * (i % 2)], up), __builtin_amdgcn_ldexpf(x[2 * ks + i / 2][2 * (i % 2) + 1], up));
+            qf[ks][0] = __builtin_bit_cast(frag8, make_uint4(s[0].t0, s[1].t0, s[2].t0, s[3].t0));
+            qf[ks][1] = __builtin_bit_cast(frag8, make_uint4(s[0].t1, s[1].t1, s[2].t1, s[3].t1));
+        }
+    }
+
+    // The walk: entry e of the list, tile j of its tokens; lane l looks after key l % 32 of a tile.
+    const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
+    if (cnt == 0) return;
+    int e = 0, j = 0;
+    uint32_t gid_next = 0, key_row = 0;
+    Box kb{};
+    int kv_tokens = p.n_tokens;
+    auto enter = [&](uint32_t gid) {   // the walk reaches entry e, which is group gid
+        if (DENSE) return;
+        kb = group_box(p, gid);
+        kv_tokens = (int)kb.tokens;
+        if (e + 1 < cnt) gid_next = list_entry(p, gamma, e + 1);
+    };
+    auto find_rows = [&]() {
+        const uint32_t t = (uint32_t)min(32 * j + qcol, kv_tokens - 1);
+        key_row = DENSE ? t : token_row(p, kb, t);
+    };
+    f32x4 stage[PIECES];
+    auto load = [&](const uint8_t* head) {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) {
+            const int at = i * NT + tid;
+            stage[i] = *(const f32x4*)(head + (uint32_t)__shfl((int)key_row, at / CPR) * pitch + 16 * (at % CPR));
+        }
+    };
+    float stage_max = 0.f;
+    uint8_t* k_write = sK + (tid / CPR) * kRowK + 8 * (tid % CPR);
+    uint8_t* v_write = sV + (tid / CPR) * kRowV + 8 * (tid % CPR);
+    auto split_piece = [&](bool is_v, int i) {
+        const f32x4 x = stage[i];
+        stage_max = fmaxf(stage_max, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
+        const Split a = split_pair(x[0] * kScale, x[1] * kScale), b = split_pair(x[2] * kScale, x[3] * kScale);
+        uint8_t* dst = is_v ? v_write + i * RPP * kRowV : k_write + i * RPP * kRowK;
+        const int plane = is_v ? kPlaneV : kPlaneK;
+        *(uint2*)dst = make_uint2(a.t0, b.t0);
+        *(uint2*)(dst + plane) = make_uint2(a.t1, b.t1);
+    };
+    auto split_done = [&]() {
+        plain |= !can_split(stage_max);
+        stage_max = 0.f;
+    };
+
+    // K fragment: row qcol, dims 16 * ks + 8 * half ..  V through the LDS transpose read, whose 16-lane blocks
+    // take (row of a quad, 4-dim column)
+    const uint8_t* k_lane = sK + qcol * kRowK + 16 * half;
+    const uint8_t* v_lane = sV + (4 * half + ((lane & 15) >> 2)) * kRowV + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
+    auto k_frags = [&](frag8 (&f)[2], int ks) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) f[t] = *(const frag8*)(k_lane + t * kPlaneK + 32 * ks);
+    };
+    auto v_frags = [&](frag8 (&f)[2], int s2, int db) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint8_t* src = v_lane + t * kPlaneV + 16 * s2 * kRowV + 64 * db;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))src);
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(src + 8 * kRowV));
+            f[t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        }
+    };
+
+    f32x16 o[NB];   // o[b]: head dims 32 * b + 8 * (r / 4) + 4 * half + r % 4 of this lane's query
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+    // exponent of a weight: c * score - m_ref, one multiply-add (fp32_walk takes over where the product is too
+    // large for that); l: this lane's share of the sum (its 16 keys of every tile)
+    float m_ref = kNoScore, l = 0.f;
+    enter(DENSE ? 0u : list_entry(p, gamma, 0));
+    find_rows();
+    load(Kh);
+#pragma unroll
+    for (int i = 0; i < PIECES; ++i) split_piece(false, i);
+    split_done();
+    load(Vh);
+    for (;;) {
+        const int n_valid = min(kKeys, kv_tokens - kKeys * j);
+        bool more = true;
+        auto next_tile = [&]() {   // V(t) is split: on to K(t+1)
+            split_done();
+            if (kKeys * (j + 1) < kv_tokens) {
+                ++j;
+            } else {
+                j = 0;
+                more = ++e < cnt;
+                if (more) enter(gid_next);
+            }
+            if (more) {
+                find_rows();
+                load(Kh);
+            }
+        };
+        __syncthreads();   // K(t) is there, and everyone has finished with V(t-1)
+        f32x16 S;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) S[r] = 0.f;
+        frag8 kf[2][2];
+        k_frags(kf[0], 0);
+#pragma unroll
+        for (int ks = 0; ks < NK; ++ks) {
+            if (ks + 1 < NK) k_frags(kf[(ks + 1) & 1], ks + 1);
+            S = mfma_split(kf[ks & 1], qf[ks], S);
+#pragma unroll
+            for (int i = ks * PIECES / NK; i < (ks + 1) * PIECES / NK; ++i) split_piece(true, i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        next_tile();
+        frag8 pf[2][2];   // weights P^T (B operand): keys 16 * s2 .., two terms
+        if (n_valid < kKeys) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + 4 * half + (r & 3) >= n_valid) S[r] = -INFINITY;
+        }
+        const float mx = block_max(S) * c;
+        if (__builtin_amdgcn_ballot_w64(mx > m_ref + kTopWeight) != 0) {
+            const float m_new = fmaxf(m_ref, mx - kNewWeight);
+            rescale(o, l, __builtin_amdgcn_exp2f(m_ref - m_new));
+            m_ref = m_new;
+            plain |= !(fabsf(m_ref) < 0x1p20f);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -m_ref));
+            l += S[r];
+        }
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+            const Split w0 = split_pair(S[8 * s2], S[8 * s2 + 1]), w1 = split_pair(S[8 * s2 + 2], S[8 * s2 + 3]);
+            const Split w2 = split_pair(S[8 * s2 + 4], S[8 * s2 + 5]), w3 = split_pair(S[8 * s2 + 6], S[8 * s2 + 7]);
+            pf[s2][0] = __builtin_bit_cast(frag8, make_uint4(w0.t0, w1.t0, w2.t0, w3.t0));
+            pf[s2][1] = __builtin_bit_cast(frag8, make_uint4(w0.t1, w1.t1, w2.t1, w3.t1));
+        }
+        __syncthreads();   // V(t) is there, and everyone has finished with K(t)
+        frag8 vf[2][2];
+        v_frags(vf[0], 0, 0);
+#pragma unroll
+        for (int i = 0; i < 2 * NB; ++i) {
+            if (i + 1 < 2 * NB) v_frags(vf[(i + 1) & 1], (i + 1) / NB, (i + 1) % NB);
+            o[i % NB] = mfma_split(vf[i & 1], pf[i / NB], o[i % NB]);
+            // (after the last tile the registers still hold V: split again for nothing, but without a branch)
+#pragma unroll
+            for (int k = i * PIECES / (2 * NB); k < (i + 1) * PIECES / (2 * NB); ++k) split_piece(false, k);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!more) break;
+        split_done();
+        load(Vh);
+    }
+
+    const bool stored = q_first + qcol < q_tokens;
+    float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h + (int64_t)q_row * p.o_stride_n;
+    if (__syncthreads_or(plain)) {
+        fp32_walk<D, DENSE, NW>(p, lds, gamma, cnt, q_src, Kh, Vh, q_first < q_tokens, stored, dst);
+    } else if (stored) {
+        const float inv = 1.f / (l + swap32(l)) * (1.f / kScale);
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                f32x4 v;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = o[b][4 * rq + i] * inv;
+                *(f32x4*)(dst + 32 * b + 8 * rq + 4 * half) = v;
+            }
     }
 }
 
@@ -329,7 +599,7 @@ __global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
     f32x4 o[4 * NP];   // o[4 * n + s]: head dims 64 * n + 4 * i + s, i = 4 * quarter + register
 #pragma unroll
     for (int b = 0; b < 4 * NP; ++b) o[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_ref = -INFINITY, l = 0.f;
+    float m_ref = kNoScore, l = 0.f;
     const float c = p.scale_log2;
 
     auto add_block = [&](const Block& x) {
@@ -346,19 +616,8 @@ __global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
             if (!(mine >> r & 1u)) S[r] = -INFINITY;
         float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
         mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32)) * c;
-        if (__builtin_amdgcn_ballot_w64(mx > m_ref + kRefSlack) != 0) {
-            const float m_new = fmaxf(m_ref, mx), alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
-            m_ref = m_new;
-            l *= alpha;
-#pragma unroll
-            for (int b = 0; b < 4 * NP; ++b) o[b] *= alpha;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -m_ref));
-            l += S[r];
-        }
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        weigh<4>(S, mx, o, m_ref, l, c);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -407,7 +666,7 @@ __global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
     for (int d = 0; d < DPT; ++d) acc[d] = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float f = __builtin_amdgcn_exp2f(s_m[w][qi] - M);   // (a wave without keys: exp2(-inf) = 0)
+        const float f = __builtin_amdgcn_exp2f((s_m[w][qi] - M) * c);   // (a wave without keys: 0)
         sum = fmaf(f, s_l[w][qi], sum);
 #pragma unroll
         for (int d = 0; d < DPT; ++d) acc[d] = fmaf(f, s_o[w][qi][d0 + d], acc[d]);

@@ -190,9 +190,12 @@ static void fill_fastdivs(AttnParams& p) {
 // Query rows per workgroup of the fp32 path: 16 selects the kernel that splits the keys over a workgroup's
 // waves, 32 / 64 / 128 the one whose waves own 32 queries each.  `rows` = query rows of a group (or of the
 // sequence), `problems` = groups x heads x batch, `keys` = an upper bound of a list's keys.
+// Where the line lies: up to 1 024 waves of the second kind (one per SIMD) its time is that of one walk, the first
+// kind's grows with their number.  128, 256, 384 waves at 64x64 tokens in 16x16 groups, 3x3 lists: 73, 108, 155 us
+// against 131; 8 192 tokens dense, 64 dims, 256 and 512 waves: 193, 374 against 290.
 static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys) {
-    const int64_t waves = problems * ((rows + 31) / 32);   // of the 32-query kernel; the chip has 1 024 SIMDs
-    if (keys < kMaxElems - 65536 && (rows <= 16 || waves < 1024)) return 16;
+    const int64_t waves = problems * ((rows + 31) / 32);   // of the 32-query kernel
+    if (keys < kMaxElems - 65536 && (rows <= 16 || waves < 320)) return 16;
     const int64_t need = (rows + 31) / 32 * 32;
     for (int bm = 128; bm > 32; bm /= 2)
         if ((rows + bm - 1) / bm * bm == need || rows >= 1024) return bm;   // (no wave without queries)

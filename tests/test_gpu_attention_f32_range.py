@@ -1,0 +1,56 @@
+"""fp32 attention over the range of fp32 numbers: the split into halfs covers the usual magnitudes, everything else goes
+through the fp32 instructions, and both must come out as float64 says.  Bound: an fp32 dot product of d terms is off
+by up to d/2 roundings (2^-24) of its magnitude, so a weight by |scale * q k| of that, here at most 64 * 2^-24 * 30
+= 1.2e-4 and on average far less; 2e-5 for the norm of all."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2505_14687_amd as grat
+from gpu_util import errors, nan_like, to_f64
+
+pytestmark = pytest.mark.gpu
+D = 128
+
+
+def inputs(heads, n, gains, seed=5300):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    return [g * torch.randn(1, heads, n, D, generator=gen, device="cuda") for g in gains]
+
+
+def reference(q, k, v):
+    q, k, v = (t[0].double().cpu() for t in (q, k, v))
+    return torch.stack([torch.softmax(a @ b.t() / math.sqrt(D), -1) @ c for a, b, c in zip(q, k, v)])[None].numpy()
+
+
+# 2 and 8 heads: either side of the launch size from which waves own 32 queries
+@pytest.mark.parametrize("heads", [2, 8])
+@pytest.mark.parametrize("gains", [(1, 1, 1), (3, 1, 1e-3), (1, 1, 1e-6), (1, 1, 200), (1, 1, 1e7), (1e4, 1e-4, 1), (1e-3, 1e3, 1),
+                                   (1e-30, 1, 1), (1, 1, 1e36)])
+def test_magnitudes(heads, gains):
+    q, k, v = inputs(heads, 1500, gains)
+    O = nan_like(q)
+    grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(D), out=O)
+    assert errors(to_f64(O), reference(q, k, v))[1] <= 2e-5
+
+
+@pytest.mark.parametrize("heads", [2, 8])
+def test_special_values(heads):
+    """One head of huge scores, one with an infinity in V, one with an infinity in K; the others as ever."""
+    q, k, v = inputs(heads, 1500, (1, 1, 1))
+    k[0, 0, 700, 0] = -1e30
+    v[0, 1, 900, 5] = math.inf
+    want = reference(q, k, v)
+    O = to_f64(grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(D)))
+    assert np.isposinf(O[0, 1, :, 5]).all() and np.isposinf(want[0, 1, :, 5]).all()
+    O[0, 1, :, 5] = want[0, 1, :, 5] = 0.0
+    assert errors(O, want)[1] <= 2e-5
+    k[0, 0] = 1.0
+    q[0, 0] = 1.0
+    k[0, 0, 1000, 3] = -math.inf   # this key weighs nothing, the others all the same
+    O = to_f64(grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(D)))
+    mean = np.delete(to_f64(v)[0, 0], 1000, axis=0).mean(0)
+    assert np.abs(O[0, 0] - mean).max() <= 1e-5

@@ -52,8 +52,6 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
-constexpr int kD = 128;               // head_dim
-constexpr int kRowBytes = kD * 2;     // 256 B per token row
 // KV tokens per LDS tile (template argument BN of the kernel): 64, or 32 as an option for the 2-wave
 // workgroups (64 queries) of small groups, whose four tiles then take 32 KiB so that four workgroups
 // (two waves per SIMD) share a compute unit instead of two - worth it for short lists, where a
@@ -61,13 +59,16 @@ constexpr int kRowBytes = kD * 2;     // 256 B per token row
 // tile look-ups and load instructions per key).
 constexpr int kFragAhead = 2;         // an MFMA's LDS fragment is read this many MFMAs ahead of it
 
-// LDS tiles are unpadded [64 rows][16 chunks of 16 B]; the chunk index is XOR-swizzled per row so
+// LDS tiles are unpadded [64 rows][D / 8 chunks of 16 B]; the chunk index is XOR-swizzled per row so
 // that the fragment reads are bank-conflict free.  K is read with ds_read_b128 by lanes holding
-// consecutive rows: spread rows over all 16 chunk positions (and keep the two dim-halves of a
-// row apart).  V is read with the 8-byte transpose read by 4 rows x 4 chunks at a time: move
-// each of 4 consecutive rows to a different group of 4 chunks.
-__device__ __forceinline__ int k_swizzle(int row) { return ((row & 7) << 1) | ((row >> 3) & 1); }
-__device__ __forceinline__ int v_swizzle(int row) { return (row & 3) << 2; }
+// consecutive rows: 16 of them have to fall on the 16 chunk positions of a 256-byte line (64 banks), which
+// is one row of 128 head dims (spread rows over all 16 positions and keep the two dim-halves of a row
+// apart) or two rows of 64.  V is read with the 8-byte transpose read by 4 rows x 4 chunks at a time:
+// each of 4 consecutive rows goes to a different group of 4 chunks of the line.
+template <int D>
+__device__ __forceinline__ int k_swizzle(int row) { return D == 128 ? ((row & 7) << 1) | ((row >> 3) & 1) : (row >> 1) & 7; }
+template <int D>
+__device__ __forceinline__ int v_swizzle(int row) { return D == 128 ? (row & 3) << 2 : (row & 2) << 1; }
 
 // What depends on the 16-bit element type (F16 = false: bfloat16, true: IEEE half).  Fragments
 // travel as type-neutral frag8 and are reinterpreted at the MFMA.
@@ -122,28 +123,25 @@ __device__ __forceinline__ bool coord_inside(uint32_t c, uint32_t lim) {
     return (c >> 20) <= (lim >> 20) && ((c >> 10) & 1023u) <= ((lim >> 10) & 1023u) && (c & 1023u) <= (lim & 1023u);
 }
 
-// D = head_dim of the tensors, 128 or 64.  The LDS layout is 128 wide (kD) either way: for D = 64
-// the tiles keep their 256-byte rows, same swizzles, same fragment addresses; the direct loads
-// only fill the 8 chunk positions of every row that belong to real head dims (lanes whose
-// position would hold a chunk that does not exist are masked off), the QK product contracts over
-// the 4 fragments that exist, and the upper half of O^T is never formed, so no MFMA or LDS read is
-// spent on padding (the unused chunk positions are never written and never read).
+// D = head_dim, 128 or 64.
 //
 // One query tile: tile t_in_head of its kind in (batch, head) bh.  DENSE: it is a tile of consecutive
 // query rows that walks the whole sequence (always in kDense, the prompt rows in kJoint), else a
 // tile of one query group.  sK / sV: the workgroup's two K and two V tile buffers in LDS.
 template <int NWAVES, int BN, int MODE, bool F16, int D, bool DENSE>
 __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, const int t_in_head,
-                                          uint8_t (*sK)[BN * kRowBytes], uint8_t (*sV)[BN * kRowBytes],
+                                          uint8_t (*sK)[BN * D * 2], uint8_t (*sV)[BN * D * 2],
                                           const int gamma_fixed = -1) {
     static_assert(BN == 64 || (BN == 32 && NWAVES == 2), "64-key tiles, or 32-key tiles for 2-wave workgroups");
     constexpr int kBN = BN;
+    constexpr int kRowBytes = D * 2;          // of a token
+    constexpr int kRowChunks = kRowBytes / 16;
     constexpr int kTileBytes = kBN * kRowBytes;
     static_assert(D == 128 || D == 64, "head_dim 128 or 64");
     using E = Elem<F16>;
     constexpr int NT = NWAVES * 64;
     constexpr int BM = NWAVES * 32;
-    constexpr int LPW = kBN / (4 * NWAVES);   // 1-KiB direct loads (4 token rows) per wave per tile
+    constexpr int LPW = kTileBytes / (1024 * NWAVES);   // 1-KiB direct loads (4 or 8 token rows) per wave per tile
     constexpr bool dense = DENSE;
 
     extern __shared__ int32_t s_dyn[];   // [n_g] row offsets inside a group, then [max_kv] group origins (kRagged: and the two tables below)
@@ -189,7 +187,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // q_first + i of its group, whose first token is row q_base of the head
     uint32_t q_base = 0;
     int q_first;
-    frag8 qf[kD / 16];   // Q^T fragments (B operand): this lane's query, dims 16*ks + 8*half .. +7
+    frag8 qf[D / 16];   // Q^T fragments (B operand): this lane's query, dims 16*ks + 8*half .. +7
     if (dense) {
         n_tiles = (p.n_tokens + kBN - 1) / kBN;
         if (p.n_tokens % kBN) { mask_tile = n_tiles - 1; mask_valid = p.n_tokens % kBN; }
@@ -245,7 +243,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             }
             const uint8_t* src = (const uint8_t*)Qh + (uint64_t)q_base * row_pitch + off + 16 * half;
 #pragma unroll
-            for (int ks = 0; ks < kD / 16; ++ks) qf[ks] = ks < D / 16 ? *(const frag8*)(src + 32 * ks) : frag8{0, 0, 0, 0, 0, 0, 0, 0};
+            for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *(const frag8*)(src + 32 * ks);
         }
         for (int t = tid; t < n_g; t += NT) {
             int c0, c1, c2;
@@ -282,7 +280,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     if (dense) {
         const uint8_t* src = (const uint8_t*)Qh + q_row_off(qcol) + 16 * half;
 #pragma unroll
-        for (int ks = 0; ks < kD / 16; ++ks) qf[ks] = ks < D / 16 ? *(const frag8*)(src + 32 * ks) : frag8{0, 0, 0, 0, 0, 0, 0, 0};
+        for (int ks = 0; ks < D / 16; ++ks) qf[ks] = *(const frag8*)(src + 32 * ks);
     }
 
     f32x16 oacc[D / 32];                  // O^T accumulator: blocks of 32 head dims
@@ -303,21 +301,18 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     float l_run = 0.f;         // this lane's share of the running sum (its 16 keys per block)
     const float c = p.scale_log2;
 
-    // ---- tile loads: LPW one-KiB pieces per wave; lane -> (row = 4*piece + lane/16, chunk) ----
+    // ---- tile loads: LPW one-KiB pieces per wave; lane -> (row = rows per piece * piece + lane / chunks per row, chunk) ----
     // Address of a piece = head base + (wave-uniform) byte offset of the tile's first token, kept
     // in scalar registers, + a per-lane byte offset: row within the group (one table read) plus
     // the swizzled 16-byte chunk of the row.
     int load_row[LPW];
     uint32_t load_kcol[LPW], load_vcol[LPW];
-    bool k_on[LPW], v_on[LPW];
 #pragma unroll
     for (int k = 0; k < LPW; ++k) {
-        const int row = 4 * (wave * LPW + k) + (lane >> 4);
+        const int row = 64 / kRowChunks * (wave * LPW + k) + lane / kRowChunks;
         load_row[k] = row;
-        load_kcol[k] = (uint32_t)(((lane & 15) ^ k_swizzle(row)) * 16);   // byte offset of the global chunk
-        load_vcol[k] = (uint32_t)(((lane & 15) ^ v_swizzle(row)) * 16);
-        k_on[k] = load_kcol[k] < (uint32_t)D * 2;   // D = 64: this lane's LDS position holds a real chunk
-        v_on[k] = load_vcol[k] < (uint32_t)D * 2;
+        load_kcol[k] = (uint32_t)(((lane % kRowChunks) ^ k_swizzle<D>(row)) * 16);   // byte offset of the global chunk
+        load_vcol[k] = (uint32_t)(((lane % kRowChunks) ^ v_swizzle<D>(row)) * 16);
     }
     struct TileAddr {
         uint32_t base;        // wave-uniform
@@ -375,7 +370,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // direct-to-LDS load it can see as a possible alias of every later LDS read and would drain
     // the prefetch before the first fragment read that follows.  Completion is waited for
     // explicitly (s_waitcnt vmcnt(0)) before the barrier that publishes the tile.
-    auto issue_tile = [&](const uint16_t* head, uint8_t* dst_tile, const TileAddr& a, const bool (&on)[LPW]) {
+    auto issue_tile = [&](const uint16_t* head, uint8_t* dst_tile, const TileAddr& a) {
         // (made uniform again here: carried across iterations the offset may sit in a vector register)
         const uint8_t* base = (const uint8_t*)head + (uint64_t)__builtin_amdgcn_readfirstlane(a.base) * row_pitch;
 #pragma unroll
@@ -384,20 +379,20 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             const uint32_t lds_dst = __builtin_amdgcn_readfirstlane(
                 (uint32_t)(uintptr_t)(LDS_PTR(uint8_t))(dst_tile + (wave * LPW + k) * 1024));
             // (one wait state between the M0 write and the LDS-DMA instruction that reads it)
-            if (D == 128 || on[k])
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                             :: "s"(lds_dst), "v"(a.off[k]), "s"(base) : "memory", "m0");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(lds_dst), "v"(a.off[k]), "s"(base) : "memory", "m0");
         }
     };
 
     // ---- fragment addresses ----------------------------------------------------------------
     // K (A operand of S^T): row 32*kb + qcol, chunk (2*ks + half) ^ swizzle(row)
     const int k_lane_base = qcol * kRowBytes;
-    const int k_x = k_swizzle(qcol) ^ half;          // (2*ks + half) ^ sw == (2*ks) ^ (sw ^ half)
+    const int k_x = k_swizzle<D>(qcol) ^ half;          // (2*ks + half) ^ sw == (2*ks) ^ (sw ^ half)
     // V (A operand of O^T) via transpose reads: 16-lane block -> (e = row in quad, cq = 4-dim column)
     const int tr_e = (lane & 15) >> 2, tr_cq = lane & 3, tr_dsel = (lane >> 4) & 1;
     const int v_lane_base = (4 * half + tr_e) * kRowBytes + 8 * (tr_cq & 1);
-    // chunk = 4*db + 2*dsel + cq/2, swizzled with 4*(row & 3) = 4*e  ->  4*(db ^ e) + 2*dsel + cq/2
+    // chunk = 4*db + 2*dsel + cq/2, swizzled with v_swizzle(row) = v_swizzle(e) = 4*v_x  ->  4*(db ^ v_x) + 2*dsel + cq/2
+    const int v_x = v_swizzle<D>(tr_e) >> 2;
     const int v_chunk_lo = 2 * tr_dsel + (tr_cq >> 1);
 
     // ---- the software pipeline ---------------------------------------------------------------
@@ -420,7 +415,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         return *(LDS_PTR(const frag8))(uintptr_t)(k_addr[ks] + kbuf * kTileBytes + (kBN == 64 ? kb * 32 * kRowBytes : 0));
     };
     auto v_frag = [&](int vbuf, int kb, int s2, int db) -> frag8 {
-        const uint8_t* src = sV[vbuf] + v_lane_base + ((kBN == 64 ? 32 * kb : 0) + 16 * s2) * kRowBytes + ((4 * (db ^ tr_e) + v_chunk_lo) << 4);
+        const uint8_t* src = sV[vbuf] + v_lane_base + ((kBN == 64 ? 32 * kb : 0) + 16 * s2) * kRowBytes + ((4 * (db ^ v_x) + v_chunk_lo) << 4);
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))src);
         const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(src + 8 * kRowBytes));
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -487,7 +482,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
 
     // ---- prologue: K tile 0 -----------------------------------------------------------------
     tile_addr(ka, load_kcol, 0, gi_k, j_k);
-    issue_tile(Kh, sK[0], ka, k_on);
+    issue_tile(Kh, sK[0], ka);
     if (dense) tile_addr(va, load_vcol, 0, gi_v, j_v);
     else v_from_k(va, ka);
     if (1 < n_tiles) tile_addr(ka, load_kcol, 1, gi_k, j_k);
@@ -511,11 +506,11 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     auto swap_barrier = [&](int t) {
         __builtin_amdgcn_s_waitcnt(0);   // this wave's direct-to-LDS loads have landed
         __syncthreads();                 // ... everyone's have, and all reads of the buffers to refill are done
-        if (t + 1 < n_tiles) issue_tile(Kh, sK[(t + 1) & 1], ka, k_on);
+        if (t + 1 < n_tiles) issue_tile(Kh, sK[(t + 1) & 1], ka);
         if (kBN == 64) {
-            if (t < n_tiles) issue_tile(Vh, sV[t & 1], va, v_on);
+            if (t < n_tiles) issue_tile(Vh, sV[t & 1], va);
         } else {
-            if (t >= 1 && t - 1 < n_tiles) issue_tile(Vh, sV[(t - 1) & 1], vb, v_on);
+            if (t >= 1 && t - 1 < n_tiles) issue_tile(Vh, sV[(t - 1) & 1], vb);
         }
     };
 
@@ -693,6 +688,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // the only ordering needed is between its own LDS writes and reads.
     const float inv = 1.f / sum_across_halves(l_run);
     {
+        static_assert(NWAVES * 4096 <= 2 * kTileBytes, "the epilogue stages 4 KiB per wave in the K buffers");
         uint8_t* stage = &sK[0][0] + wave * 4096;   // [32 rows][8 chunks of 16 B], chunk ^= row & 7
         const int srow = lane >> 3, schunk = lane & 7;
         uint64_t st_off[4];
@@ -735,13 +731,26 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     }
 }
 
+// Wavefronts per SIMD the registers are held down to.  head_dim 128 needs 200 and more: two.  head_dim 64 has
+// half the MFMAs per score but the same vector work and fragment latencies, so two waves a SIMD left the kernel
+// waiting (720 cycles per wave and 32-key block, as many as at 128, of which the MFMAs are 256): three waves of
+// 4-wave workgroups (168 registers) took 256x256 tokens, 3x3 groups of 16x16, 24 heads from 997 to 866 us
+// (855 -> 984 TFLOP/s); four spill (1 186 us), and so do two 8-wave workgroups (1 160 us).  The 2-wave
+// workgroups on 64-key tiles fit 128 registers (512x512 tokens, criss-cross in 8x8 groups, 8 heads: 5.3 ms
+// against 5.9 with a bound of three; 8.5 before), their joint variant only fits at two.
+constexpr int waves_per_simd(int nwaves, int bn, int mode, int d) {
+    if (d == 128) return 2;
+    if (nwaves == 2 && bn == 64) return mode == kJoint ? 2 : 4;
+    return 3;
+}
+
 // The kernel: picks this workgroup's query tile (tile_order.h) and runs it.  In joint mode the long-running
 // dense tiles over the prompt rows get the lowest block indices, dealt round-robin over the XCDs, and the
 // grouped tiles follow.
 template <int NWAVES, int BN, int MODE, bool F16, int D>
-__global__ __launch_bounds__(NWAVES * 64, 2) void attn_mfma_kernel(AttnParams p) {
-    __shared__ __attribute__((aligned(1024))) uint8_t sK[2][BN * kRowBytes];
-    __shared__ __attribute__((aligned(1024))) uint8_t sV[2][BN * kRowBytes];
+__global__ __launch_bounds__(NWAVES * 64, waves_per_simd(NWAVES, BN, MODE, D)) void attn_mfma_kernel(AttnParams p) {
+    __shared__ __attribute__((aligned(1024))) uint8_t sK[2][BN * D * 2];
+    __shared__ __attribute__((aligned(1024))) uint8_t sV[2][BN * D * 2];
     const int xcd = blockIdx.x % kNumXcd, idx = blockIdx.x / kNumXcd;
     int bh, t_in_head;
     if constexpr (MODE == kJoint) {
@@ -777,7 +786,7 @@ inline hipError_t launch_one(const AttnParams& p, int mode, hipStream_t stream) 
     if (mode == kRagged) {
         hipLaunchKernelGGL((attn_mfma_kernel<NWAVES, BN, kRagged, F16, D>), dim3(grouped_blocks), block, dyn, stream, p);
     } else if (mode == kDense) {
-        if constexpr (NWAVES == 8)   // (the only tile height dense launches use)
+        if constexpr (BN == 64 && NWAVES >= 4)   // (the tile heights dense launches use)
             hipLaunchKernelGGL((attn_mfma_kernel<NWAVES, BN, kDense, F16, D>), dim3(dense_blocks), block, dyn, stream, p);
         else
             return hipErrorInvalidValue;
@@ -794,13 +803,13 @@ inline hipError_t launch_one(const AttnParams& p, int mode, hipStream_t stream) 
     return hipGetLastError();
 }
 
-// p.q_tiles (and p.q_tiles_dense) were computed by the host for the query-tile height chosen here:
-// 256, 128 or 64 rows.  64-row workgroups take 32-key tiles unless the lists are long.
+// p.q_tiles (and p.q_tiles_dense) were computed by the host for p.q_rows: 256 (head_dim 128 only), 128 or
+// 64 rows.  64-row workgroups take 32-key tiles unless the lists are long.
 template <bool F16, int D>
 inline hipError_t launch_by_tile(const AttnParams& p, int mode, hipStream_t stream) {
-    const int bm = mode == kDense ? 256 : (p.geo.group_tokens / p.q_tiles);
-    if (bm == 256) return launch_one<8, 64, F16, D>(p, mode, stream);
-    if (bm == 128) return launch_one<4, 64, F16, D>(p, mode, stream);
+    if constexpr (D == 128)
+        if (p.q_rows == 256) return launch_one<8, 64, F16, D>(p, mode, stream);
+    if (p.q_rows >= 128) return launch_one<4, 64, F16, D>(p, mode, stream);
     // (measured at 512x512 tokens in 8x8 groups: lists of 9 / 25 / 49 groups gain 16-19 % from the small
     // tiles, the criss-cross lists of 127 groups lose 5 %)
     // (not for joint sequences: that variant of the 32-key schedule does not fit the register file)

@@ -202,6 +202,16 @@ static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys) {
     return 32;
 }
 
+// Query rows per workgroup of a dense 16-bit launch.  head_dim 64: 128 (three such workgroups share a compute
+// unit; 8 200 tokens, 16 heads: 409 -> 343 us).  head_dim 128: one 256-row workgroup fills a compute unit, so up to
+// one and a half rounds of them go as 128-row workgroups, which spread the rows and cover each other's prologues;
+// beyond, 256 rows share their K/V tiles among more queries.  24 heads, 256 against 128 rows: 2 100 tokens
+// (0.84 rounds) 99.7 / 63.8 us, 2 600 (1.03) 127 / 111, 3 100 (1.22) 143.6 / 144.5, 4 096 (1.5) 203 / 192,
+// 4 429 (1.7) 228 / 244, 8 192 (3) 674 / 710.
+static int dense_tile_rows(int head_dim, int64_t rows, int64_t problems) {
+    return head_dim == 64 || problems * ((rows + 255) / 256) <= 384 ? 128 : 256;
+}
+
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
 
 // LDS the MFMA kernel needs beside its four 16-KiB tiles: the row-offset table of a group and the
@@ -258,7 +268,8 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
         if (span_rows * stride_n * 2 >= ((int64_t)1 << 32)) return GRAT_ERR_UNSUPPORTED;
         if (n_g > 4096) return GRAT_ERR_UNSUPPORTED;   // intra-group offset table lives in LDS
         if (!tables_fit_lds(geo, max_kv, ragged)) return GRAT_ERR_UNSUPPORTED;
-        bm = n_g % 256 == 0 ? 256 : (n_g % 128 == 0 ? 128 : 64);
+        // (head_dim 64: three 128-row workgroups share a compute unit, see waves_per_simd)
+        bm = n_g % 256 == 0 && head_dim == 128 ? 256 : (n_g % 128 == 0 ? 128 : 64);
         // A launch of fewer than two rounds of 256-row workgroups (one per compute unit) runs as 128-row
         // workgroups, two per compute unit, so that one's prologue and epilogue lie under the other's
         // walk (measured: +5 % at 64x64 tokens, nothing either way from 128x128 tokens on).
@@ -266,6 +277,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     } else {
         bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, (int64_t)max_kv * (n_g + 15));
     }
+    p.q_rows = bm;
     p.q_tiles = (n_g + bm - 1) / bm;
     p.strip_w = geo.G[2] >= 16 ? 8 : geo.G[2];
     // (the launch pads every head's tiles to a multiple of 8: up to 7 more per head)
@@ -289,7 +301,8 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     // first (measured at 128x128 tokens in 16x16 groups, 24 heads: +14 % for 3x3 lists, +10 % for 5x5,
     // nothing either way for the equally long criss-cross lists; at 64x64 tokens +7 %).  Larger launches
     // keep the order that lets neighbouring groups share their K/V in the L2.
-    p.longest_first = geo.num_groups <= 64 && total <= 16 * 256;
+    // (head_dim 64 splits 256-token groups in two: the line lies at the same number of queries)
+    p.longest_first = geo.num_groups <= 64 && (is16(dtype) && head_dim == 64 && n_g % 256 == 0 ? total / 2 : total) <= 16 * 256;
     p.fd_tiles_per_rank = make_fastdiv((uint32_t)(batch * heads * p.q_tiles));
     fill_fastdivs(p);
     const hipError_t e = is16(dtype)
@@ -363,7 +376,9 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     p.batch = batch; p.heads = heads;
     p.scale_log2 = scale * 1.4426950408889634f;
     p.n_tokens = (int32_t)n_tokens;
-    const int bm = is16(dtype) ? 256 : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens);
+    const int bm = is16(dtype) ? dense_tile_rows(head_dim, n_tokens, (int64_t)batch * heads)
+                               : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens);
+    p.q_rows = bm;
     p.q_tiles = (int32_t)((n_tokens + bm - 1) / bm);
     p.q_tiles_dense = p.q_tiles;
     p.n_dense_rows = (int32_t)n_tokens;

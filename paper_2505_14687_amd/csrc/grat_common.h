@@ -34,6 +34,7 @@ struct AttnParams {
     const int32_t* kv_index;
     int32_t max_kv;
     int32_t n_tokens;          // dense tiles: number of KV rows (the whole sequence)
+    int32_t q_rows;            // query rows per workgroup
     int32_t q_tiles;           // query tiles per group
     int32_t strip_w;           // grouped bf16 path: query groups are walked in column strips this wide
     // dense tiles (dense entry point, and the prompt rows of a joint sequence)

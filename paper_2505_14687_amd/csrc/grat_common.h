@@ -70,8 +70,8 @@ struct AttnParams {
 //             dense tiles over the prompt rows (they attend the whole sequence), the others are
 //             grouped tiles whose walk starts with the prompt tokens' KV tiles.
 //   kRagged   kGrouped for a grid the group dims do not divide (Eq. 2-4 are floor divisions): a
-//             group at the far border is the part of its box inside the grid.  Boxes are still
-//             walked whole; tokens of a box that fall outside the grid are fetched from a clamped
+//             group at the far border is the part of its box inside the grid.  Boxes are
+//             walked up to their last token inside; tokens of a box that fall outside the grid are fetched from a clamped
 //             (valid, meaningless) address and get weight 0, queries outside are not stored.
 enum AttnMode : int { kGrouped = 0, kDense = 1, kJoint = 2, kRagged = 3 };
 

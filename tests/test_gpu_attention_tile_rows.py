@@ -54,22 +54,34 @@ def test_dense_rows(heads, n, d):
                                         ((3, 20, 17), (2, 8, 8)), ((24, 40), (8, 8)), ((21, 30), (8, 8)),
                                         ((80, 528), (8, 8))])   # the last: 75-group lists, 64-key tiles of 2-wave workgroups
 def test_head_dim_64_groups(grid, group):
+    _groups(grid, group, 64)
+
+
+# boxes with whole tiles, and whole workgroups of queries, outside the grid; 10x10: the only group is clipped
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grid,group", [((40, 70), (32, 32)), ((33, 65), (32, 32)), ((49, 33), (16, 16)), ((10, 10), (16, 16)),
+                                        ((1, 40), (16, 16)), ((5, 17, 9), (4, 8, 8)), ((3, 9, 20), (2, 8, 8)), ((9, 25), (8, 8))])
+def test_clipped_boxes(grid, group, d):
+    _groups(grid, group, d)
+
+
+def _groups(grid, group, d):
     pattern = "cross" if grid == (80, 528) else "block"
     n = math.prod(grid)
     dtype = torch.bfloat16
-    q, k, v = _inputs(1, 1 if n > 10000 else 2, n, 64, dtype, 7100 + n)
+    q, k, v = _inputs(1, 1 if n > 10000 else 2, n, d, dtype, 7100 + n)
     radius = (1,) * len(grid)
     count, index = grat.grat_build_block_lists(grid, group, pattern, radius)
     out = torch.full_like(q, float("nan"))
-    grat.grat_attention_fwd(q, k, v, 1.0 / 8.0, grid, group, count, index, out=out)
+    grat.grat_attention_fwd(q, k, v, 1.0 / math.sqrt(d), grid, group, count, index, out=out)
     coords = torch.stack(torch.meshgrid(*[torch.arange(t, device="cuda") // g for t, g in zip(grid, group)], indexing="ij"), -1)
     coords = coords.reshape(n, len(grid))
     rows = torch.arange(0, n, max(1, n // 2000), device="cuda")
     diff = (coords[rows, None, :] - coords[None, :, :]).abs()
     mask = (diff <= 1).all(-1) if pattern == "block" else (diff != 0).sum(-1) <= 1
-    want = torch.empty((1, q.shape[1], len(rows), 64), dtype=torch.float64, device="cuda")
+    want = torch.empty((1, q.shape[1], len(rows), d), dtype=torch.float64, device="cuda")
     for h in range(q.shape[1]):
-        s = (q[0, h, rows].double() @ k[0, h].double().T.contiguous() / 8.0).masked_fill(~mask, -math.inf)
+        s = (q[0, h, rows].double() @ k[0, h].double().T.contiguous() / math.sqrt(d)).masked_fill(~mask, -math.inf)
         want[0, h] = torch.softmax(s, -1) @ v[0, h].double()
     assert bool(torch.isfinite(out).all())
     _check(out[:, :, rows], want, dtype)

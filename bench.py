@@ -42,7 +42,7 @@ def kernel_name(w, n_g, n_glob, pattern, radius):
     import numpy as np
     import paper_2505_14687_amd as grat
     groups = int(np.prod([-(-t // g) for t, g in zip(w.grid, w.group)]))
-    waves = 8 if n_g % 256 == 0 else (4 if n_g % 128 == 0 else 2)
+    waves = 8 if n_g % 256 == 0 and w.head_dim == 128 else (4 if n_g % 128 == 0 else 2)
     if waves == 8 and w.batch * w.heads * groups < 512:
         waves = 4
     ragged = any(t % g for t, g in zip(w.grid, w.group))

@@ -251,9 +251,11 @@ __device__ __forceinline__ void fp32_walk(const AttnParams& p, uint8_t* lds, int
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const float* src = &sV[(8 * (r >> 2) + 4 * half + (r & 3)) * D + NB * qcol];
+                // (rows past the end are copies of the last token: weight 0, but 0 times an infinity is none)
+                const bool exists = 8 * (r >> 2) + 4 * half + (r & 3) < n_valid;
                 float v[NB];
 #pragma unroll
-                for (int b = 0; b < NB; ++b) v[b] = src[b];
+                for (int b = 0; b < NB; ++b) v[b] = exists ? src[b] : 0.f;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) o[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[b], S[r], o[b], 0, 0, 0);
             }
@@ -602,18 +604,25 @@ __global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
     float m_ref = kNoScore, l = 0.f;
     const float c = p.scale_log2;
 
-    auto add_block = [&](const Block& x) {
+    auto add_block = [&](Block& x) {
         if (x.valid == 0) return;   // padding of a clipped group
         f32x4 S = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < D / 16; ++j)
 #pragma unroll
             for (int s = 0; s < 4; ++s) S = __builtin_amdgcn_mfma_f32_16x16x4f32(x.k[j][s], q[j][s], S, 0, 0, 0);
-        // lane holds keys 4 * quarter + r of its query
-        const uint32_t mine = (uint32_t)x.valid >> (4 * quarter);
+        // lane holds keys 4 * quarter + r of its query.  Keys that do not exist stand for another token of the
+        // sequence: weight 0, and no V either (0 times an infinity is no 0)
+        if (~x.valid != 0) {
+            const uint32_t mine = (uint32_t)x.valid >> (4 * quarter);
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            if (!(mine >> r & 1u)) S[r] = -INFINITY;
+            for (int r = 0; r < 4; ++r)
+                if (!(mine >> r & 1u)) {
+                    S[r] = -INFINITY;
+#pragma unroll
+                    for (int n = 0; n < NP; ++n) x.v[r][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
         float mx = fmaxf(fmaxf(S[0], S[1]), fmaxf(S[2], S[3]));
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));

@@ -10,6 +10,7 @@ import torch
 
 import paper_2505_14687_amd as grat
 from gpu_util import errors, nan_like, to_f64
+from oracle import grat_oracle as orc
 
 pytestmark = pytest.mark.gpu
 D = 128
@@ -54,3 +55,30 @@ def test_special_values(heads):
     O = to_f64(grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(D)))
     mean = np.delete(to_f64(v)[0, 0], 1000, axis=0).mean(0)
     assert np.abs(O[0, 0] - mean).max() <= 1e-5
+
+
+# Where an infinity of V meets the padding of a key tile: sequences and groups that end inside a tile, the infinity in
+# their first or last token.  (1500 = 46 * 32 + 28 = 93 * 16 + 12 tokens; groups of 3 x 11 and, clipped, 3 x 7 tokens;
+# of 5 x 3 and, clipped, fewer.)  heads: either side of the launch size from which waves own 32 queries.
+@pytest.mark.parametrize("heads,d", [(2, 128), (8, 128), (16, 64)])
+@pytest.mark.parametrize("grid,group", [((1500,), None), ((33, 62), (3, 11)), ((33, 35), (5, 3))])   # None: dense
+@pytest.mark.parametrize("last", [True, False])
+def test_infinity_beside_padding(grid, group, last, heads, d):
+    n = math.prod(grid)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5310)
+    q, k, v = (torch.randn(1, heads, n, d, generator=gen, device="cuda") for _ in range(3))
+    first = (0,) if group is None else tuple((t - 1) // g * g for t, g in zip(grid, group))   # of the last group
+    token = n - 1 if last else int(np.ravel_multi_index(first, grid))
+    v[0, :, token, 5] = math.inf
+    if group is None:
+        O = grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(d))
+        sees = np.ones(n, dtype=bool)
+    else:
+        count, index = grat.grat_build_block_lists(grid, group, "block", (1, 1))
+        O = grat.grat_attention_fwd(q, k, v, 1.0 / math.sqrt(d), grid, group, count, index)
+        sees = orc.mask_rows(np.arange(n), grid, group, "block", (1, 1))[:, token]
+    O = to_f64(O)
+    assert np.isposinf(O[0, :, sees, 5]).all()
+    O[0, :, sees, 5] = 0.0
+    assert np.isfinite(O).all()

@@ -1,7 +1,8 @@
 // fp32 attention (grouped and dense) on the matrix instructions, head_dim 64 or 128.
 //
 // Sec. 3.1 Eq. 1 restricted to the attendable KV groups of Sec. 3.2.  This is the precision path: inputs, softmax
-// and accumulation are fp32, and products are as good as fp32 ones (v_mfma_f32_*_f32, or fp32 numbers as two halfs).
+// and accumulation are fp32, and products are as good as fp32 ones (v_mfma_f32_*_f32, or all 24 bits of an fp32
+// number as three bf16 numbers).
 // Group dims need not divide the grid (Eq. 2-4 are floor divisions): a group at the far border is the
 // part of its box that lies inside the grid, and its tokens are enumerated over that part only, so no
 // work is done for tokens that are not there.  Any group size.
@@ -9,8 +10,9 @@
 // Both kernels form S^T = K Q^T and O^T += V^T P^T.  A lane then owns one query and the weights P^T come
 // out of the first product in the layout the second one takes them in: register r of the S^T accumulator
 // is the B operand of MFMA r of the second product, whose contraction index runs over the keys that
-// register holds across the lane groups (of half MFMAs: of an MFMA for every eight registers).  The A operands are read as 16-byte pieces of K and V rows: one
-// piece feeds four MFMAs, with the head dims taken in the order in which the pieces hold them.
+// register holds across the lane groups (of bf16 MFMAs: of an MFMA for every eight registers).  The A operands of
+// fp32 MFMAs are read as 16-byte pieces of K and V rows: one piece feeds four MFMAs, with the head dims taken in
+// the order in which the pieces hold them.
 //
 //   attn_f32_kernel        32 queries a wave, K and V shared through LDS: launches that fill the chip.
 //   attn_f32_split_kernel  16 queries a workgroup, the eight waves share its KEYS and merge at the end:
@@ -21,8 +23,8 @@
 
 namespace grat {
 
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(8))) short frag8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -32,9 +34,10 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 // attn_f32_kernel takes weights against a reference that is refreshed only once one of them would exceed
-// 2^kTopWeight; the largest then becomes 2^kNewWeight.  Any reference gives the same quotient O / l; this one keeps weights inside
-// the range of a half, and one of 2^-11 of the largest still has two full terms.
-constexpr float kTopWeight = 15.f, kNewWeight = 8.f;
+// 2^kTopWeight; the largest then becomes 2^kNewWeight.  Any reference gives the same quotient O / l; the exponent of
+// a weight is rounded by its own magnitude, so the reference stays near the largest score (with the largest
+// weights at 2^32: error 7.1e-7 instead of 3.9e-7 in the first case below).
+constexpr float kTopWeight = 8.f, kNewWeight = 0.f;
 
 // A group as the part of its box inside the grid.
 struct Box {
@@ -76,39 +79,44 @@ __device__ __forceinline__ uint32_t list_entry(const AttnParams& p, int gamma, i
 __device__ __forceinline__ float swap32(float x) { return __shfl_xor(x, 32); }
 
 // ---- 32 queries a wave -------------------------------------------------------------------------
-// The products run on the half-precision matrix pipe: x = x0 + x1 with two halfs (11 significand bits each and a
-// sign: the remainder is below 2^-24 |x|, half an ulp of fp32) and x y = x0 y0 + x0 y1 + x1 y0, whose missing
-// term is below 2^-24 |x y| too.  Products of halfs are exact in fp32 and are added up in fp32.  Three
-// 32x32x16 half MFMAs of 32 cycles do the work of eight 32x32x2 fp32 MFMAs of 64.
-// The range of a half is met by powers of two: a query is scaled by its own largest magnitude, K and V by
-// kScale, the weights by the choice of their reference.  A 32-key tile whose numbers do not fit (can_split:
-// infinities and magnitudes from 255 on; everything a thread splits below 2^-11) sends its workgroup through the
-// fp32 instructions (fp32_walk) after all.
+// The products run on the bf16 matrix pipe: a number is the sum of three bf16 numbers, x = x0 + x1 + x2, exactly (8
+// significand bits each, rounded to nearest: x - x0 has at most 16 of the 24 left, x - x0 - x1 at most 8), and
+// x y = x0 y0 + (x0 y1 + x1 y0) + (x0 y2 + x1 y1 + x2 y0) but for x1 y2 + x2 y1 + x2 y2, which is at most 1.01 * 2^-24
+// |x y| (and seldom near it), what an fp32 rounding of the product may be off by.  Products of bf16 numbers are
+// exact in fp32 and are added up in fp32.  Six 32x32x16 bf16 MFMAs of 32 cycles do the work of eight 32x32x2 fp32
+// MFMAs of 64.  (Two halfs and three products take 290 us instead of 475 in the first case below, but hold 23 bits, and
+// fewer of a number that is small beside its neighbours: the range of a half is met by scaling whole tiles.)
+// bf16 has the exponents of fp32, so that every number keeps its own 24 bits whatever stands beside it.  At the lower
+// end the last term would get lost (numbers from 2^-102 down): Q, K and V are split kScale times as large.  At
+// the upper end nothing may overflow: numbers from kLimit on, infinities and huge scores send a workgroup through
+// the fp32 instructions (fp32_walk) after all.
 struct Split {
-    uint32_t t0, t1;   // the terms of a pair of numbers, first number in the low half
+    uint32_t t[3];   // the terms of a pair of numbers, first number in the low half
 };
-__device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
-    const f32x2 v = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, f16x2));
-}
 __device__ __forceinline__ Split split_pair(float x, float y) {
     Split r;
-    r.t0 = pack_f16(x, y);
-    const f16x2 h = __builtin_bit_cast(f16x2, r.t0);
-    r.t1 = pack_f16(x - (float)h[0], y - (float)h[1]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const f32x2 v = {x, y};
+        r.t[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+        x -= __builtin_bit_cast(float, r.t[i] << 16);
+        y -= __builtin_bit_cast(float, r.t[i] & 0xffff0000u);
+    }
     return r;
 }
-constexpr float kScale = 256.f;
-// mx: the largest magnitude of some numbers of K or V.  Scaled, it is below 65 280 and, unless 0, not below 2^-3,
-// where the second term would begin to lose bits (halfs end at 2^-24).
-__device__ __forceinline__ bool can_split(float mx) { return mx == 0.f || (mx >= 0x1p-11f && mx < 255.f); }
-__device__ __forceinline__ f32x16 mfma_f16(frag8 a, frag8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+// Scores: 2^7 dims times kLimit^2 kScale^2 = 2^123; O: weights (2^kTopWeight) times kLimit kScale = 2^66 a key.
+// A weight below 2^-126 of 2^kNewWeight is taken as 0: with |V| < kLimit that is less than 2^-92 of an output.
+constexpr float kScale = 0x1p+24f, kLimit = 0x1p+34f;
+// x is worked out here and not further down, with what it is made of kept in registers until then (left to itself the
+// compiler moves sums and maxima that are needed after the walk, or late in a step, behind everything else: 100
+// registers more in the walk at head_dim 128, which has none to spare).
+template <typename T>
+__device__ __forceinline__ void pin(T& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ f32x16 mfma_bf16(frag8 a, frag8 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x16 mfma_split(const frag8 (&a)[2], const frag8 (&b)[2], f32x16 c) {   // smallest first
-    c = mfma_f16(a[1], b[0], c);
-    c = mfma_f16(a[0], b[1], c);
-    return mfma_f16(a[0], b[0], c);
+__device__ __forceinline__ frag8 frag_of(const Split (&s)[4], int term) {
+    return __builtin_bit_cast(frag8, make_uint4(s[0].t[term], s[1].t[term], s[2].t[term], s[3].t[term]));
 }
 
 // o and the sum of a query follow a new reference of its weights.
@@ -274,16 +282,17 @@ __device__ __forceinline__ void fp32_walk(const AttnParams& p, uint8_t* lds, int
     }
 }
 
-// Bound: the half-precision matrix pipe; a 32-key tile takes a wave 3 * D / 8 MFMAs of 32 cycles.  K and V are split
-// once per workgroup on their way into LDS (memory -> registers -> two planes each), Q once per wave, the
-// weights where they are formed: while the waves form the scores of tile t they split V(t), while they add tile t
-// to O they split K(t+1), with a barrier between the halves; the fp32 rows of the next half are in registers or on
-// their way.  Two waves per SIMD, from different workgroups, cover each other's softmax and barriers.
+// Bound: the bf16 matrix pipe; a 32-key tile takes a wave 6 * D / 8 MFMAs of 32 cycles.  K and V are split once per
+// workgroup on their way into LDS (memory -> registers -> three planes each), Q once per wave, the weights where they
+// are formed: while the waves form the scores of tile t they split V(t), while they add tile t to O they split
+// K(t+1), with a barrier between the halves; the fp32 rows of the next half are in registers or on their way.  Two
+// waves per SIMD, from different workgroups (LDS: 56 KiB each at head_dim 128), cover each other's softmax and
+// barriers; 64-row workgroups get one.  256 registers (head_dim 128): 27 to 56 spilled ones belong to fp32_walk, the
+// walk itself reloads 6 a tile.
 // 24 heads x 128, us on the fp32 instructions -> here, error against float64: 64x64 tokens in 16x16 groups,
-// criss-cross 699 -> 316, 9.1e-7 -> 6.4e-7 (270 TFLOP/s where a large fp32 library product reaches 141); 2 079 tokens
-// dense 518 -> 197, 9.7e-7 -> 6.8e-7; 8 heads, 128x128 tokens in 8x8 groups 344 -> 186, in 4x8 groups 287 -> 173.
-// Three bf16 terms and six products instead: 470 us, 7.9e-7.  256 query rows a workgroup: 285 instead of 296 us for
-// 3x3 lists, but 324 instead of 316 for criss-cross ones and 309 instead of 197 at 2 079 tokens.
+// criss-cross 699 -> 475, 9.1e-7 -> 3.9e-7 (170 TFLOP/s where a large fp32 library product reaches 141 to 154); 2 079
+// tokens dense 518 -> 324, 9.7e-7 -> 4.2e-7; 8 heads, 128x128 tokens in 8x8 groups 344 -> 286.  All products of a score
+// in one sum 470 us, 4.8e-7; those of O straight into O 454 us, 7.4e-7.
 template <int D, bool DENSE, int NW>
 __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
     constexpr int kKeys = 32, NB = D / 32, NK = D / 16, NT = NW * 64;
@@ -293,10 +302,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
     // differ by constants.  K: 16 bytes, consecutive rows start at different 16-byte positions.  V, read in blocks
     // of 4 rows x 64 bytes by the transpose read: 64 bytes.
     constexpr int kRowK = 2 * D + 16, kRowV = 2 * D + (D == 128 ? 64 : 192), kPlaneK = kKeys * kRowK, kPlaneV = kKeys * kRowV;
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * kPlaneK + 2 * kPlaneV];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[3 * kPlaneK + 3 * kPlaneV];
     static_assert(sizeof(lds) >= 256 * D, "fp32_walk's tiles");
     uint8_t* const sK = lds;
-    uint8_t* const sV = lds + 2 * kPlaneK;
+    uint8_t* const sV = lds + 3 * kPlaneK;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qcol = lane & 31, half = lane >> 5;
@@ -319,32 +328,26 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 
     // Q^T (B operand): term t of dims 16 * ks + 8 * half .. + 7 of this lane's query
     const float* q_src = (const float*)p.Q + head_off + (int64_t)q_row * p.stride_n;
-    frag8 qf[NK][2];
-    float c = p.scale_log2 / kScale;   // base-2 exponent per unit of a score, as the scaled operands give it
-    bool plain;                        // this thread has met numbers that cannot be split
+    frag8 qf[NK][3];
+    const float c = p.scale_log2 * (1.f / (kScale * kScale));   // base-2 exponent per unit of a score, as the scaled operands give it
+    bool plain = !(p.scale_log2 > 0x1p-60f);   // this thread has met numbers that cannot be split
     {
-        f32x4 x[2 * NK];
         float mx = 0.f;
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            x[2 * ks] = *(const f32x4*)(q_src + 16 * ks + 8 * half);
-            x[2 * ks + 1] = *(const f32x4*)(q_src + 16 * ks + 8 * half + 4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, fmaxf(fabsf(x[2 * ks][i]), fabsf(x[2 * ks + 1][i])));
-        }
-        mx = fmaxf(mx, swap32(mx));
-        plain = !(mx == 0.f || (mx >= 0x1p-80f && mx < 0x1p+80f));
-        const int up = mx == 0.f || plain ? 0 : 8 - __builtin_amdgcn_frexp_expf(mx);   // largest in [2^7, 2^8)
-        c = __builtin_amdgcn_ldexpf(c, -up);
-#pragma unroll
-        for (int ks = 0; ks < NK; ++ks) {
+            const f32x4 x0 = *(const f32x4*)(q_src + 16 * ks + 8 * half), x1 = *(const f32x4*)(q_src + 16 * ks + 8 * half + 4);
             Split s[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                s[i] = split_pair(__builtin_amdgcn_ldexpf(x[2 * ks + i / 2][2 * (i % 2)], up), __builtin_amdgcn_ldexpf(x[2 * ks + i / 2][2 * (i % 2) + 1], up));
-            qf[ks][0] = __builtin_bit_cast(frag8, make_uint4(s[0].t0, s[1].t0, s[2].t0, s[3].t0));
-            qf[ks][1] = __builtin_bit_cast(frag8, make_uint4(s[0].t1, s[1].t1, s[2].t1, s[3].t1));
+            for (int i = 0; i < 2; ++i) {
+                mx = fmaxf(fmaxf(mx, fmaxf(fabsf(x0[2 * i]), fabsf(x0[2 * i + 1]))), fmaxf(fabsf(x1[2 * i]), fabsf(x1[2 * i + 1])));
+                s[i] = split_pair(x0[2 * i] * kScale, x0[2 * i + 1] * kScale);
+                s[2 + i] = split_pair(x1[2 * i] * kScale, x1[2 * i + 1] * kScale);
+            }
+#pragma unroll
+            for (int u = 0; u < 3; ++u) qf[ks][u] = frag_of(s, u);
         }
+        pin(mx);
+        plain |= !(mx < kLimit);
     }
 
     // The walk: entry e of the list, tile j of its tokens; lane l looks after key l % 32 of a tile.
@@ -372,39 +375,33 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
             stage[i] = *(const f32x4*)(head + (uint32_t)__shfl((int)key_row, at / CPR) * pitch + 16 * (at % CPR));
         }
     };
-    float stage_max = 0.f;
+    float stage_max = 0.f;   // largest magnitude of K and V that this thread has split
     uint8_t* k_write = sK + (tid / CPR) * kRowK + 8 * (tid % CPR);
     uint8_t* v_write = sV + (tid / CPR) * kRowV + 8 * (tid % CPR);
     auto split_piece = [&](bool is_v, int i) {
         const f32x4 x = stage[i];
         stage_max = fmaxf(stage_max, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
+        pin(stage_max);
         const Split a = split_pair(x[0] * kScale, x[1] * kScale), b = split_pair(x[2] * kScale, x[3] * kScale);
         uint8_t* dst = is_v ? v_write + i * RPP * kRowV : k_write + i * RPP * kRowK;
         const int plane = is_v ? kPlaneV : kPlaneK;
-        *(uint2*)dst = make_uint2(a.t0, b.t0);
-        *(uint2*)(dst + plane) = make_uint2(a.t1, b.t1);
+#pragma unroll
+        for (int u = 0; u < 3; ++u) *(uint2*)(dst + u * plane) = make_uint2(a.t[u], b.t[u]);
     };
-    auto split_done = [&]() {
-        plain |= !can_split(stage_max);
-        stage_max = 0.f;
-    };
-
     // K fragment: row qcol, dims 16 * ks + 8 * half ..  V through the LDS transpose read, whose 16-lane blocks
     // take (row of a quad, 4-dim column)
     const uint8_t* k_lane = sK + qcol * kRowK + 16 * half;
     const uint8_t* v_lane = sV + (4 * half + ((lane & 15) >> 2)) * kRowV + 32 * ((lane >> 4) & 1) + 8 * (lane & 3);
-    auto k_frags = [&](frag8 (&f)[2], int ks) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t) f[t] = *(const frag8*)(k_lane + t * kPlaneK + 32 * ks);
+    auto k_frag = [&](int u, int ks) -> frag8 { return *(const frag8*)(k_lane + u * kPlaneK + 32 * ks); };
+    auto v_frag = [&](int u, int s2, int db) -> frag8 {
+        const uint8_t* src = v_lane + u * kPlaneV + 16 * s2 * kRowV + 64 * db;
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))src);
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(src + 8 * kRowV));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
-    auto v_frags = [&](frag8 (&f)[2], int s2, int db) {
+    auto zero16 = [](f32x16& x) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const uint8_t* src = v_lane + t * kPlaneV + 16 * s2 * kRowV + 64 * db;
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))src);
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_PTR(s16x4))(src + 8 * kRowV));
-            f[t] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        }
+        for (int r = 0; r < 16; ++r) x[r] = 0.f;
     };
 
     f32x16 o[NB];   // o[b]: head dims 32 * b + 8 * (r / 4) + 4 * half + r % 4 of this lane's query
@@ -420,13 +417,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
     load(Kh);
 #pragma unroll
     for (int i = 0; i < PIECES; ++i) split_piece(false, i);
-    split_done();
     load(Vh);
     for (;;) {
         const int n_valid = min(kKeys, kv_tokens - kKeys * j);
         bool more = true;
         auto next_tile = [&]() {   // V(t) is split: on to K(t+1)
-            split_done();
             if (kKeys * (j + 1) < kv_tokens) {
                 ++j;
             } else {
@@ -440,62 +435,90 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
             }
         };
         __syncthreads();   // K(t) is there, and everyone has finished with V(t-1)
-        f32x16 S;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) S[r] = 0.f;
-        frag8 kf[2][2];
-        k_frags(kf[0], 0);
+        // (the leading products in a sum of their own: every MFMA rounds, by the magnitude of its sum)
+        f32x16 S, S_low;
+        zero16(S);
+        zero16(S_low);
+        frag8 f2 = k_frag(2, 0), f1 = k_frag(1, 0), f0;
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            if (ks + 1 < NK) k_frags(kf[(ks + 1) & 1], ks + 1);
-            S = mfma_split(kf[ks & 1], qf[ks], S);
+            f0 = k_frag(0, ks);
+            S_low = mfma_bf16(f2, qf[ks][0], S_low);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks + 1 < NK) f2 = k_frag(2, ks + 1);
+            S_low = mfma_bf16(f1, qf[ks][1], S_low);
+            S_low = mfma_bf16(f1, qf[ks][0], S_low);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ks + 1 < NK) f1 = k_frag(1, ks + 1);
+            S_low = mfma_bf16(f0, qf[ks][2], S_low);
+            S_low = mfma_bf16(f0, qf[ks][1], S_low);
+            S = mfma_bf16(f0, qf[ks][0], S);
 #pragma unroll
-            for (int i = ks * PIECES / NK; i < (ks + 1) * PIECES / NK; ++i) split_piece(true, i);
+            for (int k = ks * PIECES / NK; k < (ks + 1) * PIECES / NK; ++k) split_piece(true, k);
             __builtin_amdgcn_sched_barrier(0);
         }
+        S += S_low;
         next_tile();
-        frag8 pf[2][2];   // weights P^T (B operand): keys 16 * s2 .., two terms
+        frag8 pf[2][3];   // weights P^T (B operand): keys 16 * s2 ..
         if (n_valid < kKeys) {
+            const int left = n_valid - 4 * half;   // (one register instead of 16 kept through the walk)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
-                if (8 * (r >> 2) + 4 * half + (r & 3) >= n_valid) S[r] = -INFINITY;
+                if (8 * (r >> 2) + (r & 3) >= left) S[r] = -INFINITY;
         }
         const float mx = block_max(S) * c;
         if (__builtin_amdgcn_ballot_w64(mx > m_ref + kTopWeight) != 0) {
             const float m_new = fmaxf(m_ref, mx - kNewWeight);
             rescale(o, l, __builtin_amdgcn_exp2f(m_ref - m_new));
             m_ref = m_new;
-            plain |= !(fabsf(m_ref) < 0x1p20f);
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             S[r] = __builtin_amdgcn_exp2f(fmaf(S[r], c, -m_ref));
             l += S[r];
         }
+        pin(l);
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
-            const Split w0 = split_pair(S[8 * s2], S[8 * s2 + 1]), w1 = split_pair(S[8 * s2 + 2], S[8 * s2 + 3]);
-            const Split w2 = split_pair(S[8 * s2 + 4], S[8 * s2 + 5]), w3 = split_pair(S[8 * s2 + 6], S[8 * s2 + 7]);
-            pf[s2][0] = __builtin_bit_cast(frag8, make_uint4(w0.t0, w1.t0, w2.t0, w3.t0));
-            pf[s2][1] = __builtin_bit_cast(frag8, make_uint4(w0.t1, w1.t1, w2.t1, w3.t1));
+            Split w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = split_pair(S[8 * s2 + 2 * i], S[8 * s2 + 2 * i + 1]);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) pf[s2][u] = frag_of(w, u);
         }
         __syncthreads();   // V(t) is there, and everyone has finished with K(t)
-        frag8 vf[2][2];
-        v_frags(vf[0], 0, 0);
+        f32x16 add;   // what this tile adds to 32 head dims, so that O is rounded once a tile
+        f2 = v_frag(2, 0, 0);
+        f1 = v_frag(1, 0, 0);
 #pragma unroll
         for (int i = 0; i < 2 * NB; ++i) {
-            if (i + 1 < 2 * NB) v_frags(vf[(i + 1) & 1], (i + 1) / NB, (i + 1) % NB);
-            o[i % NB] = mfma_split(vf[i & 1], pf[i / NB], o[i % NB]);
+            const int s2 = i % 2, db = i / 2, s2n = (i + 1) % 2, dbn = (i + 1) / 2;
+            if (s2 == 0) zero16(add);
+            f0 = v_frag(0, s2, db);
+            add = mfma_bf16(f2, pf[s2][0], add);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < 2 * NB) f2 = v_frag(2, s2n, dbn);
+            add = mfma_bf16(f1, pf[s2][1], add);
+            add = mfma_bf16(f1, pf[s2][0], add);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < 2 * NB) f1 = v_frag(1, s2n, dbn);
+            add = mfma_bf16(f0, pf[s2][2], add);
+            add = mfma_bf16(f0, pf[s2][1], add);
+            add = mfma_bf16(f0, pf[s2][0], add);
             // (after the last tile the registers still hold V: split again for nothing, but without a branch)
 #pragma unroll
             for (int k = i * PIECES / (2 * NB); k < (i + 1) * PIECES / (2 * NB); ++k) split_piece(false, k);
+            if (s2 == 1) {
+                o[db] += add;
+                pin(o[db]);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
         if (!more) break;
-        split_done();
         load(Vh);
     }
 
+    plain |= !(stage_max < kLimit) || !(fabsf(m_ref) < 0x1p20f);
     const bool stored = q_first + qcol < q_tokens;
     float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h + (int64_t)q_row * p.o_stride_n;
     if (__syncthreads_or(plain)) {
@@ -693,12 +716,11 @@ template <int D, bool DENSE>
 static void launch_d(const AttnParams& p, int rows, hipStream_t stream) {
     const dim3 grid(tile_blocks<DENSE>(p));
     if (rows == 16) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE>), grid, dim3(512), 0, stream, p);
-    else if (rows == 32) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 1>), grid, dim3(64), 0, stream, p);
     else if (rows == 64) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 2>), grid, dim3(128), 0, stream, p);
     else hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 4>), grid, dim3(256), 0, stream, p);
 }
 
-// rows: query rows per workgroup, 16, 32, 64 or 128 (f32_tile_rows), for which p's tile counts were made
+// rows: query rows per workgroup, 16, 64 or 128 (f32_tile_rows), for which p's tile counts were made
 hipError_t launch_attn_f32(const AttnParams& p, int rows, int head_dim, bool dense, hipStream_t stream) {
     if (head_dim == 64) {
         if (dense) launch_d<64, true>(p, rows, stream);

@@ -188,18 +188,21 @@ static void fill_fastdivs(AttnParams& p) {
 }
 
 // Query rows per workgroup of the fp32 path: 16 selects the kernel that splits the keys over a workgroup's
-// waves, 32 / 64 / 128 the one whose waves own 32 queries each.  `rows` = query rows of a group (or of the
+// waves, 64 / 128 the one whose waves own 32 queries each.  `rows` = query rows of a group (or of the
 // sequence), `problems` = groups x heads x batch, `keys` = an upper bound of a list's keys.
-// Where the line lies: up to 1 024 waves of the second kind (one per SIMD) its time is that of one walk, the first
-// kind's grows with their number.  128, 256, 384 waves at 64x64 tokens in 16x16 groups, 3x3 lists: 73, 108, 155 us
-// against 131; 8 192 tokens dense, 64 dims, 256 and 512 waves: 193, 374 against 290.
+// Where the line lies: up to 512 waves of the second kind (one workgroup a compute unit) its time is that of one walk,
+// the first kind's grows with their number.  First against second kind, us: 64x64 tokens in 16x16 groups, 3x3 lists, 256 /
+// 384 / 512 / 640 waves 101 / 146 / 190 / 229 against 214 to 224; 8 192 tokens dense, 64 dims, 256 / 512 / 768 waves 192 /
+// 357 / 529 against 432; 2 048 tokens dense, 256 / 512 waves 112 / 211 against 197; 512 tokens, 256 / 512 waves 37 / 71
+// against 56.
+// Groups of at most 16 tokens are one workgroup of the first kind, 17 to 32 tokens two, which is already slower than
+// one half-filled workgroup of the second kind (4x8 groups, 128x128 tokens, 8 heads, 3x3 lists: 390 against 305).
+// Up to 64 tokens 64 rows; beyond, 128 even where a wave or two have no query (6x11 groups, 96x176 tokens, 16 heads:
+// 1 087 us, 1 126 as three 32-row workgroups were).
 static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys) {
     const int64_t waves = problems * ((rows + 31) / 32);   // of the 32-query kernel
-    if (keys < kMaxElems - 65536 && (rows <= 16 || waves < 320)) return 16;
-    const int64_t need = (rows + 31) / 32 * 32;
-    for (int bm = 128; bm > 32; bm /= 2)
-        if ((rows + bm - 1) / bm * bm == need || rows >= 1024) return bm;   // (no wave without queries)
-    return 32;
+    if (keys < kMaxElems - 65536 && (rows <= 16 || waves < 512)) return 16;
+    return rows <= 64 ? 64 : 128;
 }
 
 // Query rows per workgroup of a dense 16-bit launch.  head_dim 64: 128 (three such workgroups share a compute

@@ -127,19 +127,20 @@ __device__ __forceinline__ void rescale(Vec (&o)[N], float& l, float alpha) {
     for (int b = 0; b < N; ++b) o[b] *= alpha;
 }
 // Scores are weighted by exp2(c * (score - m_ref)), m_ref the largest so far (no score is below kNoScore, so that a block
-// of nothing but -infinity weighs 0).  For any numbers: the difference of huge scores is formed first, and no
-// weight is above 1, so that O overflows only where its sum does.
+// of nothing but -infinity weighs 0).  For any numbers: the difference of huge scores is formed first, no
+// weight is above 1, so that O overflows only where its sum does, and weights below 2^-126 are kept as far as fp32
+// has them (exp2f; the bare instruction gives 0 there).
 constexpr float kNoScore = -3.4028234e38f;
 template <int R, int N, typename Scores, typename Vec>
 __device__ __forceinline__ void weigh(Scores& S, float mx, Vec (&o)[N], float& m_ref, float& l, float c) {
     if (__builtin_amdgcn_ballot_w64(mx > m_ref) != 0) {
         const float m_new = fmaxf(m_ref, mx);
-        rescale(o, l, __builtin_amdgcn_exp2f((m_ref - m_new) * c));
+        rescale(o, l, exp2f((m_ref - m_new) * c));
         m_ref = m_new;
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        S[r] = __builtin_amdgcn_exp2f((S[r] - m_ref) * c);
+        S[r] = exp2f((S[r] - m_ref) * c);
         l += S[r];
     }
 }
@@ -698,7 +699,7 @@ __global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
     for (int d = 0; d < DPT; ++d) acc[d] = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float f = __builtin_amdgcn_exp2f((s_m[w][qi] - M) * c);   // (a wave without keys: 0)
+        const float f = exp2f((s_m[w][qi] - M) * c);   // (a wave without keys: 0)
         sum = fmaf(f, s_l[w][qi], sum);
 #pragma unroll
         for (int d = 0; d < DPT; ++d) acc[d] = fmaf(f, s_o[w][qi][d0 + d], acc[d]);

@@ -136,3 +136,16 @@ def test_scales(heads, scale):
     q, k, v = (t[0].double().cpu() for t in (q, k, v))
     want = torch.stack([torch.softmax(a @ b.t() * float(np.float32(scale)), -1) @ c for a, b, c in zip(q, k, v)])[None].numpy()
     assert errors(O, want)[1] <= 2e-5
+
+
+@pytest.mark.parametrize("heads,v_gain", [(2, 1e36), (12, 1e36)])   # (the second: the walk on the fp32 instructions)
+def test_weights_below_the_normal_range(heads, v_gain):
+    """One token has all but 2^-120 of the weight and no value, the others weigh 2^-130 each.  Bound: their exponent, 130, is
+    rounded twice (2^-17 each, times ln 2) and the weight has 19 bits left: 1.3e-5."""
+    q, k, v = inputs(heads, 1500, (0, 0, v_gain), 5404)
+    q[..., 0], k[..., 0] = 10.0, -13.0 / math.log2(math.e)
+    k[:, :, 700], v[:, :, 700] = 0.0, 0.0
+    O = to_f64(grat.grat_dense_attention_fwd(q, k, v, 1.0))
+    q, k, v = (t[0].double().cpu() for t in (q, k, v))
+    want = torch.stack([torch.softmax(a @ b.t(), -1) @ c for a, b, c in zip(q, k, v)])[None].numpy()
+    assert errors(O, want)[1] <= 2e-5

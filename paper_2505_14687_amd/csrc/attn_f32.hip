@@ -546,8 +546,11 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 // from the listed groups laid end to end, each padded to a multiple of 16 tokens - groups of fewer than
 // 16 tokens are not padded but packed, several to a block.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
 // with the list building: 390 us with one query per lane (32 waves in all), 28 us here, most of it host time.
+// Two workgroups a compute unit where LDS has room for them (head_dim 64: 33 of 160 KiB, four waves a SIMD, 128
+// registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, 182 us against 123,
+// 20 000 sequences of 16 tokens 777 against 542).
 template <int D, bool DENSE>
-__global__ __launch_bounds__(512, 2) void attn_f32_split_kernel(AttnParams p) {
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(AttnParams p) {
     constexpr int NW = 8, NP = D / 64;   // 64-dim parts of a V row
     __shared__ __attribute__((aligned(16))) float s_o[NW][16][D];
     __shared__ float s_m[NW][16], s_l[NW][16];

@@ -18,6 +18,8 @@
 //   attn_f32_split_kernel  16 queries a workgroup, the eight waves share its KEYS and merge at the end:
 //                          launches too small to give every SIMD a wave of its own, and groups of at most
 //                          16 tokens.
+#include <algorithm>
+
 #include "grat_common.h"
 #include "tile_order.h"
 
@@ -716,24 +718,29 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(At
     }
 }
 
+// A launch holds fewer than 2^32 threads (with more it silently runs a part of them): workgroups of 512 reach that with
+// 2^23 small groups, all heads together, so launches go out in parts of 2^22 workgroups (a multiple of the XCDs, so
+// that every workgroup stays on its own).
 template <int D, bool DENSE>
-static void launch_d(const AttnParams& p, int rows, hipStream_t stream) {
-    const dim3 grid(tile_blocks<DENSE>(p));
-    if (rows == 16) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE>), grid, dim3(512), 0, stream, p);
-    else if (rows == 64) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 2>), grid, dim3(128), 0, stream, p);
-    else hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 4>), grid, dim3(256), 0, stream, p);
+static hipError_t launch_d(AttnParams p, int rows, hipStream_t stream) {
+    constexpr int kPart = 1 << 22;
+    const int blocks = tile_blocks<DENSE>(p);
+    for (int first = 0; first < blocks; first += kPart) {
+        p.first_block = first;
+        const dim3 grid(std::min(kPart, blocks - first));
+        if (rows == 16) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE>), grid, dim3(512), 0, stream, p);
+        else if (rows == 64) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 2>), grid, dim3(128), 0, stream, p);
+        else hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 4>), grid, dim3(256), 0, stream, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || blocks - first <= kPart) return e;   // (first + kPart may not fit an int)
+    }
+    return hipSuccess;
 }
 
 // rows: query rows per workgroup, 16, 64 or 128 (f32_tile_rows), for which p's tile counts were made
 hipError_t launch_attn_f32(const AttnParams& p, int rows, int head_dim, bool dense, hipStream_t stream) {
-    if (head_dim == 64) {
-        if (dense) launch_d<64, true>(p, rows, stream);
-        else launch_d<64, false>(p, rows, stream);
-    } else {
-        if (dense) launch_d<128, true>(p, rows, stream);
-        else launch_d<128, false>(p, rows, stream);
-    }
-    return hipGetLastError();
+    if (head_dim == 64) return dense ? launch_d<64, true>(p, rows, stream) : launch_d<64, false>(p, rows, stream);
+    return dense ? launch_d<128, true>(p, rows, stream) : launch_d<128, false>(p, rows, stream);
 }
 
 }  // namespace grat

@@ -61,6 +61,7 @@ struct AttnParams {
     FastDiv fd_last1, fd_last2;
     int32_t pad_tokens;               // tokens a listed group takes up in the split kernel's key order
     FastDiv fd_pad_tokens;
+    int32_t first_block;              // number of the launch's first workgroup: large launches go out in parts
 };
 
 // What a workgroup of the MFMA attention kernel can be (its MODE template argument).

@@ -57,9 +57,9 @@ __device__ __forceinline__ bool longest_first_tile(const AttnParams& p, int b, i
 // tile qt of query group gamma there.  false: a workgroup that only pads the launch.
 template <bool DENSE>
 __device__ __forceinline__ bool pick_tile(const AttnParams& p, int& bh, int& qt, int& gamma) {
-    const int xcd = blockIdx.x % kNumXcd, idx = blockIdx.x / kNumXcd;
+    const int block = p.first_block + (int)blockIdx.x, xcd = block % kNumXcd, idx = block / kNumXcd;
     if (DENSE) return head_sync_tile<true>(p, xcd, idx, bh, qt);
-    if (p.longest_first) return longest_first_tile(p, (int)blockIdx.x, bh, qt, gamma);
+    if (p.longest_first) return longest_first_tile(p, block, bh, qt, gamma);
     int t;
     if (!head_sync_tile<false>(p, xcd, idx, bh, t)) return false;
     const uint32_t u = fdiv((uint32_t)t, p.fd_q_tiles);

@@ -78,6 +78,17 @@ __device__ __forceinline__ uint32_t list_entry(const AttnParams& p, int gamma, i
     return (uint32_t)min(max(p.kv_index[(int64_t)gamma * p.max_kv + i], 0), p.geo.num_groups - 1);
 }
 
+__device__ __forceinline__ float* out_row(const AttnParams& p, int b_idx, int h_idx, uint32_t row) {
+    return (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h + (int64_t)row * p.o_stride_n;
+}
+// An empty list is outside the contract; the mean of nothing is NaN.
+template <int N>
+__device__ __forceinline__ void nothing_attended(float* dst) {   // N times four head dims
+    const float nan = __builtin_nanf("");
+#pragma unroll
+    for (int i = 0; i < N; ++i) *(f32x4*)(dst + 4 * i) = f32x4{nan, nan, nan, nan};
+}
+
 __device__ __forceinline__ float swap32(float x) { return __shfl_xor(x, 32); }
 
 // ---- 32 queries a wave -------------------------------------------------------------------------
@@ -131,7 +142,8 @@ __device__ __forceinline__ void rescale(Vec (&o)[N], float& l, float alpha) {
 // Scores are weighted by exp2(c * (score - m_ref)), m_ref the largest so far (no score is below kNoScore, so that a block
 // of nothing but -infinity weighs 0).  For any numbers: the difference of huge scores is formed first, no
 // weight is above 1, so that O overflows only where its sum does, and weights below 2^-126 are kept as far as fp32
-// has them (exp2f; the bare instruction gives 0 there).
+// has them (exp2f; the bare instruction gives 0 there.  20 000 sequences of 16 tokens, head_dim 64: 564 us, 507 with the
+// bare one, 634 with a test that picks one of the two).
 constexpr float kNoScore = -3.4028234e38f;
 template <int R, int N, typename Scores, typename Vec>
 __device__ __forceinline__ void weigh(Scores& S, float mx, Vec (&o)[N], float& m_ref, float& l, float c) {
@@ -355,7 +367,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 
     // The walk: entry e of the list, tile j of its tokens; lane l looks after key l % 32 of a tile.
     const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
-    if (cnt == 0) return;
+    if (cnt == 0) {
+        if (q_first + qcol < q_tokens) nothing_attended<D / 8>(out_row(p, b_idx, h_idx, q_row) + half * (D / 2));
+        return;
+    }
     int e = 0, j = 0;
     uint32_t gid_next = 0, key_row = 0;
     Box kb{};
@@ -523,7 +538,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 
     plain |= !(stage_max < kLimit) || !(fabsf(m_ref) < 0x1p20f);
     const bool stored = q_first + qcol < q_tokens;
-    float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h + (int64_t)q_row * p.o_stride_n;
+    float* dst = out_row(p, b_idx, h_idx, q_row);
     if (__syncthreads_or(plain)) {
         fp32_walk<D, DENSE, NW>(p, lds, gamma, cnt, q_src, Kh, Vh, q_first < q_tokens, stored, dst);
     } else if (stored) {
@@ -549,8 +564,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 // 16 tokens are not padded but packed, several to a block.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
 // with the list building: 390 us with one query per lane (32 waves in all), 28 us here, most of it host time.
 // Two workgroups a compute unit where LDS has room for them (head_dim 64: 33 of 160 KiB, four waves a SIMD, 128
-// registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, 182 us against 123,
-// 20 000 sequences of 16 tokens 777 against 542).
+// registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, 182 us against 122,
+// 20 000 sequences of 16 tokens 777 against 564).
 template <int D, bool DENSE>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(AttnParams p) {
     constexpr int NW = 8, NP = D / 64;   // 64-dim parts of a V row
@@ -576,7 +591,11 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(At
     };
 
     const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
-    if (cnt == 0) return;
+    if (cnt == 0) {
+        const int i = threadIdx.x / (D / 4);   // (the first 4 D threads: four head dims each)
+        if (i < 16 && qt * 16 + i < q_tokens) nothing_attended<1>(out_row(p, b_idx, h_idx, query_row(i)) + threadIdx.x % (D / 4) * 4);
+        return;
+    }
     const int n_blocks = DENSE ? (p.n_tokens + 15) / 16 : (int)(((int64_t)cnt * p.pad_tokens + 15) / 16);
     // block b: lane looks after key `col` of it.  The group it belongs to is read one block before its rows
     // are needed, its K and V one block before they are multiplied.
@@ -711,8 +730,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(At
     }
     if (qt * 16 + qi < q_tokens) {
         const float inv = 1.f / sum;
-        float* dst = (float*)p.O + (int64_t)b_idx * p.o_stride_b + (int64_t)h_idx * p.o_stride_h +
-                     (int64_t)query_row(qi) * p.o_stride_n + d0;
+        float* dst = out_row(p, b_idx, h_idx, query_row(qi)) + d0;
 #pragma unroll
         for (int d = 0; d < DPT; ++d) dst[d] = acc[d] * inv;
     }

@@ -89,3 +89,20 @@ def test_token_major_strides():
     torch.cuda.synchronize()
     assert not out.is_contiguous()
     assert_close(to_f64(out), want, "f32", "token-major")
+
+
+@pytest.mark.parametrize("group,heads", [((16, 16), 2), ((16, 16), 64), ((4, 4), 2)])   # both kernels
+def test_empty_list_gives_nan(group, heads):
+    """A caller-made list with a count of 0 (outside the contract): its rows are NaN, the others as ever."""
+    grid, scale = (32, 32), 0.125
+    Q, K, V = synth.make_qkv(1, heads, 1024, 64, "f32", 80)
+    count, index = grat.grat_build_block_lists(grid, group, "block", (1, 1))
+    count[1] = 0
+    O = torch.zeros((1, heads, 1024, 64), device="cuda")
+    grat.grat_attention_fwd(to_device(Q), to_device(K), to_device(V), scale, grid, group, count, index, out=O)
+    got = to_f64(O)
+    coords = orc.token_group_coords(np.arange(1024), grid, group)
+    empty = (coords == (0, 1)).all(-1)
+    assert np.isnan(got[0, :, empty]).all()
+    want = orc.grat_attention(Q, K, V, grid, group, "block", (1, 1), scale)
+    assert_close(got[:, :, ~empty], want[:, :, ~empty], "f32", "other groups")

@@ -15,9 +15,9 @@
 // the order in which the pieces hold them.
 //
 //   attn_f32_kernel        32 queries a wave, K and V shared through LDS: launches that fill the chip.
-//   attn_f32_split_kernel  16 queries a workgroup, the eight waves share its KEYS and merge at the end:
-//                          launches too small to give every SIMD a wave of its own, and groups of at most
-//                          16 tokens.
+//   attn_f32_split_kernel  16 queries a workgroup, whose eight waves share its KEYS and merge at the end, or whose
+//                          only wave takes them all: launches too small to give every SIMD a wave of its own, groups
+//                          of at most 48 tokens, short sequences.
 #include <algorithm>
 
 #include "grat_common.h"
@@ -561,16 +561,15 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 // half the chain), wave w takes every eighth block of 16 keys, straight from memory into registers (nobody
 // else reads it), one block ahead, and the eight partial results are merged through LDS.  Blocks are cut
 // from the listed groups laid end to end, each padded to a multiple of 16 tokens - groups of fewer than
-// 16 tokens are not padded but packed, several to a block.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
+// 16 tokens are not padded but packed, several to a block.  Where the tiles alone fill the chip a workgroup is one
+// wave (NW = 1), which has all the keys and nothing to merge.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
 // with the list building: 390 us with one query per lane (32 waves in all), 28 us here, most of it host time.
 // Two workgroups a compute unit where LDS has room for them (head_dim 64: 33 of 160 KiB, four waves a SIMD, 128
 // registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, 182 us against 122,
 // 20 000 sequences of 16 tokens 777 against 564).
-template <int D, bool DENSE>
-__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(AttnParams p) {
-    constexpr int NW = 8, NP = D / 64;   // 64-dim parts of a V row
-    __shared__ __attribute__((aligned(16))) float s_o[NW][16][D];
-    __shared__ float s_m[NW][16], s_l[NW][16];
+template <int D, bool DENSE, int NW>
+__global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void attn_f32_split_kernel(AttnParams p) {
+    constexpr int NP = D / 64;   // 64-dim parts of a V row
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, quarter = lane >> 4;
@@ -592,8 +591,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(At
 
     const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
     if (cnt == 0) {
-        const int i = threadIdx.x / (D / 4);   // (the first 4 D threads: four head dims each)
-        if (i < 16 && qt * 16 + i < q_tokens) nothing_attended<1>(out_row(p, b_idx, h_idx, query_row(i)) + threadIdx.x % (D / 4) * 4);
+        if (wave == 0 && qt * 16 + col < q_tokens) nothing_attended<D / 16>(out_row(p, b_idx, h_idx, query_row(col)) + quarter * (D / 4));
         return;
     }
     const int n_blocks = DENSE ? (p.n_tokens + 15) / 16 : (int)(((int64_t)cnt * p.pad_tokens + 15) / 16);
@@ -699,40 +697,54 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(At
         b += NW;
     }
 
-    // merge: every wave leaves its reference, sum and O; a thread then adds up one query's share of dims
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    if (quarter == 0) {
-        s_m[wave][col] = m_ref;
-        s_l[wave][col] = l;
-    }
+    if constexpr (NW == 1) {
+        if (qt * 16 + col < q_tokens) {
+            const float inv = 1.f / l;
+            float* dst = out_row(p, b_idx, h_idx, query_row(col));
 #pragma unroll
-    for (int n = 0; n < NP; ++n)
+            for (int n = 0; n < NP; ++n)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            *(f32x4*)&s_o[wave][col][64 * n + 4 * (4 * quarter + r)] =
-                f32x4{o[4 * n][r], o[4 * n + 1][r], o[4 * n + 2][r], o[4 * n + 3][r]};
-    __syncthreads();
-    constexpr int DPT = 16 * D / 512;   // head dims per thread: 2 or 4
-    const int qi = threadIdx.x / 32, d0 = (threadIdx.x % 32) * DPT;
-    float M = s_m[0][qi];
+                for (int r = 0; r < 4; ++r)
+                    *(f32x4*)(dst + 64 * n + 4 * (4 * quarter + r)) =
+                        f32x4{o[4 * n][r] * inv, o[4 * n + 1][r] * inv, o[4 * n + 2][r] * inv, o[4 * n + 3][r] * inv};
+        }
+    } else {   // every wave leaves its reference, sum and O; a thread then adds up one query's share of dims
+        __shared__ __attribute__((aligned(16))) float s_o[NW][16][D];
+        __shared__ float s_m[NW][16], s_l[NW][16];
+        if (quarter == 0) {
+            s_m[wave][col] = m_ref;
+            s_l[wave][col] = l;
+        }
 #pragma unroll
-    for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w][qi]);
-    float sum = 0.f, acc[DPT];
+        for (int n = 0; n < NP; ++n)
 #pragma unroll
-    for (int d = 0; d < DPT; ++d) acc[d] = 0.f;
+            for (int r = 0; r < 4; ++r)
+                *(f32x4*)&s_o[wave][col][64 * n + 4 * (4 * quarter + r)] =
+                    f32x4{o[4 * n][r], o[4 * n + 1][r], o[4 * n + 2][r], o[4 * n + 3][r]};
+        __syncthreads();
+        constexpr int DPT = 16 * D / 512;   // head dims per thread: 2 or 4
+        const int qi = threadIdx.x / 32, d0 = (threadIdx.x % 32) * DPT;
+        float M = s_m[0][qi];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        const float f = exp2f((s_m[w][qi] - M) * c);   // (a wave without keys: 0)
-        sum = fmaf(f, s_l[w][qi], sum);
+        for (int w = 1; w < NW; ++w) M = fmaxf(M, s_m[w][qi]);
+        float sum = 0.f, acc[DPT];
 #pragma unroll
-        for (int d = 0; d < DPT; ++d) acc[d] = fmaf(f, s_o[w][qi][d0 + d], acc[d]);
-    }
-    if (qt * 16 + qi < q_tokens) {
-        const float inv = 1.f / sum;
-        float* dst = out_row(p, b_idx, h_idx, query_row(qi)) + d0;
+        for (int d = 0; d < DPT; ++d) acc[d] = 0.f;
 #pragma unroll
-        for (int d = 0; d < DPT; ++d) dst[d] = acc[d] * inv;
+        for (int w = 0; w < NW; ++w) {
+            const float f = exp2f((s_m[w][qi] - M) * c);   // (a wave without keys: 0)
+            sum = fmaf(f, s_l[w][qi], sum);
+#pragma unroll
+            for (int d = 0; d < DPT; ++d) acc[d] = fmaf(f, s_o[w][qi][d0 + d], acc[d]);
+        }
+        if (qt * 16 + qi < q_tokens) {
+            const float inv = 1.f / sum;
+            float* dst = out_row(p, b_idx, h_idx, query_row(qi)) + d0;
+#pragma unroll
+            for (int d = 0; d < DPT; ++d) dst[d] = acc[d] * inv;
+        }
     }
 }
 
@@ -740,14 +752,15 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void attn_f32_split_kernel(At
 // 2^23 small groups, all heads together, so launches go out in parts of 2^22 workgroups (a multiple of the XCDs, so
 // that every workgroup stays on its own).
 template <int D, bool DENSE>
-static hipError_t launch_d(AttnParams p, int rows, hipStream_t stream) {
+static hipError_t launch_d(AttnParams p, int rows, int key_waves, hipStream_t stream) {
     constexpr int kPart = 1 << 22;
     const int blocks = tile_blocks<DENSE>(p);
     for (int first = 0; first < blocks; first += kPart) {
         p.first_block = first;
         const dim3 grid(std::min(kPart, blocks - first));
-        if (rows == 16) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE>), grid, dim3(512), 0, stream, p);
-        else if (rows == 64) hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 2>), grid, dim3(128), 0, stream, p);
+        if (rows == 16 && key_waves == 1) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE, 1>), grid, dim3(64), 0, stream, p);
+        else if (rows == 16) hipLaunchKernelGGL((attn_f32_split_kernel<D, DENSE, 8>), grid, dim3(512), 0, stream, p);
+        else if (rows == 64) hipLaunchKernelGGL((attn_f32_kernel<D, false, 2>), grid, dim3(128), 0, stream, p);   // (groups only)
         else hipLaunchKernelGGL((attn_f32_kernel<D, DENSE, 4>), grid, dim3(256), 0, stream, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || blocks - first <= kPart) return e;   // (first + kPart may not fit an int)
@@ -755,10 +768,12 @@ static hipError_t launch_d(AttnParams p, int rows, hipStream_t stream) {
     return hipSuccess;
 }
 
-// rows: query rows per workgroup, 16, 64 or 128 (f32_tile_rows), for which p's tile counts were made
-hipError_t launch_attn_f32(const AttnParams& p, int rows, int head_dim, bool dense, hipStream_t stream) {
-    if (head_dim == 64) return dense ? launch_d<64, true>(p, rows, stream) : launch_d<64, false>(p, rows, stream);
-    return dense ? launch_d<128, true>(p, rows, stream) : launch_d<128, false>(p, rows, stream);
+// rows: query rows per workgroup, 16, 64 or 128 (f32_tile_rows), for which p's tile counts were made; key_waves: waves
+// that share the keys of 16 rows, 1 or 8
+hipError_t launch_attn_f32(const AttnParams& p, int rows, int key_waves, int head_dim, bool dense, hipStream_t stream) {
+    if (head_dim == 64)
+        return dense ? launch_d<64, true>(p, rows, key_waves, stream) : launch_d<64, false>(p, rows, key_waves, stream);
+    return dense ? launch_d<128, true>(p, rows, key_waves, stream) : launch_d<128, false>(p, rows, key_waves, stream);
 }
 
 }  // namespace grat

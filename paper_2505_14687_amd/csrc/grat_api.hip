@@ -161,6 +161,9 @@ extern "C" grat_status grat_validate_block_lists(int32_t ndim, const int32_t* gr
     return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
 }
 
+// Tokens a listed group takes up in the key order of the fp32 kernel that works in blocks of 16 keys.
+static int32_t pad_tokens(int32_t group_tokens) { return group_tokens < 16 ? group_tokens : (group_tokens + 15) / 16 * 16; }
+
 // Divisors of the MFMA kernel's index decompositions, from the finished launch parameters.
 static void fill_fastdivs(AttnParams& p) {
     const Geometry& geo = p.geo;
@@ -183,27 +186,37 @@ static void fill_fastdivs(AttnParams& p) {
     p.last0 = geo.T[0] - (geo.G[0] - 1) * geo.g[0];
     p.fd_last1 = make_fastdiv((uint32_t)(geo.T[1] - (geo.G[1] - 1) * geo.g[1]));
     p.fd_last2 = make_fastdiv((uint32_t)(geo.T[2] - (geo.G[2] - 1) * geo.g[2]));
-    p.pad_tokens = geo.group_tokens < 16 ? geo.group_tokens : (geo.group_tokens + 15) / 16 * 16;
+    p.pad_tokens = pad_tokens(geo.group_tokens);
     p.fd_pad_tokens = make_fastdiv((uint32_t)p.pad_tokens);
 }
 
-// Query rows per workgroup of the fp32 path: 16 selects the kernel that splits the keys over a workgroup's
-// waves, 64 / 128 the one whose waves own 32 queries each.  `rows` = query rows of a group (or of the
+// Query rows per workgroup of the fp32 path: 16 selects the kernel whose waves own 16 queries (all of them, or a share
+// of the keys each), 64 / 128 the one whose waves own 32 queries each.  `rows` = query rows of a group (or of the
 // sequence), `problems` = groups x heads x batch, `keys` = an upper bound of a list's keys.
-// Where the line lies: up to 512 waves of the second kind (one workgroup a compute unit) its time is that of one walk,
-// the first kind's grows with their number.  First against second kind, us: 64x64 tokens in 16x16 groups, 3x3 lists, 256 /
-// 384 / 512 / 640 waves 101 / 146 / 190 / 229 against 214 to 224; 8 192 tokens dense, 64 dims, 256 / 512 / 768 waves 192 /
-// 357 / 529 against 432; 2 048 tokens dense, 256 / 512 waves 112 / 211 against 197; 512 tokens, 256 / 512 waves 37 / 71
-// against 56.
-// Groups of at most 16 tokens are one workgroup of the first kind, 17 to 32 tokens two, which is already slower than
-// one half-filled workgroup of the second kind (4x8 groups, 128x128 tokens, 8 heads, 3x3 lists: 390 against 305).
-// Up to 64 tokens 64 rows; beyond, 128 even where a wave or two have no query (6x11 groups, 96x176 tokens, 16 heads:
+// Where the lines lie, first against second kind, us.
+// 512 waves of the second kind (one workgroup a compute unit): up to there its time is that of one walk, the first kind's
+// grows with their number.  64x64 tokens in 16x16 groups, 3x3 lists, 256 / 384 / 512 / 640 waves 101 / 146 / 190 / 229
+// against 214 to 224; 8 192 tokens dense, 64 dims, 256 / 512 / 768 waves 192 / 357 / 529 against 432; 2 048 tokens dense,
+// 256 / 512 waves 112 / 211 against 197; 512 tokens, 256 / 512 waves 37 / 71 against 56.
+// 48 tokens: a workgroup of the second kind has at least 64 rows.  128x128 tokens, 8 heads x 128, 3x3 lists in groups of
+// 1x17 / 4x8 / 5x8 / 6x8 371 / 231 / 390 / 332 against 515 / 302 / 472 / 407, criss-cross 5x8 / 6x8 1 728 / 1 263 against
+// 2 104 / 1 638; 8x8 groups, 64x64 tokens 150 against 76.
+// Short sequences (dense): a workgroup of the second kind takes its time to start.  Head_dim 64 / 128: 5 000 sequences of 64
+// tokens 113 / 219 against 260 / 553, 2 500 of 128 203 / 394 against 284 / 521, but 1 000 of 200 165 / 349 against 161 / 313.
+// (Not so for groups with no more keys, whose K and V the group itself brings into the cache: 8x8 groups that attend
+// themselves, 256x256 tokens, 8 heads 162 / 302 against 130 / 271.)  Up to 64 tokens 64 rows; beyond, 128 even where a wave or two have no query (6x11 groups, 96x176 tokens, 16 heads:
 // 1 087 us, 1 126 as three 32-row workgroups were).
 static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys) {
     const int64_t waves = problems * ((rows + 31) / 32);   // of the 32-query kernel
-    if (keys < kMaxElems - 65536 && (rows <= 16 || waves < 512)) return 16;
+    if (keys < kMaxElems - 65536 && (rows <= 48 || waves < 512)) return 16;
     return rows <= 64 ? 64 : 128;
 }
+// Waves that share the keys of 16 rows: one where the launch gives every SIMD a wave that way, or nearly so and there is
+// little to share; `tiles` = 16-row tiles of the launch.  One against eight, us, head_dim 64 / 128: 1 024 tiles, 256
+// keys 21 / 32 against 22 / 45, 512 keys 36 / 54 against 34 / 72; 512 tiles, 64 keys 10 / 12 against 10 / 17, 256 keys 19 / 28
+// against 13 / 24; 256 tiles, 16 keys 11 / 11 against 11 / 17; 1x1, 2x2 and 4x4 groups, 128x128
+// tokens, 8 heads x 64: 157, 90, 70 against 870, 253, 120; 20 000 sequences of 16 tokens 175 against 562 (178 with a query a lane).
+static int f32_key_waves(int64_t tiles, int64_t keys) { return tiles >= 1024 || (tiles >= 256 && keys <= 64) ? 1 : 8; }
 
 // Query rows per workgroup of a dense 16-bit launch.  head_dim 64: 128 (three such workgroups share a compute
 // unit; 8 200 tokens, 16 heads: 409 -> 343 us).  head_dim 128: one 256-row workgroup fills a compute unit, so up to
@@ -264,6 +277,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
 
     const int n_g = geo.group_tokens;
     int bm;   // query rows per workgroup
+    const int64_t f32_keys = (int64_t)max_kv * pad_tokens(n_g);   // at most, of a list
     if (is16(dtype)) {
         if (n_g % 64) return GRAT_ERR_UNSUPPORTED;
         // byte offsets inside one group are kept in 32 bits
@@ -278,7 +292,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
         // walk (measured: +5 % at 64x64 tokens, nothing either way from 128x128 tokens on).
         if (bm == 256 && (int64_t)batch * heads * geo.num_groups < 2 * 256) bm = 128;
     } else {
-        bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, (int64_t)max_kv * (n_g + 15));
+        bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, f32_keys);
     }
     p.q_rows = bm;
     p.q_tiles = (n_g + bm - 1) / bm;
@@ -310,7 +324,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     fill_fastdivs(p);
     const hipError_t e = is16(dtype)
                              ? launch_attn_bf16(p, mode, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
-                             : launch_attn_f32(p, bm, head_dim, false, (hipStream_t)hip_stream);
+                             : launch_attn_f32(p, bm, f32_key_waves(total, f32_keys), head_dim, false, (hipStream_t)hip_stream);
     return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
 }
 
@@ -380,7 +394,7 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     p.scale_log2 = scale * 1.4426950408889634f;
     p.n_tokens = (int32_t)n_tokens;
     const int bm = is16(dtype) ? dense_tile_rows(head_dim, n_tokens, (int64_t)batch * heads)
-                               : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens);
+                               : n_tokens <= 128 ? 16 : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens);
     p.q_rows = bm;
     p.q_tiles = (int32_t)((n_tokens + bm - 1) / bm);
     p.q_tiles_dense = p.q_tiles;
@@ -391,7 +405,8 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     fill_fastdivs(p);
     const hipError_t e = is16(dtype)
                              ? launch_attn_bf16(p, kDense, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
-                             : launch_attn_f32(p, bm, head_dim, true, (hipStream_t)hip_stream);
+                             : launch_attn_f32(p, bm, f32_key_waves((int64_t)batch * heads * p.q_tiles, n_tokens), head_dim, true,
+                                               (hipStream_t)hip_stream);
     return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
 }
 

@@ -82,7 +82,7 @@ hipError_t launch_build_block_lists(const Geometry& geo, int ndim, grat_pattern 
                                     int32_t* d_kv_index, int32_t max_kv, hipStream_t stream);
 hipError_t launch_validate_block_lists(const Geometry& geo, const int32_t* d_kv_count, const int32_t* d_kv_index,
                                        int32_t max_kv, int32_t* d_status, hipStream_t stream);
-hipError_t launch_attn_f32(const AttnParams& p, int rows /* per workgroup */, int head_dim, bool dense, hipStream_t stream);
+hipError_t launch_attn_f32(const AttnParams& p, int rows /* per workgroup */, int key_waves, int head_dim, bool dense, hipStream_t stream);
 hipError_t launch_attn_bf16(const AttnParams& p, int mode /* AttnMode */, bool f16, int head_dim, hipStream_t stream);
 
 // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).

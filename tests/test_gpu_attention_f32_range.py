@@ -59,9 +59,10 @@ def test_special_values(heads):
 
 # Where an infinity of V meets the padding of a key tile: sequences and groups that end inside a tile, the infinity in
 # their first or last token.  (1500 = 46 * 32 + 28 = 93 * 16 + 12 tokens; groups of 3 x 11 and, clipped, 3 x 7 tokens;
-# of 5 x 3 and, clipped, fewer.)  heads: either side of the launch size from which waves own 32 queries.
+# of 5 x 3 and, clipped, fewer; of 7 x 9, whose workgroups own 64 queries.)  heads: either side of the launch size from
+# which waves own 32 queries.
 @pytest.mark.parametrize("heads,d", [(2, 128), (12, 128), (16, 64)])
-@pytest.mark.parametrize("grid,group", [((1500,), None), ((33, 62), (3, 11)), ((33, 35), (5, 3))])   # None: dense
+@pytest.mark.parametrize("grid,group", [((1500,), None), ((33, 62), (3, 11)), ((33, 35), (5, 3)), ((33, 62), (7, 9))])   # None: dense
 @pytest.mark.parametrize("last", [True, False])
 def test_infinity_beside_padding(grid, group, last, heads, d):
     n = math.prod(grid)

@@ -34,7 +34,6 @@ struct AttnParams {
     const int32_t* kv_index;
     int32_t max_kv;
     int32_t n_tokens;          // dense tiles: number of KV rows (the whole sequence)
-    int32_t q_rows;            // query rows per workgroup
     int32_t q_tiles;           // query tiles per group
     int32_t strip_w;           // grouped bf16 path: query groups are walked in column strips this wide
     // dense tiles (dense entry point, and the prompt rows of a joint sequence)
@@ -61,7 +60,10 @@ struct AttnParams {
     FastDiv fd_last1, fd_last2;
     int32_t pad_tokens;               // tokens a listed group takes up in the split kernel's key order
     FastDiv fd_pad_tokens;
-    int32_t first_block;              // number of the launch's first workgroup: large launches go out in parts
+    int32_t first_block;              // fp32 kernels: number of the launch's first workgroup (large ones go out in parts)
+    // host only: query rows per workgroup.  (Behind everything the kernels load: among the tile counts it cost the
+    // 8-wave joint kernel 23 more spilled scalar registers and 0.7 % of its time.)
+    int32_t q_rows;
 };
 
 // What a workgroup of the MFMA attention kernel can be (its MODE template argument).

@@ -750,12 +750,17 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
 // half the MFMAs per score but the same vector work and fragment latencies, so two waves a SIMD left the kernel
 // waiting (720 cycles per wave and 32-key block, as many as at 128, of which the MFMAs are 256): three waves of
 // 4-wave workgroups (168 registers) took 256x256 tokens, 3x3 groups of 16x16, 24 heads from 997 to 866 us
-// (855 -> 984 TFLOP/s); four spill (1 186 us), and so do two 8-wave workgroups (1 160 us).  The 2-wave
-// workgroups on 64-key tiles fit 128 registers (512x512 tokens, criss-cross in 8x8 groups, 8 heads: 5.3 ms
-// against 5.9 with a bound of three; 8.5 before), their joint variant only fits at two.
+// (855 -> 984 TFLOP/s); four spill (1 186 us), and so do two 8-wave workgroups (1 160 us).  Joint sequences spill 17 registers
+// (40 bytes) at three and none at two, and are still better off at three: 128x128 tokens in 16x16 groups, 24 heads,
+// 512 prompt tokens, 3x3 lists 335 against 355 us, 77 prompt tokens, criss-cross 457 against 497; 256x256 packed 1 369
+// against 1 450.
+// The 2-wave workgroups on 64-key tiles are held to two waves a SIMD by their 32 KiB of LDS.  Whole groups do best
+// with no bound (192 registers; 512x512 tokens, criss-cross in 8x8 groups, 8 heads: 5.22 ms against 5.83 with the 141
+// registers of a bound of three), clipped ones with a bound of three (145 registers; 500x500 tokens: 5.99 ms against
+// 6.27 with the 208 of none); the joint variant spills below two.
 constexpr int waves_per_simd(int nwaves, int bn, int mode, int d) {
     if (d == 128) return 2;
-    if (nwaves == 2 && bn == 64) return mode == kJoint ? 2 : 4;
+    if (nwaves == 2 && bn == 64) return mode == kJoint ? 2 : mode == kRagged ? 3 : 1;
     return 3;
 }
 

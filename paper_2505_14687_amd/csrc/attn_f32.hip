@@ -17,7 +17,7 @@
 //   attn_f32_kernel        32 queries a wave, K and V shared through LDS: launches that fill the chip.
 //   attn_f32_split_kernel  16 queries a workgroup, whose eight waves share its KEYS and merge at the end, or whose
 //                          only wave takes them all: launches too small to give every SIMD a wave of its own, groups
-//                          of at most 48 tokens, short sequences.
+//                          (or sequences) of at most 48 tokens.
 #include <algorithm>
 
 #include "grat_common.h"
@@ -142,8 +142,8 @@ __device__ __forceinline__ void rescale(Vec (&o)[N], float& l, float alpha) {
 // Scores are weighted by exp2(c * (score - m_ref)), m_ref the largest so far (no score is below kNoScore, so that a block
 // of nothing but -infinity weighs 0).  For any numbers: the difference of huge scores is formed first, no
 // weight is above 1, so that O overflows only where its sum does, and weights below 2^-126 are kept as far as fp32
-// has them (exp2f; the bare instruction gives 0 there.  20 000 sequences of 16 tokens, head_dim 64: 564 us, 507 with the
-// bare one, 634 with a test that picks one of the two).
+// has them (exp2f; the bare instruction gives 0 there.  Where lists are a block or two long that is 5 to 10 % of the
+// eight-wave kernel's time; a test that picks one of the two costs more).
 constexpr float kNoScore = -3.4028234e38f;
 template <int R, int N, typename Scores, typename Vec>
 __device__ __forceinline__ void weigh(Scores& S, float mx, Vec (&o)[N], float& m_ref, float& l, float c) {
@@ -565,8 +565,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 // wave (NW = 1), which has all the keys and nothing to merge.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
 // with the list building: 390 us with one query per lane (32 waves in all), 28 us here, most of it host time.
 // Two workgroups a compute unit where LDS has room for them (head_dim 64: 33 of 160 KiB, four waves a SIMD, 128
-// registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, 182 us against 122,
-// 20 000 sequences of 16 tokens 777 against 564).
+// registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, eight waves, 182
+// us against 122).
 template <int D, bool DENSE, int NW>
 __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void attn_f32_split_kernel(AttnParams p) {
     constexpr int NP = D / 64;   // 64-dim parts of a V row

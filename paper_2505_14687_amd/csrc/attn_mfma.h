@@ -778,23 +778,26 @@ __global__ __launch_bounds__(NWAVES * 64, waves_per_simd(NWAVES, BN, MODE, D)) v
         if (idx < dense_per_xcd) {
             const int tile = idx * kNumXcd + xcd;
             if (tile < p.n_dense_tiles) {
-                bh = (int)fdiv((uint32_t)tile, p.fd_tiles_per_head_dense);
-                attn_tile<NWAVES, BN, MODE, F16, D, true>(p, bh, tile - bh * p.q_tiles_dense, sK, sV);
+                dense_tile(p, tile, bh, t_in_head);
+                attn_tile<NWAVES, BN, MODE, F16, D, true>(p, bh, t_in_head, sK, sV);
             }
         } else if (p.longest_first) {
             int qt, gamma;
             if (longest_first_tile(p, (int)blockIdx.x - dense_per_xcd * kNumXcd, bh, qt, gamma))
                 attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, qt, sK, sV, gamma);
-        } else if (head_sync_tile<false>(p, xcd, idx - dense_per_xcd, bh, t_in_head)) {
+        } else if (head_sync_tile(p, xcd, idx - dense_per_xcd, bh, t_in_head)) {
             attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, t_in_head, sK, sV);
         }
-    } else if (MODE != kDense && p.longest_first) {
+    } else if constexpr (MODE == kDense) {
+        dense_tile(p, (int)blockIdx.x, bh, t_in_head);
+        attn_tile<NWAVES, BN, MODE, F16, D, true>(p, bh, t_in_head, sK, sV);
+    } else if (p.longest_first) {
         int qt, gamma;
         if (longest_first_tile(p, (int)blockIdx.x, bh, qt, gamma))
             attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, qt, sK, sV, gamma);
     } else {
-        if (head_sync_tile<MODE == kDense>(p, xcd, idx, bh, t_in_head))
-            attn_tile<NWAVES, BN, MODE, F16, D, MODE == kDense>(p, bh, t_in_head, sK, sV);
+        if (head_sync_tile(p, xcd, idx, bh, t_in_head))
+            attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, t_in_head, sK, sV);
     }
 }
 

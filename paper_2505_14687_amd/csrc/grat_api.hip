@@ -168,9 +168,7 @@ static int32_t pad_tokens(int32_t group_tokens) { return group_tokens < 16 ? gro
 static void fill_fastdivs(AttnParams& p) {
     const Geometry& geo = p.geo;
     p.per_xcd = (geo.num_groups * p.q_tiles + kNumXcd - 1) / kNumXcd;
-    p.per_xcd_dense = (p.q_tiles_dense + kNumXcd - 1) / kNumXcd;
     p.fd_per_xcd = make_fastdiv((uint32_t)p.per_xcd);
-    p.fd_per_xcd_dense = make_fastdiv((uint32_t)p.per_xcd_dense);
     p.fd_tiles_per_head_dense = make_fastdiv((uint32_t)p.q_tiles_dense);
     p.fd_heads = make_fastdiv((uint32_t)p.heads);
     p.fd_q_tiles = make_fastdiv((uint32_t)p.q_tiles);
@@ -201,31 +199,37 @@ static void fill_fastdivs(AttnParams& p) {
 // 48 tokens: a workgroup of the second kind has at least 64 rows.  128x128 tokens, 8 heads x 128, 3x3 lists in groups of
 // 1x17 / 4x8 / 5x8 / 6x8 371 / 231 / 390 / 332 against 515 / 302 / 472 / 407, criss-cross 5x8 / 6x8 1 728 / 1 263 against
 // 2 104 / 1 638; 8x8 groups, 64x64 tokens 150 against 76.
-// Short sequences (dense): a workgroup of the second kind takes its time to start.  Head_dim 64 / 128: 5 000 sequences of 64
-// tokens 113 / 219 against 260 / 553, 2 500 of 128 203 / 394 against 284 / 521, but 1 000 of 200 165 / 349 against 161 / 313.
-// (Not so for groups with no more keys, whose K and V the group itself brings into the cache: 8x8 groups that attend
-// themselves, 256x256 tokens, 8 heads 162 / 302 against 130 / 271.)  Up to 64 tokens 64 rows; beyond, 128 even where a wave or two have no query (6x11 groups, 96x176 tokens, 16 heads:
-// 1 087 us, 1 126 as three 32-row workgroups were).
-static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys) {
+// Up to 64 tokens a group 64 rows; beyond, 128 even where a wave or two have no query (6x11 groups, 96x176 tokens, 16
+// heads: 1 087 us, 1 126 as three 32-row workgroups were).  Sequences (dense) 128: 5 000 of 64 tokens, head_dim 64 / 128,
+// 102 / 206 (first kind 114 / 217), 2 500 of 128 95 / 205 (203 / 395); 2 000 of 48 35 / 67 (31 / 58).
+static int f32_tile_rows(int64_t rows, int64_t problems, int64_t keys, bool dense) {
     const int64_t waves = problems * ((rows + 31) / 32);   // of the 32-query kernel
     if (keys < kMaxElems - 65536 && (rows <= 48 || waves < 512)) return 16;
-    return rows <= 64 ? 64 : 128;
+    return rows <= 64 && !dense ? 64 : 128;
 }
 // Waves that share the keys of 16 rows: one where the launch gives every SIMD a wave that way, or nearly so and there is
 // little to share; `tiles` = 16-row tiles of the launch.  One against eight, us, head_dim 64 / 128: 1 024 tiles, 256
 // keys 21 / 32 against 22 / 45, 512 keys 36 / 54 against 34 / 72; 512 tiles, 64 keys 10 / 12 against 10 / 17, 256 keys 19 / 28
-// against 13 / 24; 256 tiles, 16 keys 11 / 11 against 11 / 17; 1x1, 2x2 and 4x4 groups, 128x128
-// tokens, 8 heads x 64: 157, 90, 70 against 870, 253, 120; 20 000 sequences of 16 tokens 175 against 562 (178 with a query a lane).
+// against 13 / 24; 256 tiles, 16 keys 11 / 11 against 11 / 17; 1x1, 2x2 and 4x4 groups,
+// 128x128 tokens, 8 heads x 64: 157, 90, 70 against 870, 253, 120.
 static int f32_key_waves(int64_t tiles, int64_t keys) { return tiles >= 1024 || (tiles >= 256 && keys <= 64) ? 1 : 8; }
 
-// Query rows per workgroup of a dense 16-bit launch.  head_dim 64: 128 (three such workgroups share a compute
-// unit; 8 200 tokens, 16 heads: 409 -> 343 us).  head_dim 128: one 256-row workgroup fills a compute unit, so up to
-// one and a half rounds of them go as 128-row workgroups, which spread the rows and cover each other's prologues;
-// beyond, 256 rows share their K/V tiles among more queries.  24 heads, 256 against 128 rows: 2 100 tokens
-// (0.84 rounds) 99.7 / 63.8 us, 2 600 (1.03) 127 / 111, 3 100 (1.22) 143.6 / 144.5, 4 096 (1.5) 203 / 192,
-// 4 429 (1.7) 228 / 244, 8 192 (3) 674 / 710.
+// Query rows per workgroup of a dense 16-bit launch.  head_dim 64: 128, three such workgroups share a compute unit (no
+// difference to 256 rows otherwise: 8 200 tokens, 16 heads 342 against 341 us).
+// head_dim 128: one 256-row workgroup fills a compute unit, or two 128-row ones.  256 rows share K and V among more
+// queries, so 128 rows are taken where they leave enough less of the last round idle: a round of them that is at most
+// half full takes 0.7 of one (a workgroup alone on its compute unit is faster), and they have to win 6 %.  us for
+// 256 / 128 rows (heads x tokens): 1 x 10 240 197 / 144, 24 x 2 816 142 / 126, 8 x 9 216 435 / 390, 24 x 4 096 (1.5
+// rounds) 205 / 195; 64 x 1 024 38 / 45, 24 x 2 560 78 / 81, 16 x 4 096 (1.0 rounds) 122 / 129, 24 x 8 192 674 / 710.
+// Over 448 launches of 1 to 384 heads, 256 tokens to 200 000, the rule is within 0.4 % of the better of the two, 19 %
+// ahead of 256 rows with padded launches (see dense_tile), and more than 3.5 % behind those in five (96 x 768 and 96 x
+// 1 024: 7 and 9 %).
 static int dense_tile_rows(int head_dim, int64_t rows, int64_t problems) {
-    return head_dim == 64 || problems * ((rows + 255) / 256) <= 384 ? 128 : 256;
+    if (head_dim == 64) return 128;
+    const int64_t tiles128 = problems * ((rows + 127) / 128), tiles256 = problems * ((rows + 255) / 256);
+    const int64_t last = tiles128 % 512;
+    const int64_t cost128 = tiles128 / 512 * 10 + (last == 0 ? 0 : last <= 256 ? 7 : 10), cost256 = (tiles256 + 255) / 256 * 10;
+    return cost128 * 106 < cost256 * 100 ? 128 : 256;
 }
 
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
@@ -292,7 +296,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
         // walk (measured: +5 % at 64x64 tokens, nothing either way from 128x128 tokens on).
         if (bm == 256 && (int64_t)batch * heads * geo.num_groups < 2 * 256) bm = 128;
     } else {
-        bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, f32_keys);
+        bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, f32_keys, false);
     }
     p.q_rows = bm;
     p.q_tiles = (n_g + bm - 1) / bm;
@@ -394,10 +398,11 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     p.scale_log2 = scale * 1.4426950408889634f;
     p.n_tokens = (int32_t)n_tokens;
     const int bm = is16(dtype) ? dense_tile_rows(head_dim, n_tokens, (int64_t)batch * heads)
-                               : n_tokens <= 128 ? 16 : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens);
+                               : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens, true);
     p.q_rows = bm;
     p.q_tiles = (int32_t)((n_tokens + bm - 1) / bm);
     p.q_tiles_dense = p.q_tiles;
+    p.n_dense_tiles = batch * heads * p.q_tiles;
     p.n_dense_rows = (int32_t)n_tokens;
     p.dense_row0 = 0;
     if ((int64_t)batch * heads * ((int64_t)p.q_tiles + 8) >= kMaxElems - 8) return GRAT_ERR_UNSUPPORTED;

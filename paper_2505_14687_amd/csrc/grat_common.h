@@ -40,7 +40,7 @@ struct AttnParams {
     int32_t q_tiles_dense;     // query tiles per head
     int32_t n_dense_rows;      // query rows per head
     int32_t dense_row0;        // first of them
-    int32_t n_dense_tiles;     // joint sequence: batch * heads * q_tiles_dense, launched ahead of the grouped tiles
+    int32_t n_dense_tiles;     // batch * heads * q_tiles_dense (joint sequence: launched ahead of the grouped tiles)
     // joint sequence (prompt tokens + grid tokens)
     int32_t n_global;          // prompt tokens
     int32_t global_row0;       // first prompt row
@@ -48,8 +48,8 @@ struct AttnParams {
     // MFMA kernel: host-prepared divisors for the index decompositions of its prologue
     FastDiv fd_tiles_per_head_dense;  // by q_tiles_dense
     FastDiv fd_heads, fd_q_tiles;
-    int32_t per_xcd, per_xcd_dense;   // tiles of one head that one XCD owns: ceil(tiles per head / 8), grouped and dense
-    FastDiv fd_per_xcd, fd_per_xcd_dense;
+    int32_t per_xcd;                  // grouped tiles of one head that one XCD owns: ceil(tiles per head / 8)
+    FastDiv fd_per_xcd;
     int32_t longest_first;            // small grouped launches: tiles are handed out by list length, longest first
     FastDiv fd_tiles_per_rank;        // by batch * heads * q_tiles
     FastDiv fd_strip, fd_strip_w, fd_strip_tail;   // strip order: by rows * strip_w, strip_w, width of the last strip

@@ -47,7 +47,7 @@ def test_grouped_tiles(grid, group, pattern, radius, heads, d, v_gain):
 
 @pytest.mark.parametrize("v_gain", [1.0, 2.0 ** 40])
 @pytest.mark.parametrize("N,heads,d", [(2050, 16, 64), (2079, 16, 128), (16, 1, 128), (17, 2, 64), (129, 3, 128),
-                                       (33, 300, 128), (61, 300, 64), (128, 130, 128), (129, 130, 64),   # up to 128 tokens
+                                       (48, 300, 128), (49, 300, 64), (64, 300, 128), (128, 130, 128), (129, 130, 64),
                                        (1, 1100, 64), (15, 300, 128)])
 def test_dense_tiles(N, heads, d, v_gain):
     host = synth.make_qkv(1, heads, N, d, "f32", 5200, q_gain=3.0)

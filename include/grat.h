@@ -141,6 +141,9 @@ grat_status grat_validate_block_lists(int32_t ndim, const int32_t* grid, const i
  *              sequence is passed as three pointers into it with stride_n = 3 * H * d.
  * 16-bit paths: scores, running max / sum and the output accumulator are fp32; softmax weights
  * are rounded to the element type (nearest-even) before multiplying V; O is rounded once.
+ * GRAT_F32: inputs, scores, weights, sums and accumulators keep the 24 bits of fp32, whatever the magnitudes (also of
+ * single head dims or tokens beside much larger ones); some launches take a product as the sum of exact bf16 products,
+ * leaving out no more than rounding the product to fp32 would.
  * Asynchronous on hip_stream.
  */
 grat_status grat_attention_fwd(const void* Q, const void* K, const void* V, void* O,

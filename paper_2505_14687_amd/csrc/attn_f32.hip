@@ -302,7 +302,7 @@ __device__ __forceinline__ void fp32_walk(const AttnParams& p, uint8_t* lds, int
 // are formed: while the waves form the scores of tile t they split V(t), while they add tile t to O they split
 // K(t+1), with a barrier between the halves; the fp32 rows of the next half are in registers or on their way.  Two
 // waves per SIMD, from different workgroups (LDS: 56 KiB each at head_dim 128), cover each other's softmax and
-// barriers; 64-row workgroups get one.  256 registers (head_dim 128): 27 to 56 spilled ones belong to fp32_walk, the
+// barriers; 64-row workgroups get one.  256 registers (head_dim 128): 27 to 60 spilled ones belong to fp32_walk, the
 // walk itself reloads 6 a tile.
 // 24 heads x 128, us on the fp32 instructions -> here, error against float64: 64x64 tokens in 16x16 groups,
 // criss-cross 699 -> 475, 9.1e-7 -> 3.9e-7 (170 TFLOP/s where a large fp32 library product reaches 141 to 154); 2 079

@@ -1,9 +1,11 @@
-"""Compile libgrat.so for gfx950 with hipcc (in-tree, next to this file)."""
+"""Compile libgrat.so for gfx950 with hipcc, and the binding's native part, _binding.so, with the host compiler
+(both in-tree, next to this file)."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -11,6 +13,7 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 CSRC = os.path.join(PKG_DIR, "csrc")
 LIB_PATH = os.path.join(PKG_DIR, "libgrat.so")
+BINDING_PATH = os.path.join(PKG_DIR, "_binding.so")
 # attn_mfma_*.hip: the instantiations of the MFMA kernel template (attn_mfma.h), one slice per
 # element type and head_dim, so that the slow part of the build runs side by side
 SOURCES = ["grat_api.hip", "block_lists.hip", "attn_f32.hip", "mfma_probe.hip", "attn_mfma.hip",
@@ -42,6 +45,22 @@ def _run(cmd, verbose):
     return res.stderr
 
 
+def _binding_command() -> list:
+    """Host code only, against the headers and libraries of the torch it is going to run in."""
+    import torch
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        raise RuntimeError("no host C++ compiler: the binding needs g++")
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
+    return [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+            "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+            "-isystem", os.path.join(rocm, "include"), "-isystem", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "binding.cpp"), "-o", BINDING_PATH, "-L", os.path.join(os.path.dirname(torch.__file__), "lib"),
+            "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+
+
 def build_library(verbose: bool = False, extra_flags=(), jobs: int = 8) -> str:
     """Always recompiles every source (objects go to a scratch directory); returns the library path."""
     hipcc = hipcc_path()
@@ -53,8 +72,10 @@ def build_library(verbose: bool = False, extra_flags=(), jobs: int = 8) -> str:
             src, obj = pair
             return _run([hipcc, *HIPCC_FLAGS, *extra_flags, *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
 
-        with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES)))) as ex:
+        with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES) + 1))) as ex:
+            binding = ex.submit(_run, _binding_command(), verbose)
             warnings = list(ex.map(compile_one, zip(SOURCES, objs)))
+            binding.result()
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH], verbose)
     if verbose:
         for w in warnings:

@@ -1,8 +1,11 @@
-"""Thin ctypes binding over libgrat.so: argument marshalling only.
+"""Thin binding over libgrat.so: argument marshalling only.
 
 PyTorch supplies device memory and the current HIP stream; every step of the attention path
 runs inside the library's kernels.  There is no fallback: if libgrat.so has not been built
 (python -m paper_2505_14687_amd.build) every call raises.
+
+An ordinary call is marshalled by csrc/binding.cpp (_binding.so).  What that does not take (it answers None) goes through
+ctypes here: arguments of unusual types, tensor subclasses, and everything that is refused.
 """
 from __future__ import annotations
 
@@ -12,7 +15,7 @@ from typing import Optional, Sequence, Tuple
 
 import torch
 
-from .build import LIB_PATH
+from .build import BINDING_PATH, LIB_PATH
 
 GRAT_OK = 0
 PATTERNS = {"block": 0, "cross": 1, "cross_planes": 2, "dense": 3}
@@ -24,6 +27,7 @@ EXPORTS = ("grat_block_list_shape", "grat_build_block_lists", "grat_validate_blo
 _i32, _i64, _f32, _vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_void_p
 _pi32 = ctypes.POINTER(ctypes.c_int32)
 _lib = None
+_native = None   # csrc/binding.cpp, entered by way of _lib's entry points
 
 
 class GratError(RuntimeError):
@@ -35,11 +39,12 @@ class GratError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Load libgrat.so (once).  Raises if it is not there: there is no other implementation."""
-    global _lib
+    global _lib, _native
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"{LIB_PATH} is missing: build it with "
-                               "`python -m paper_2505_14687_amd.build` (needs hipcc)")
+        for path in (LIB_PATH, BINDING_PATH):
+            if not os.path.exists(path):
+                raise RuntimeError(f"{path} is missing: build it with "
+                                   "`python -m paper_2505_14687_amd.build` (needs hipcc)")
         L = ctypes.CDLL(LIB_PATH)
         L.grat_block_list_shape.argtypes = [_i32, _pi32, _pi32, _i32, _pi32, _pi32, _pi32]
         L.grat_block_list_shape.restype = _i32
@@ -64,8 +69,19 @@ def lib() -> ctypes.CDLL:
         L.grat_status_string.restype = ctypes.c_char_p
         L.grat_probe_mfma.argtypes = [_i32, _i32, _vp, _i32, _i32, _vp]
         L.grat_probe_mfma.restype = _i32
-        _lib = L
+        from . import _binding
+        _binding.set_library(*(ctypes.cast(f, _vp).value for f in
+                               (L.grat_block_list_shape, L.grat_build_block_lists, L.grat_attention_fwd,
+                                L.grat_attention_global_fwd, L.grat_attention_packed_fwd, L.grat_dense_attention_fwd)))
+        _lib, _native = L, _binding
     return _lib
+
+
+def _result(r, where: str):
+    """What a call through _binding came to: its result, or the library's status."""
+    if type(r) is int:
+        raise GratError(r, where)
+    return r
 
 
 def _ivec(values: Optional[Sequence[int]]):
@@ -98,6 +114,11 @@ def grat_build_block_lists(grid: Sequence[int], group: Sequence[int], pattern,
                            radius: Optional[Sequence[int]] = None, device="cuda",
                            max_kv: Optional[int] = None, stream=None):
     """Build the lists on the GPU.  Returns (kv_count int32 [G], kv_index int32 [G, max_kv])."""
+    lib()
+    if max_kv is None and type(device) is str and device == "cuda":
+        r = _native.block_lists(grid, group, _pattern_id(pattern), radius, stream)
+        if r is not None:
+            return _result(r, "grat_build_block_lists")
     G, need = grat_block_list_shape(grid, group, pattern, radius)
     max_kv = need if max_kv is None else int(max_kv)
     kv_count = torch.empty(G, dtype=torch.int32, device=device)
@@ -179,6 +200,10 @@ def _check_lists(kv_count, kv_index, num_groups: int, device):
 def grat_attention_fwd(Q, K, V, scale: float, grid: Sequence[int], group: Sequence[int],
                        kv_count, kv_index, out=None, stream=None):
     """O = softmax(scale * Q K^T over the listed KV groups) V.  Q, K, V: [B, H, N, d] views."""
+    lib()
+    r = _native.attention(Q, K, V, scale, None, True, grid, group, kv_count, kv_index, out, stream)
+    if r is not None:
+        return _result(r, "grat_attention_fwd")
     O = torch.empty_like(Q) if out is None else out
     if Q.dim() == 4:
         _check_sequence(Q.shape[2], grid)
@@ -199,6 +224,10 @@ def grat_attention_global_fwd(Q, K, V, scale: float, n_global: int, global_first
                               grid: Sequence[int], group: Sequence[int], kv_count, kv_index,
                               out=None, stream=None):
     """Joint sequence of n_global prompt tokens and the grid tokens; Q, K, V: [B, H, n_global + N, d]."""
+    lib()
+    r = _native.attention(Q, K, V, scale, n_global, global_first, grid, group, kv_count, kv_index, out, stream)
+    if r is not None:
+        return _result(r, "grat_attention_global_fwd")
     O = torch.empty_like(Q) if out is None else out
     if Q.dim() == 4:
         _check_sequence(Q.shape[2], grid, n_global)
@@ -220,6 +249,10 @@ def grat_attention_packed_fwd(QKV, scale: float, grid: Sequence[int], group: Seq
                               kv_index, n_global: int = 0, global_first: bool = True, out=None,
                               stream=None):
     """QKV: contiguous [B, L, 3, H, d] (L = n_global + grid tokens); returns O as [B, L, H, d]."""
+    lib()
+    r = _native.packed(QKV, scale, n_global, global_first, grid, group, kv_count, kv_index, out, stream)
+    if r is not None:
+        return _result(r, "grat_attention_packed_fwd")
     if QKV.dim() != 5 or QKV.shape[2] != 3 or not QKV.is_contiguous():
         raise ValueError("expected a contiguous [B, L, 3, H, d] tensor")
     B, L, _, H, d = QKV.shape
@@ -242,6 +275,10 @@ def grat_attention_packed_fwd(QKV, scale: float, grid: Sequence[int], group: Seq
 
 def grat_dense_attention_fwd(Q, K, V, scale: float, out=None, stream=None):
     """O = softmax(scale * Q K^T) V over the whole sequence."""
+    lib()
+    r = _native.dense(Q, K, V, scale, out, stream)
+    if r is not None:
+        return _result(r, "grat_dense_attention_fwd")
     O = torch.empty_like(Q) if out is None else out
     _check_qkvo(Q, K, V, O)
     B, H, N, d = Q.shape

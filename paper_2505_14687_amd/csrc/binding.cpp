@@ -50,8 +50,8 @@ const at::Tensor& tensor_of(PyObject* o) {
     need(t.defined() && t.layout() == at::kStrided && t.has_storage());
     using K = c10::DispatchKey;
     const c10::DispatchKeySet keys = t.key_set();
-    for (const K k : {K::Python, K::PythonTLSSnapshot, K::FuncTorchBatched, K::FuncTorchGradWrapper, K::FuncTorchBatchedDecomposition,
-                      K::Functionalize, K::Negative, K::Conjugate, K::ZeroTensor})
+    for (const K k : {K::Python, K::PythonTLSSnapshot, K::FuncTorchBatched, K::FuncTorchGradWrapper, K::Functionalize,
+                      K::Negative, K::Conjugate, K::ZeroTensor})
         need(!keys.has(k));
     return t;
 }

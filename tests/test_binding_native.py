@@ -41,6 +41,10 @@ def test_both_ways_give_the_same_and_refuse_the_same():
     ints = [np.int64(t) for t in GRID]
     want = grat.grat_attention_fwd(q, k, v, 0.125, ints, GROUP, cnt, idx)                           # the long way
     assert binding._native.attention(q, k, v, 0.125, None, True, ints, GROUP, cnt, idx, None, None) is None
+    n, qkv = binding._native, torch.randn(1, 1024, 3, 2, 64, generator=g, device="cuda")
+    for r in (n.attention(q, k, v, 0.125, None, True, GRID, GROUP, cnt, idx, None, None), n.dense(q, k, v, 0.125, None, None),
+              n.packed(qkv, 0.125, 0, True, GRID, GROUP, cnt, idx, None, None), n.block_lists(GRID, GROUP, 0, (1, 1), None)[0]):
+        assert isinstance(r, torch.Tensor)                                                          # ordinary calls
     got = grat.grat_attention_fwd(q, k, v, 0.125, GRID, GROUP, cnt, idx)
     assert torch.equal(got, want) and got.stride() == want.stride()
     out = torch.full_like(q, float("nan"))

@@ -563,7 +563,9 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 // from the listed groups laid end to end, each padded to a multiple of 16 tokens - groups of fewer than
 // 16 tokens are not padded but packed, several to a block.  Where the tiles alone fill the chip a workgroup is one
 // wave (NW = 1), which has all the keys and nothing to merge.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
-// with the list building: 390 us with one query per lane (32 waves in all), 28 us here, most of it host time.
+// with the list building: 390 us with one query per lane (32 waves in all), 15.5 us here (the matrix instructions of the
+// 128 workgroups take 4 us of the 12 of this kernel; entries read ahead of the count and no ranking of lists took it
+// from 13.6, launches of a graph).
 // Two workgroups a compute unit where LDS has room for them (head_dim 64: 33 of 160 KiB, four waves a SIMD, 128
 // registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, eight waves, 182
 // us against 122).
@@ -589,14 +591,10 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void attn_f32_split_kerne
         return DENSE ? t : token_row(p, qb, t);
     };
 
-    const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
-    if (cnt == 0) {
-        if (wave == 0 && qt * 16 + col < q_tokens) nothing_attended<D / 16>(out_row(p, b_idx, h_idx, query_row(col)) + quarter * (D / 4));
-        return;
-    }
-    const int n_blocks = DENSE ? (p.n_tokens + 15) / 16 : (int)(((int64_t)cnt * p.pad_tokens + 15) / 16);
     // block b: lane looks after key `col` of it.  The group it belongs to is read one block before its rows
-    // are needed, its K and V one block before they are multiplied.
+    // are needed, its K and V one block before they are multiplied.  (Entries are read without regard to the list's
+    // count, so that the first of them do not wait for it: those behind the last one are padding, forced into range
+    // like any other, and their keys do not exist.)
     auto entry_of = [&](int b, uint32_t& t) -> int {
         uint32_t e;
         fdivmod((uint32_t)(16 * b + col), p.fd_pad_tokens, e, t);
@@ -605,8 +603,15 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void attn_f32_split_kerne
     auto read_gid = [&](int b) -> uint32_t {
         if (DENSE) return 0;
         uint32_t t;
-        return list_entry(p, gamma, min(entry_of(min(b, n_blocks - 1), t), cnt - 1));
+        return list_entry(p, gamma, min(entry_of(b, t), p.max_kv - 1));
     };
+    uint32_t gid0 = read_gid(wave), gid1 = read_gid(wave + NW);
+    const int cnt = DENSE ? 1 : min(max(p.kv_count[gamma], 0), p.max_kv);
+    if (cnt == 0) {
+        if (wave == 0 && qt * 16 + col < q_tokens) nothing_attended<D / 16>(out_row(p, b_idx, h_idx, query_row(col)) + quarter * (D / 4));
+        return;
+    }
+    const int n_blocks = DENSE ? (p.n_tokens + 15) / 16 : (int)(((int64_t)cnt * p.pad_tokens + 15) / 16);
     struct Block {
         f32x4 k[D / 16], v[4][NP];
         uint64_t valid;   // bit l: lane l's key exists
@@ -636,7 +641,6 @@ __global__ __launch_bounds__(NW * 64, D == 64 ? 4 : 2) void attn_f32_split_kerne
         }
     };
 
-    uint32_t gid0 = read_gid(wave), gid1 = read_gid(wave + NW);
     // Q^T (B operand): q[j][s] = dim 16 * j + 4 * quarter + s of query `col`
     f32x4 q[D / 16];
     {

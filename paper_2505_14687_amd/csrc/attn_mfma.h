@@ -177,11 +177,14 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     uint32_t* s_limit = s_origin + p.max_kv;
     uint32_t q_limit = 0;   // kRagged: the same limit for the query group
     // kRagged: index of the last token of a box that is inside the grid, and the tiles of the box up to it
-    // (later ones would only add weights of 0: 90x160 tokens in 16x16 groups, half, 2 x 24 heads: 784 -> 762 us
+    // (later ones would only add weights of 0: 90x160 tokens in 16x16 groups, half, 2 x 24 heads: 3 % of the time
     // for 2 of 64 tiles a column of groups)
     auto last_inside = [&](uint32_t lim) { return (int)(((lim >> 20) * geo.g[1] + ((lim >> 10) & 1023u)) * geo.g[2] + (lim & 1023u)); };
     auto box_tiles = [&](uint32_t lim) { return last_inside(lim) / kBN + 1; };
     const uint32_t row_pitch = (uint32_t)stride_n * 2u;   // bytes between consecutive tokens
+    const uint32_t full_box = pack_coord(geo.g[0] - 1, geo.g[1] - 1, geo.g[2] - 1);
+    bool clipped = false;   // kRagged: this workgroup's query group or one it attends is cut by the border
+    bool active = true;     // kRagged: one of this wave's queries is inside the grid
 
     int n_tiles;        // KV tiles to walk
     int tiles_per_group = 1;
@@ -245,6 +248,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             if (MODE == kRagged) {
                 q_limit = box_limit(gamma);
                 if (qt * BM > last_inside(q_limit)) return;   // no query of this workgroup is inside the grid
+                active = q_first <= last_inside(q_limit);
                 if (!coord_inside(pack_coord(c0, c1, c2), q_limit)) off = 0;   // a query outside the grid: any valid row will do
             }
             const uint8_t* src = (const uint8_t*)Qh + (uint64_t)q_base * row_pitch + off + 16 * half;
@@ -274,11 +278,16 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         }
         n_tiles = n_lead + cnt * tiles_per_group;
         if (MODE == kRagged) {
-            n_tiles = 0;
-            for (int i = lane; i < cnt; i += 64) n_tiles += box_tiles(s_limit[i]);
+            bool cut = q_limit != full_box;
+            for (int i = lane; i < cnt; i += 64) cut = cut || s_limit[i] != full_box;
+            clipped = __builtin_amdgcn_ballot_w64(cut) != 0;
+            if (clipped) {
+                n_tiles = 0;
+                for (int i = lane; i < cnt; i += 64) n_tiles += box_tiles(s_limit[i]);
 #pragma unroll
-            for (int m = 1; m < 64; m *= 2) n_tiles += __shfl_xor(n_tiles, m);
-            n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+                for (int m = 1; m < 64; m *= 2) n_tiles += __shfl_xor(n_tiles, m);
+                n_tiles = __builtin_amdgcn_readfirstlane(n_tiles);
+            }
         }
         n_listed = cnt;
     }
@@ -346,7 +355,9 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     };
     // Offsets of a tile are looked up one tile before it is fetched, so the table reads never sit
     // between a barrier and the loads that follow it.
-    auto tile_addr = [&](TileAddr& a, const uint32_t* col, int t, int& gi, int& j) {
+    // (clip: the walk of a workgroup that has to do with a clipped group, see `walk`)
+    auto tile_addr = [&](auto clip, TileAddr& a, const uint32_t* col, int t, int& gi, int& j) {
+        constexpr bool kClip = MODE == kRagged && decltype(clip)::value;
         if (dense) {
             // consecutive rows of the whole sequence; rows past the end re-read the last token (masked later)
             a.base = (uint32_t)(t * kBN);
@@ -369,14 +380,14 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         } else {
             a.base = __builtin_amdgcn_readfirstlane(s_origin[min(gi, n_listed - 1)]);   // (may be asked past the end)
             int tiles_here = tiles_per_group;
-            if (MODE == kRagged) tiles_here = box_tiles(__builtin_amdgcn_readfirstlane(s_limit[min(gi, n_listed - 1)]));
-            // kRagged: rows of the box beyond the last token of the sequence are pulled back onto it
+            if (kClip) tiles_here = box_tiles(__builtin_amdgcn_readfirstlane(s_limit[min(gi, n_listed - 1)]));
+            // kClip: rows of the box beyond the last token of the sequence are pulled back onto it
             const uint64_t to_end = (uint64_t)((uint32_t)geo.n_tokens - 1u - a.base) * row_pitch;
             const uint32_t max_off = to_end > 0xffffffffull ? 0xffffffffu : (uint32_t)to_end;
 #pragma unroll
             for (int k = 0; k < LPW; ++k) {
                 const uint32_t o = s_rowbytes[j * kBN + load_row[k]];
-                a.off[k] = (MODE == kRagged ? min(o, max_off) : o) + col[k];
+                a.off[k] = (kClip ? min(o, max_off) : o) + col[k];
             }
             if (++j == tiles_here) { j = 0; ++gi; }
         }
@@ -446,7 +457,6 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // outside the grid get weight 0.  (The first block of every box holds its first token, which is
     // always inside, so the first block of a walk never ends up without a finite score.)
     int gi_m = 0, j_m = 0;   // list entry / tile-in-group of the tile whose scores are being weighted
-    const uint32_t full_box = pack_coord(geo.g[0] - 1, geo.g[1] - 1, geo.g[2] - 1);
     auto mask_outside = [&](int kb) {
         const uint32_t lim = __builtin_amdgcn_readfirstlane(s_limit[min(gi_m, n_listed - 1)]);
         if (lim != full_box) {
@@ -496,11 +506,15 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     };
 
     // ---- prologue: K tile 0 -----------------------------------------------------------------
-    tile_addr(ka, load_kcol, 0, gi_k, j_k);
-    issue_tile(Kh, sK[0], ka);
-    if (dense) tile_addr(va, load_vcol, 0, gi_v, j_v);
-    else v_from_k(va, ka);
-    if (1 < n_tiles) tile_addr(ka, load_kcol, 1, gi_k, j_k);
+    TileAddr vb{};
+    auto start = [&](auto clip) {
+        tile_addr(clip, ka, load_kcol, 0, gi_k, j_k);
+        issue_tile(Kh, sK[0], ka);
+        if (dense) tile_addr(clip, va, load_vcol, 0, gi_v, j_v);
+        else v_from_k(va, ka);
+        vb = va;
+        if (1 < n_tiles) tile_addr(clip, ka, load_kcol, 1, gi_k, j_k);
+    };
 
     // swap_barrier(t) publishes K(t) and V(t-1), fetched during the previous tile, and frees the
     // buffers of K(t-1) and V(t-2), which are refilled with K(t+1) and V(t) right away.
@@ -509,14 +523,13 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // 32-key tiles (2-wave workgroups): a step is a single 32-key block, so PV trails QK by two tiles
     // and V(t) is only fetched at barrier t+1, into the buffer V(t-2) was read from during step t;
     // vb = where V(t-1) lies, one tile behind va.
-    TileAddr vb = va;
-    auto next_addrs = [&](int t) {
+    auto next_addrs = [&](auto clip, int t) {
         // (looked up unconditionally, also past the last tile, so that the table reads stay inside the
         // straight-line block around them instead of becoming a block of their own with its own waits)
         if (kBN == 32) vb = va;
-        if (dense) tile_addr(va, load_vcol, t + 1, gi_v, j_v);
+        if (dense) tile_addr(clip, va, load_vcol, t + 1, gi_v, j_v);
         else v_from_k(va, ka);   // tile t + 1, whose K part has just been asked for
-        tile_addr(ka, load_kcol, t + 2, gi_k, j_k);
+        tile_addr(clip, ka, load_kcol, t + 2, gi_k, j_k);
     };
     auto swap_barrier = [&](int t) {
         __builtin_amdgcn_s_waitcnt(0);   // this wave's direct-to-LDS loads have landed
@@ -534,7 +547,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // sK[kbuf]; SM: weights of the block whose scores are in S[KB ^ 1] (0 none, 1 against the current
     // reference, 2 first block of the walk: the reference is its maximum); PV: O^T += V^T P^T for
     // half KB of the V tile in sV[vbuf], with the weights in pw[KB].  check: the walk contains a tile
-    // with fewer than 64 valid keys; t_sm0 / t_sm1 = tile index of the block weighted in each half.
+    // with fewer than 64 valid keys (kRagged: has to do with a clipped group); t_sm0 / t_sm1 = tile index of the block weighted in each half.
     // The items (one MFMA each, with its fragment read kFragAhead items ahead) run in one rolling
     // sequence over both halves; the vector chunks of a half are dealt out over its items.
     auto step = [&](auto qk0_c, auto sm0_c, auto pv0_c, auto qk1_c, auto sm1_c, auto pv1_c, auto check, auto kbuf_c,
@@ -556,9 +569,9 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             if (SMm[h] == 0) return;
             const int sb = h ^ 1;
             if constexpr (decltype(check)::value) {
-                if ((h ? t_sm1 : t_sm0) == mask_tile) mask_tail(sb);
+                if constexpr (MODE == kRagged) mask_outside(sb);
+                else if ((h ? t_sm1 : t_sm0) == mask_tile) mask_tail(sb);
             }
-            if (MODE == kRagged) mask_outside(sb);
             if (SMm[h] == 2) m_ref = block_max(sb);
             mc = m_ref * c;
         };
@@ -629,25 +642,30 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     constexpr std::false_type no{};
     constexpr std::true_type yes{};
 
+    // kRagged: a workgroup whose own group and listed groups are all whole takes the plain walk; in the others (clip) border
+    // keys are masked, and waves without a query inside the grid only fetch (90x160 tokens, 16x16 groups, half, 2 x
+    // 24 heads: two thirds of the workgroups take the plain walk; 760 -> 741 us, head_dim 64, 250x250 tokens 990 -> 950).
+    auto busy = [&](auto check) { return MODE != kRagged || !decltype(check)::value || active; };
     if constexpr (kBN == 64) {
         // tile 0: both QK products, and the weights of its first block against that block's maximum
-        {
+        auto first_tile = [&](auto clip) {
+            start(clip);
             swap_barrier(0);
-            next_addrs(0);
+            next_addrs(clip, 0);
             if (!kLists && mask_tile == 0) {
                 step(yes, c0, no, no, c0, no, no, c0, 0, 0, 0);
                 mask_tail(0);
                 step(no, c0, no, yes, c2, no, no, c0, 0, 0, 0);
-            } else {
-                step(yes, c0, no, yes, c2, no, no, c0, 0, 0, 0);
+            } else if (busy(clip)) {
+                step(yes, c0, no, yes, c2, no, clip, c0, 0, 0, 0);
             }
-        }
+        };
         // tile t >= 1, first half: QK(t, keys 0..31), weights of (t-1, keys 32..63), PV of (t-1, keys 0..31);
         // second half: QK(t, 32..63), weights of (t, 0..31), PV of (t-1, 32..63)
         auto tile_step = [&](auto check, auto kbuf, int t) {   // kbuf = t & 1, as a compile-time constant
             swap_barrier(t);
-            next_addrs(t);
-            step(yes, c1, yes, yes, c1, yes, check, kbuf, kbuf ^ 1, t - 1, t);
+            next_addrs(check, t);
+            if (busy(check)) step(yes, c1, yes, yes, c1, yes, check, kbuf, kbuf ^ 1, t - 1, t);
         };
         auto walk = [&](auto check) {
             int t = 1;   // (two steps per trip: the LDS buffers of every step are compile-time constants)
@@ -657,20 +675,33 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             }
             if (t < n_tiles) tile_step(check, c1, t);
             swap_barrier(n_tiles);
-            step(no, c1, yes, no, c0, yes, check, c0, (n_tiles - 1) & 1, n_tiles - 1, n_tiles - 1);
+            if (busy(check)) step(no, c1, yes, no, c0, yes, check, c0, (n_tiles - 1) & 1, n_tiles - 1, n_tiles - 1);
         };
-        if (!kLists && mask_tile >= 0) walk(yes);
-        else walk(no);
+        if constexpr (MODE == kRagged) {
+            if (clipped) {
+                first_tile(yes);
+                walk(yes);
+            } else {
+                first_tile(no);
+                walk(no);
+            }
+        } else {
+            first_tile(no);
+            if (!kLists && mask_tile >= 0) walk(yes);
+            else walk(no);
+        }
     } else {
         // 32-key tiles: the step behind barrier b forms the scores of tile b, weights tile b-1 and adds
         // tile b-2 to O^T, all in the half (of S, pw and of the K and V buffers) of its parity.
         auto block_step = [&](auto check, auto par, auto qk, auto sm, auto pv, int b) {
             swap_barrier(b);
-            next_addrs(b);
+            next_addrs(check, b);
+            if (!busy(check)) return;
             if constexpr (decltype(par)::value == 0) step(qk, sm, pv, no, c0, no, check, c0, 0, b - 1, 0);
             else step(no, c0, no, qk, sm, pv, check, c1, 1, 0, b - 1);
         };
         auto walk = [&](auto check) {
+            start(check);
             block_step(check, c0, yes, c0, no, 0);
             if (n_tiles > 1) block_step(check, c1, yes, c2, no, 1);
             else block_step(check, c1, no, c2, no, 1);
@@ -689,7 +720,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             if (b & 1) block_step(check, c1, no, c0, yes, b);
             else block_step(check, c0, no, c0, yes, b);
         };
-        if (!kLists && mask_tile >= 0) walk(yes);
+        if (MODE == kRagged ? clipped : !kLists && mask_tile >= 0) walk(yes);
         else walk(no);
     }
 

@@ -65,11 +65,21 @@ def test_clipped_boxes(grid, group, d):
     _groups(grid, group, d)
 
 
-def _groups(grid, group, d):
-    pattern = "cross" if grid == (80, 528) else "block"
+# one launch with workgroups that take the plain walk (nothing clipped in reach) and ones that do not, whose last token
+# inside the grid is the last of a wave's 32 queries, or the next; 4 heads of 130x256: 256-row workgroups at head_dim 128
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grid,group,heads", [((66, 48), (16, 16), 2), ((67, 48), (16, 16), 2), ((78, 70), (16, 16), 2),
+                                              ((130, 256), (16, 16), 4), ((36, 24), (8, 8), 2), ((37, 44), (8, 8), 2),
+                                              ((9, 20, 24), (2, 8, 8), 2), ((40, 648), (8, 8), 1)])
+def test_clipped_beside_whole_groups(grid, group, heads, d):
+    _groups(grid, group, d, heads)
+
+
+def _groups(grid, group, d, heads=None):
+    pattern = "cross" if grid in ((80, 528), (40, 648)) else "block"
     n = math.prod(grid)
     dtype = torch.bfloat16
-    q, k, v = _inputs(1, 1 if n > 10000 else 2, n, d, dtype, 7100 + n)
+    q, k, v = _inputs(1, heads or (1 if n > 10000 else 2), n, d, dtype, 7100 + n)
     radius = (1,) * len(grid)
     count, index = grat.grat_build_block_lists(grid, group, pattern, radius)
     out = torch.full_like(q, float("nan"))

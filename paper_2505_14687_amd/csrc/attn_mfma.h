@@ -127,11 +127,17 @@ __device__ __forceinline__ bool coord_inside(uint32_t c, uint32_t lim) {
 //
 // One query tile: tile t_in_head of its kind in (batch, head) bh.  DENSE: it is a tile of consecutive
 // query rows that walks the whole sequence (always in kDense, the prompt rows in kJoint), else a
-// tile of one query group.  sK / sV: the workgroup's two K and two V tile buffers in LDS.
-template <int NWAVES, int BN, int MODE, bool F16, int D, bool DENSE>
+// tile of one query group.  k_tiles / v_tiles: the workgroup's tile buffers in LDS, two for K and two for V of every
+// team (of several teams: V's right behind K's).
+//
+// TEAMS > 1 (small launches): the workgroup is that many teams of NWAVES waves; every team owns all its queries
+// and walks the KV tiles team, team + TEAMS, ... in buffers of its own, and the results are merged through LDS at
+// the end.
+template <int NWAVES, int BN, int MODE, bool F16, int D, bool DENSE, int TEAMS>
 __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, const int t_in_head,
-                                          uint8_t (*sK)[BN * D * 2], uint8_t (*sV)[BN * D * 2],
+                                          uint8_t (*k_tiles)[BN * D * 2], uint8_t (*v_tiles)[BN * D * 2],
                                           const int gamma_fixed = -1) {
+    static_assert(TEAMS == 1 || MODE != kRagged, "tiles are dealt to teams by their number, boxes all of one size");
     static_assert(BN == 64 || (BN == 32 && NWAVES == 2), "64-key tiles, or 32-key tiles for 2-wave workgroups");
     constexpr int kBN = BN;
     constexpr int kRowBytes = D * 2;          // of a token
@@ -139,7 +145,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     constexpr int kTileBytes = kBN * kRowBytes;
     static_assert(D == 128 || D == 64, "head_dim 128 or 64");
     using E = Elem<F16>;
-    constexpr int NT = NWAVES * 64;
+    constexpr int NT = NWAVES * TEAMS * 64;
     constexpr int BM = NWAVES * 32;
     constexpr int LPW = kTileBytes / (1024 * NWAVES);   // 1-KiB direct loads (4 or 8 token rows) per wave per tile
     constexpr bool dense = DENSE;
@@ -150,7 +156,11 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_in_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int team = TEAMS == 1 ? 0 : wave_in_wg / NWAVES;
+    const int wave = TEAMS == 1 ? wave_in_wg : wave_in_wg % NWAVES;   // in its team
+    uint8_t (*const sK)[kTileBytes] = k_tiles + 2 * team;
+    uint8_t (*const sV)[kTileBytes] = v_tiles + 2 * team;
     const int qcol = lane & 31;   // query within the wave's 32
     const int half = lane >> 5;
 
@@ -292,6 +302,11 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         n_listed = cnt;
     }
     if (n_tiles == 0) return;   // an empty list is outside the contract; never touch memory for it
+    const int n_longest = (n_tiles + TEAMS - 1) / TEAMS;   // tiles of the team with most
+    if constexpr (TEAMS > 1) {   // from here on tiles are counted within the team
+        if (mask_tile >= 0) mask_tile = mask_tile % TEAMS == team ? mask_tile / TEAMS : -1;
+        n_tiles = (n_tiles - team + TEAMS - 1) / TEAMS;
+    }
     // byte offset inside the head of row i of this wave's 32 query (= output) rows; the rows of a
     // dense tile past the last query re-read the last one and are never stored
     auto q_row_off = [&](int i) -> uint64_t {
@@ -358,6 +373,14 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // (clip: the walk of a workgroup that has to do with a clipped group, see `walk`)
     auto tile_addr = [&](auto clip, TileAddr& a, const uint32_t* col, int t, int& gi, int& j) {
         constexpr bool kClip = MODE == kRagged && decltype(clip)::value;
+        if constexpr (TEAMS > 1) {   // back to the number of the tile in the walk of all teams
+            t = t * TEAMS + team;
+            if (!dense) {
+                const uint32_t u = (uint32_t)max(0, t - n_lead);
+                gi = (int)fdiv(u, p.fd_group_tiles);
+                j = (int)u - gi * tiles_per_group;
+            }
+        }
         if (dense) {
             // consecutive rows of the whole sequence; rows past the end re-read the last token (masked later)
             a.base = (uint32_t)(t * kBN);
@@ -572,7 +595,12 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
                 if constexpr (MODE == kRagged) mask_outside(sb);
                 else if ((h ? t_sm1 : t_sm0) == mask_tile) mask_tail(sb);
             }
-            if (SMm[h] == 2) m_ref = block_max(sb);
+            if (SMm[h] == 2) {
+                m_ref = block_max(sb);
+                // (what is a team's first block would be a later one of an undivided walk, where scores of -infinity
+                // only weigh 0: any reference that later scores replace)
+                if (TEAMS > 1 && m_ref == -INFINITY) m_ref = -1e38f / fmaxf(c, 1.f);
+            }
             mc = m_ref * c;
         };
         // two vector chunks per pair of scores: {fma, fma, exp2} and {exp2, pack, add, add}
@@ -645,7 +673,15 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // kRagged: a workgroup whose own group and listed groups are all whole takes the plain walk; in the others (clip) border
     // keys are masked, and waves without a query inside the grid only fetch (90x160 tokens, 16x16 groups, half, 2 x
     // 24 heads: two thirds of the workgroups take the plain walk; 760 -> 741 us, head_dim 64, 250x250 tokens 990 -> 950).
-    auto busy = [&](auto check) { return MODE != kRagged || !decltype(check)::value || active; };
+    // (A loop of their own for those waves: a branch around the steps of the others would end the straight-line code that
+    // covers the table reads, 1.6 % at 97x70 tokens, head_dim 64.)
+    auto fetch_only = [&]() {
+        start(yes);
+        for (int t = 0; t < n_tiles + (kBN == 64 ? 1 : 2); ++t) {   // as many barriers as the walks below have
+            swap_barrier(t);
+            next_addrs(yes, t);
+        }
+    };
     if constexpr (kBN == 64) {
         // tile 0: both QK products, and the weights of its first block against that block's maximum
         auto first_tile = [&](auto clip) {
@@ -656,7 +692,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
                 step(yes, c0, no, no, c0, no, no, c0, 0, 0, 0);
                 mask_tail(0);
                 step(no, c0, no, yes, c2, no, no, c0, 0, 0, 0);
-            } else if (busy(clip)) {
+            } else {
                 step(yes, c0, no, yes, c2, no, clip, c0, 0, 0, 0);
             }
         };
@@ -665,7 +701,7 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         auto tile_step = [&](auto check, auto kbuf, int t) {   // kbuf = t & 1, as a compile-time constant
             swap_barrier(t);
             next_addrs(check, t);
-            if (busy(check)) step(yes, c1, yes, yes, c1, yes, check, kbuf, kbuf ^ 1, t - 1, t);
+            step(yes, c1, yes, yes, c1, yes, check, kbuf, kbuf ^ 1, t - 1, t);
         };
         auto walk = [&](auto check) {
             int t = 1;   // (two steps per trip: the LDS buffers of every step are compile-time constants)
@@ -675,10 +711,13 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             }
             if (t < n_tiles) tile_step(check, c1, t);
             swap_barrier(n_tiles);
-            if (busy(check)) step(no, c1, yes, no, c0, yes, check, c0, (n_tiles - 1) & 1, n_tiles - 1, n_tiles - 1);
+            step(no, c1, yes, no, c0, yes, check, c0, (n_tiles - 1) & 1, n_tiles - 1, n_tiles - 1);
         };
-        if constexpr (MODE == kRagged) {
-            if (clipped) {
+        if (TEAMS > 1 && n_tiles == 0) {
+        } else if constexpr (MODE == kRagged) {
+            if (clipped && !active) {
+                fetch_only();
+            } else if (clipped) {
                 first_tile(yes);
                 walk(yes);
             } else {
@@ -696,7 +735,6 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         auto block_step = [&](auto check, auto par, auto qk, auto sm, auto pv, int b) {
             swap_barrier(b);
             next_addrs(check, b);
-            if (!busy(check)) return;
             if constexpr (decltype(par)::value == 0) step(qk, sm, pv, no, c0, no, check, c0, 0, b - 1, 0);
             else step(no, c0, no, qk, sm, pv, check, c1, 1, 0, b - 1);
         };
@@ -720,8 +758,84 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             if (b & 1) block_step(check, c1, no, c0, yes, b);
             else block_step(check, c0, no, c0, yes, b);
         };
-        if (MODE == kRagged ? clipped : !kLists && mask_tile >= 0) walk(yes);
-        else walk(no);
+        if (TEAMS > 1 && n_tiles == 0) {
+        } else if (MODE == kRagged && clipped && !active) {
+            fetch_only();
+        } else if (MODE == kRagged ? clipped : !kLists && mask_tile >= 0) {
+            walk(yes);
+        } else {
+            walk(no);
+        }
+    }
+
+    // ---- merge of the teams -------------------------------------------------------------------
+    // Every team leaves its O (fp32, [query][16-byte chunks, the chunk number XORed with the query]), reference and
+    // sum in LDS; a thread then adds up a share of one query's head dims.
+    if constexpr (TEAMS > 1) {
+        constexpr int kMore = BN == 64 ? 1 : 2;   // barriers of a walk beside its tiles
+        for (int i = n_tiles == 0 ? 0 : n_tiles + kMore; i < n_longest + kMore; ++i) __syncthreads();
+        __syncthreads();   // everyone has finished with the tile buffers
+        static_assert(TEAMS * BM * D * 4 == 4 * TEAMS * kTileBytes, "the partial results fill the tile buffers");
+        constexpr int kChunks = D / 4;
+        __shared__ float s_m[TEAMS][BM], s_l[TEAMS][BM];
+        float* const part = (float*)&k_tiles[0][0];
+        {
+            const int row = wave * 32 + qcol;
+            float* const dst = part + (team * BM + row) * D;
+#pragma unroll
+            for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) {
+                    const f32x16& o = oacc[db];
+                    *(float4*)(dst + 4 * ((8 * db + 2 * rq + half) ^ (row % kChunks))) =
+                        make_float4(o[4 * rq], o[4 * rq + 1], o[4 * rq + 2], o[4 * rq + 3]);
+                }
+            const float l = sum_across_halves(l_run);
+            if (half == 0) {
+                s_m[team][row] = m_ref;
+                s_l[team][row] = l;
+            }
+        }
+        __syncthreads();
+        constexpr int TPR = NT / BM, kPieces = D / 8 / TPR;   // threads of a row; 16-byte pieces of the output row for each
+        const int row = tid / TPR, sub = tid % TPR, q_tile = q_first - wave * 32;
+        if (dense && q_tile + row >= p.n_dense_rows) return;
+        float M = s_m[0][row], f[TEAMS], sum = 0.f;
+#pragma unroll
+        for (int w = 1; w < TEAMS; ++w) M = fmaxf(M, s_m[w][row]);
+#pragma unroll
+        for (int w = 0; w < TEAMS; ++w) {   // (a team without tiles: weight 0)
+            f[w] = __builtin_amdgcn_exp2f((s_m[w][row] - M) * c);
+            sum = fmaf(f[w], s_l[w][row], sum);
+        }
+        const float inv = 1.f / sum;
+        const uint64_t out_row = dense ? (uint64_t)(uint32_t)(p.dense_row0 + q_tile + row)
+                                       : (uint64_t)(q_base + s_rowbytes[q_tile + row] / row_pitch);
+        uint8_t* const dst = (uint8_t*)Oh + out_row * ((uint32_t)p.o_stride_n * 2u);
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int piece = i * TPR + sub;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = 0.f;
+#pragma unroll
+            for (int w = 0; w < TEAMS; ++w)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const float4 v = *(const float4*)(part + (w * BM + row) * D + 4 * ((2 * piece + u) ^ (row % kChunks)));
+                    x[4 * u] = fmaf(f[w], v.x, x[4 * u]);
+                    x[4 * u + 1] = fmaf(f[w], v.y, x[4 * u + 1]);
+                    x[4 * u + 2] = fmaf(f[w], v.z, x[4 * u + 2]);
+                    x[4 * u + 3] = fmaf(f[w], v.w, x[4 * u + 3]);
+                }
+            uint4 v;
+            v.x = E::pack(x[0] * inv, x[1] * inv);
+            v.y = E::pack(x[2] * inv, x[3] * inv);
+            v.z = E::pack(x[4] * inv, x[5] * inv);
+            v.w = E::pack(x[6] * inv, x[7] * inv);
+            *(uint4*)(dst + 16 * piece) = v;
+        }
+        return;
     }
 
     // ---- epilogue: normalise, round to bf16, store ------------------------------------------
@@ -797,38 +911,59 @@ constexpr int waves_per_simd(int nwaves, int bn, int mode, int d) {
 
 // The kernel: picks this workgroup's query tile (tile_order.h) and runs it.  In joint mode the long-running
 // dense tiles over the prompt rows get the lowest block indices, dealt round-robin over the XCDs, and the
-// grouped tiles follow.
+// grouped tiles follow.  (Both ways to pick a grouped tile lead to one copy of its code: with a copy each, of the 512x512
+// token kernels some spilled 5 to 21 scalar registers, clipped grids 13 to 66; 250x250 tokens 1 640 -> 1 620 us.  The 8-wave
+// joint kernel is 1 % faster with two: 128x128 tokens, 512 prompt tokens 537 against 543 us.)
 template <int NWAVES, int BN, int MODE, bool F16, int D>
 __global__ __launch_bounds__(NWAVES * 64, waves_per_simd(NWAVES, BN, MODE, D)) void attn_mfma_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t sK[2][BN * D * 2];
     __shared__ __attribute__((aligned(1024))) uint8_t sV[2][BN * D * 2];
-    const int xcd = blockIdx.x % kNumXcd, idx = blockIdx.x / kNumXcd;
-    int bh, t_in_head;
-    if constexpr (MODE == kJoint) {
-        const int dense_per_xcd = (p.n_dense_tiles + kNumXcd - 1) / kNumXcd;
-        if (idx < dense_per_xcd) {
-            const int tile = idx * kNumXcd + xcd;
-            if (tile < p.n_dense_tiles) {
-                dense_tile(p, tile, bh, t_in_head);
-                attn_tile<NWAVES, BN, MODE, F16, D, true>(p, bh, t_in_head, sK, sV);
-            }
-        } else if (p.longest_first) {
-            int qt, gamma;
-            if (longest_first_tile(p, (int)blockIdx.x - dense_per_xcd * kNumXcd, bh, qt, gamma))
-                attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, qt, sK, sV, gamma);
-        } else if (head_sync_tile(p, xcd, idx - dense_per_xcd, bh, t_in_head)) {
-            attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, t_in_head, sK, sV);
+    const int first_grouped = MODE == kDense ? p.n_dense_tiles : MODE == kJoint ? (p.n_dense_tiles + kNumXcd - 1) / kNumXcd * kNumXcd : 0;
+    const int block = (int)blockIdx.x - first_grouped;
+    int bh, tile;
+    if constexpr (MODE == kDense || MODE == kJoint) {
+        if (MODE == kDense || block < 0) {
+            if (MODE == kJoint && (int)blockIdx.x >= p.n_dense_tiles) return;
+            dense_tile(p, (int)blockIdx.x, bh, tile);
+            attn_tile<NWAVES, BN, MODE, F16, D, true, 1>(p, bh, tile, sK, sV);
+            return;
         }
-    } else if constexpr (MODE == kDense) {
-        dense_tile(p, (int)blockIdx.x, bh, t_in_head);
-        attn_tile<NWAVES, BN, MODE, F16, D, true>(p, bh, t_in_head, sK, sV);
-    } else if (p.longest_first) {
-        int qt, gamma;
-        if (longest_first_tile(p, (int)blockIdx.x, bh, qt, gamma))
-            attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, qt, sK, sV, gamma);
-    } else {
-        if (head_sync_tile(p, xcd, idx, bh, t_in_head))
-            attn_tile<NWAVES, BN, MODE, F16, D, false>(p, bh, t_in_head, sK, sV);
+    }
+    if constexpr (MODE == kJoint && NWAVES == 8) {
+        int gamma;
+        if (p.longest_first) {
+            if (longest_first_tile(p, block, bh, tile, gamma))
+                attn_tile<NWAVES, BN, MODE, F16, D, false, 1>(p, bh, tile, sK, sV, gamma);
+        } else if (head_sync_tile(p, block % kNumXcd, block / kNumXcd, bh, tile)) {
+            attn_tile<NWAVES, BN, MODE, F16, D, false, 1>(p, bh, tile, sK, sV);
+        }
+    } else if constexpr (MODE != kDense) {
+        int gamma = -1;
+        if (p.longest_first ? longest_first_tile(p, block, bh, tile, gamma) : head_sync_tile(p, block % kNumXcd, block / kNumXcd, bh, tile))
+            attn_tile<NWAVES, BN, MODE, F16, D, false, 1>(p, bh, tile, sK, sV, gamma);
+    }
+}
+
+// Small launches: eight waves in teams of NWAVES that share the keys.  (The lines that pick the tile stand here again: in a
+// function of their own they cost the kernel above registers, 8192^2 pixels in 16x16 groups 1 %.)
+template <int NWAVES, int BN, int MODE, bool F16, int D, int TEAMS>
+__global__ __launch_bounds__(NWAVES * TEAMS * 64, 2) void attn_mfma_teams_kernel(AttnParams p) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[4 * TEAMS][BN * D * 2];
+    const int first_grouped = MODE == kDense ? p.n_dense_tiles : MODE == kJoint ? (p.n_dense_tiles + kNumXcd - 1) / kNumXcd * kNumXcd : 0;
+    const int block = (int)blockIdx.x - first_grouped;
+    int bh, tile;
+    if constexpr (MODE == kDense || MODE == kJoint) {
+        if (MODE == kDense || block < 0) {
+            if (MODE == kJoint && (int)blockIdx.x >= p.n_dense_tiles) return;
+            dense_tile(p, (int)blockIdx.x, bh, tile);
+            attn_tile<NWAVES, BN, MODE, F16, D, true, TEAMS>(p, bh, tile, lds, lds + 2 * TEAMS);
+            return;
+        }
+    }
+    if constexpr (MODE != kDense) {
+        int gamma = -1;
+        if (p.longest_first ? longest_first_tile(p, block, bh, tile, gamma) : head_sync_tile(p, block % kNumXcd, block / kNumXcd, bh, tile))
+            attn_tile<NWAVES, BN, MODE, F16, D, false, TEAMS>(p, bh, tile, lds, lds + 2 * TEAMS, gamma);
     }
 }
 
@@ -857,10 +992,34 @@ inline hipError_t launch_one(const AttnParams& p, int mode, hipStream_t stream) 
     return hipGetLastError();
 }
 
+// Workgroups of several teams (p.teams).
+template <int NWAVES, int BN, int TEAMS, bool F16, int D>
+inline hipError_t launch_teams(const AttnParams& p, int mode, hipStream_t stream) {
+    const dim3 block(NWAVES * TEAMS * 64);
+    const size_t dyn = mode == kDense ? 0 : sizeof(int32_t) * ((size_t)p.geo.group_tokens + p.max_kv);
+    const int grouped_blocks = tile_blocks<false>(p), dense_blocks = tile_blocks<true>(p);
+    if (mode == kDense) {
+        hipLaunchKernelGGL((attn_mfma_teams_kernel<NWAVES, BN, kDense, F16, D, TEAMS>), dim3(dense_blocks), block, dyn, stream, p);
+    } else if (mode == kGrouped) {
+        hipLaunchKernelGGL((attn_mfma_teams_kernel<NWAVES, BN, kGrouped, F16, D, TEAMS>), dim3(grouped_blocks), block, dyn, stream, p);
+    } else {
+        if constexpr (BN == 64) {
+            if (mode != kJoint) return hipErrorInvalidValue;
+            const int blocks = xcd_padded_blocks(p.n_dense_tiles) + grouped_blocks;
+            hipLaunchKernelGGL((attn_mfma_teams_kernel<NWAVES, BN, kJoint, F16, D, TEAMS>), dim3(blocks), block, dyn, stream, p);
+        } else {
+            return hipErrorInvalidValue;
+        }
+    }
+    return hipGetLastError();
+}
+
 // p.q_tiles (and p.q_tiles_dense) were computed by the host for p.q_rows: 256 (head_dim 128 only), 128 or
 // 64 rows.  64-row workgroups take 32-key tiles unless the lists are long.
 template <bool F16, int D>
 inline hipError_t launch_by_tile(const AttnParams& p, int mode, hipStream_t stream) {
+    if (p.teams == 4) return launch_teams<2, 32, 4, F16, D>(p, mode, stream);   // 64 rows
+    if (p.teams == 2) return launch_teams<4, 64, 2, F16, D>(p, mode, stream);   // 128 rows
     if constexpr (D == 128)
         if (p.q_rows == 256) return launch_one<8, 64, F16, D>(p, mode, stream);
     if (p.q_rows >= 128) return launch_one<4, 64, F16, D>(p, mode, stream);

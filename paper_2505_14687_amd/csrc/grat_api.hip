@@ -186,6 +186,7 @@ static void fill_fastdivs(AttnParams& p) {
     p.fd_last2 = make_fastdiv((uint32_t)(geo.T[2] - (geo.G[2] - 1) * geo.g[2]));
     p.pad_tokens = pad_tokens(geo.group_tokens);
     p.fd_pad_tokens = make_fastdiv((uint32_t)p.pad_tokens);
+    p.fd_group_tiles = make_fastdiv((uint32_t)(geo.group_tokens / (p.teams == 4 ? 32 : 64)));
 }
 
 // Query rows per workgroup of the fp32 path: 16 selects the kernel whose waves own 16 queries (all of them, or a share
@@ -230,6 +231,36 @@ static int dense_tile_rows(int head_dim, int64_t rows, int64_t problems) {
     const int64_t last = tiles128 % 512;
     const int64_t cost128 = tiles128 / 512 * 10 + (last == 0 ? 0 : last <= 256 ? 7 : 10), cost256 = (tiles256 + 255) / 256 * 10;
     return cost128 * 106 < cost256 * 100 ? 128 : 256;
+}
+
+// Teams of waves that share the keys of a 16-bit workgroup: 4 of two waves (64 rows), 2 of four (128 rows), or 1.  A
+// launch that cannot give every compute unit a workgroup waits for one workgroup's walk, and that for the memory latency
+// of each of its steps (a lone 128-row workgroup takes 1 us for 64 keys, of which its products are 0.45).
+// `tiles64` / `tiles128` = workgroups of the launch with that many rows (0: not possible), `keys` = an upper bound of a
+// list's keys, `tables` = LDS for them.  us, 1 / 2 / 4 teams, head_dim 128 | 64:
+//   64x64 tokens in 16x16 groups, 3x3 lists, 1 head 36 / 31 / 24 | 25 / 22 / 16, 4 heads 38 / 33 / 26 | 26 / 22 / 17, 8 heads
+//   (256 tiles of 128 rows) 41 / 38 / 46 | 27 / 24 / 30; 32x32 tokens in 8x8 groups 13.5 / - / 11 | 10.5 / - / 8;
+//   own group only (256 keys) 8.0 / 9.3 / 8.7 | 6.5 / 7.2 / 6.6; video 8x32x48, 2 heads 53 / 46 / 55 | 38 / 32 / 37;
+//   sequences x tokens: 16 x 512 11 / 12 / 14 | 8.6 / 8.5 / 7.0, 8 x 1 024 19 / 19 / 17 | 14 / 12 / 9, 16 x 1 024 20 / 20 / 20 |
+//   15 / 13 / 10, 24 x 1 200 24 / 25 / 37 | 19 / 16 / 21, 14 x 1 500 27 / 25 / 39 | 22 / 18 / 24, 8 x 2 048 34 / 32 / 28 |
+//   25 / 22 / 16, 1 x 16 384 224 / 190 / 149 | 167 / 130 / 88, 1 x 32 768 514 / 482 / 567 | 341 / 292 / 333.
+static int key_teams(int head_dim, int64_t tiles64, int64_t tiles128, int64_t keys, int64_t tables, bool dense) {
+    if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
+    // (the four-team walk over a sequence spills at head_dim 128: more keys have to make up for it)
+    const int64_t enough4 = head_dim == 64 ? 384 : dense ? std::max<int64_t>(640, 8 * tiles64) : 512;
+    if (tiles64 > 0 && tiles64 <= 256 && keys >= enough4) return 4;
+    if (tiles128 > 0 && tiles128 <= 256 && keys >= (head_dim == 64 ? 1024 : 1408)) return 2;
+    return 1;
+}
+// Joint sequences: a prompt tile walks the whole sequence, which such a launch waits for where the rest of it is done
+// sooner.  `rest` = steps of 128 rows x 64 keys of the launch, for each of 512 places; 1 / 2 teams, us, head_dim 128 | 64 with
+// (walk / rest): 128x128 tokens, criss-cross, 100 prompt tokens 2 / 8 / 12 / 24 heads (8.1 / 2.0 / 1.3 / 0.7) 252 / 199,
+// 356 / 310, 419 / 445, 771 / 868 | 183 / 131, 216 / 202, 257 / 288, 456 / 545; 64x64 tokens, 3x3 lists, 256 prompt tokens, 12 / 24
+// heads (2.1 / 1.0) 79 / 64, 113 / 125 | 50 / 43, 70 / 81; 128x128 tokens, 3x3, 512 prompt tokens, 8 heads (2.5) 352 / 246 | 198 / 144.
+static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t group_tiles, int64_t list, int64_t tables) {
+    if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
+    const int64_t rest = prompt_tiles * walk + group_tiles * list;
+    return walk * 512 * 10 >= rest * 17 ? 2 : 1;
 }
 
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
@@ -280,6 +311,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     p.n_tokens = (int32_t)seq_len;
 
     const int n_g = geo.group_tokens;
+    p.teams = 1;
     int bm;   // query rows per workgroup
     const int64_t f32_keys = (int64_t)max_kv * pad_tokens(n_g);   // at most, of a list
     if (is16(dtype)) {
@@ -295,6 +327,15 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
         // workgroups, two per compute unit, so that one's prologue and epilogue lie under the other's
         // walk (measured: +5 % at 64x64 tokens, nothing either way from 128x128 tokens on).
         if (bm == 256 && (int64_t)batch * heads * geo.num_groups < 2 * 256) bm = 128;
+        if (!ragged) {
+            const int64_t bh = (int64_t)batch * heads, tables = ((int64_t)n_g + max_kv) * (int64_t)sizeof(int32_t);
+            const int64_t tiles64 = bh * geo.num_groups * (n_g / 64), tiles128 = n_g % 128 ? 0 : tiles64 / 2;
+            if (n_global == 0) p.teams = key_teams(head_dim, tiles64, tiles128, (int64_t)max_kv * n_g, tables, false);
+            else if (tiles128 > 0) p.teams = joint_teams(head_dim, bh * ((n_global + 127) / 128), (seq_len + 63) / 64, tiles128,
+                                                         (int64_t)max_kv * (n_g / 64) + (n_global + 63) / 64, tables);
+            if (p.teams == 4) bm = 64;
+            else if (p.teams == 2) bm = 128;
+        }
     } else {
         bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, f32_keys, false);
     }
@@ -401,8 +442,12 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     p.batch = batch; p.heads = heads;
     p.scale_log2 = scale * 1.4426950408889634f;
     p.n_tokens = (int32_t)n_tokens;
-    const int bm = is16(dtype) ? dense_tile_rows(head_dim, n_tokens, (int64_t)batch * heads)
-                               : f32_tile_rows(n_tokens, (int64_t)batch * heads, n_tokens, true);
+    const int64_t bh = (int64_t)batch * heads;
+    p.teams = is16(dtype) ? key_teams(head_dim, bh * ((n_tokens + 63) / 64), bh * ((n_tokens + 127) / 128), n_tokens, 0, true) : 1;
+    const int bm = p.teams == 4     ? 64
+                   : p.teams == 2   ? 128
+                   : is16(dtype)    ? dense_tile_rows(head_dim, n_tokens, bh)
+                                    : f32_tile_rows(n_tokens, bh, n_tokens, true);
     p.q_rows = bm;
     p.q_tiles = (int32_t)((n_tokens + bm - 1) / bm);
     p.q_tiles_dense = p.q_tiles;

@@ -64,6 +64,8 @@ struct AttnParams {
     // host only: query rows per workgroup.  (Behind everything the kernels load: among the tile counts it cost the
     // 8-wave joint kernel 23 more spilled scalar registers and 0.7 % of its time.)
     int32_t q_rows;
+    int32_t teams;                    // host only: teams of a workgroup of the MFMA kernel (1, 2 or 4)
+    FastDiv fd_group_tiles;           // workgroups of several teams: KV tiles of a listed group
 };
 
 // What a workgroup of the MFMA attention kernel can be (its MODE template argument).

@@ -244,9 +244,12 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
             return pack_coord(min(geo.g[0], geo.T[0] - p0 * geo.g[0]) - 1, min(geo.g[1], geo.T[1] - p1 * geo.g[1]) - 1,
                               min(geo.g[2], geo.T[2] - p2 * geo.g[2]) - 1);
         };
-        // The queries are asked for first of all, with their row offset worked out in arithmetic
-        // rather than read from the table below: they come from HBM (nobody has touched them
-        // before) and everything up to the first barrier then happens in the shadow of that fetch.
+        // The list's count and entries are asked for first (each thread one entry, without regard to the count: what
+        // lies behind it is padding and not used), then the queries, with their row offset worked out in arithmetic
+        // rather than read from the table below: they come from HBM (nobody has touched them before), loads return in
+        // order, and the tables, the barrier and the first K tile's request do not wait for them that way.
+        const int listed = p.kv_count[gamma], first_entry = p.kv_index[(int64_t)gamma * p.max_kv + min(tid, p.max_kv - 1)];
+        asm volatile("" ::: "memory");   // (... in this order)
         {
             int gp0, gp1, gp2;
             const int q_origin = group_origin((uint32_t)gamma, gp0, gp1, gp2);
@@ -273,14 +276,18 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
         }
         // (a caller-made list is taken as it is, but its count and entries are forced into range: a
         // bad list then gives wrong numbers, never an access outside the tables or the tensors)
-        const int cnt = min(max(p.kv_count[gamma], 0), p.max_kv);
+        const int cnt = min(max(__builtin_amdgcn_readfirstlane(listed), 0), p.max_kv);
         for (int i = tid; i < cnt; i += NT) {
-            const int gid = min(max(p.kv_index[(int64_t)gamma * p.max_kv + i], 0), geo.num_groups - 1);
+            const int entry = i == tid ? first_entry : p.kv_index[(int64_t)gamma * p.max_kv + i];
+            const int gid = min(max(entry, 0), geo.num_groups - 1);
             int p0, p1, p2;
             s_origin[i] = grid_base + (uint32_t)group_origin((uint32_t)gid, p0, p1, p2);
             if (MODE == kRagged) s_limit[i] = box_limit(gid);
         }
-        __syncthreads();
+        // the tables stand (a barrier that waits for LDS only: __syncthreads() would wait for the queries)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         tiles_per_group = n_g / kBN;
         if (MODE == kJoint) {
             n_lead = (p.n_global + kBN - 1) / kBN;

@@ -52,6 +52,16 @@ def kernel_name(w, n_g, n_glob, pattern, radius):
     return "grat::attn_mfma_kernel<%d, %d, %d, %s, %d>" % (waves, keys, mode, "true" if w.dtype == "f16" else "false", w.head_dim)
 
 
+def launched_kernel(w, n_g, n_glob, pattern, radius):
+    """kernel_name, but for launches of little more than one round of 256-row workgroups (mixed_whole in grat_api.hip)."""
+    import numpy as np
+    groups = int(np.prod([-(-t // g) for t, g in zip(w.grid, w.group)]))
+    ragged = any(t % g for t, g in zip(w.grid, w.group))
+    if w.head_dim == 128 and n_g == 256 and groups <= 64 and not n_glob and not ragged and 256 < w.batch * w.heads * groups <= 384:
+        return "grat::attn_mfma_mixed_kernel<%s>" % ("true" if w.dtype == "f16" else "false")
+    return kernel_name(w, n_g, n_glob, pattern, radius)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -329,7 +339,7 @@ def main():
                                        f"profiles/attn_mfma_{args.workload}_{args.pattern}.md: stored figure of a separate "
                                        "rocprofv3 --pmc run of this command, not measured in this run",
                      # template arguments: waves per workgroup, keys per LDS tile, mode (0 grouped, 2 joint), half?, head_dim
-                     "kernel": kernel_name(w, n_g, n_glob, pattern, radius),
+                     "kernel": launched_kernel(w, n_g, n_glob, pattern, radius),
                      # the same matrix instruction in a register-resident loop on this machine (operands
                      # with full significands spread like N(0,1); then all ones), and `achieved` as a
                      # fraction of the former

@@ -974,6 +974,20 @@ __global__ __launch_bounds__(NWAVES * TEAMS * 64, 2) void attn_mfma_teams_kernel
     }
 }
 
+// Launches of little more than one round: p.n_whole tiles of 256 rows, one for every compute unit, the others as two 128-row
+// workgroups of two teams each, all longest list first (64x64 tokens in 16x16 groups, 3x3 lists, 24 heads: 87.5 us as 128-row
+// workgroups, 85.1; 64x80 tokens, 16 heads 80.5, 70.4).
+template <bool F16>
+__global__ __launch_bounds__(512, 2) void attn_mfma_mixed_kernel(AttnParams p) {
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[8][64 * 128 * 2];
+    const int b = (int)blockIdx.x;
+    const bool whole = b < p.n_whole;
+    int bh, tile, gamma;
+    if (!longest_first_tile(p, whole ? b : p.n_whole + (b - p.n_whole) / 2, bh, tile, gamma)) return;
+    if (whole) attn_tile<8, 64, kGrouped, F16, 128, false, 1>(p, bh, tile, lds, lds + 2, gamma);
+    else attn_tile<4, 64, kGrouped, F16, 128, false, 2>(p, bh, 2 * tile + ((b - p.n_whole) & 1), lds, lds + 4, gamma);
+}
+
 template <int NWAVES, int BN, bool F16, int D>
 inline hipError_t launch_one(const AttnParams& p, int mode, hipStream_t stream) {
     const dim3 block(NWAVES * 64);
@@ -1027,6 +1041,13 @@ template <bool F16, int D>
 inline hipError_t launch_by_tile(const AttnParams& p, int mode, hipStream_t stream) {
     if (p.teams == 4) return launch_teams<2, 32, 4, F16, D>(p, mode, stream);   // 64 rows
     if (p.teams == 2) return launch_teams<4, 64, 2, F16, D>(p, mode, stream);   // 128 rows
+    if constexpr (D == 128)
+        if (p.n_whole > 0) {
+            const size_t dyn = sizeof(int32_t) * ((size_t)p.geo.group_tokens + p.max_kv);
+            const int tiles = p.batch * p.heads * p.geo.num_groups * p.q_tiles;
+            hipLaunchKernelGGL((attn_mfma_mixed_kernel<F16>), dim3(2 * tiles - p.n_whole), dim3(512), dyn, stream, p);
+            return hipGetLastError();
+        }
     if constexpr (D == 128)
         if (p.q_rows == 256) return launch_one<8, 64, F16, D>(p, mode, stream);
     if (p.q_rows >= 128) return launch_one<4, 64, F16, D>(p, mode, stream);

@@ -263,6 +263,19 @@ static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t
     return walk * 512 * 10 >= rest * 17 ? 2 : 1;
 }
 
+// Whole tiles of a mixed launch (attn_mfma_mixed_kernel), 0: not one.  A compute unit each for the first 256 tiles of
+// 256 rows; what is left, if it is at most 128 tiles, keeps the others busy as twice as many workgroups of half the walk,
+// where 128-row workgroups, two a compute unit, would take another 0.7 of a round.  us as those | mixed, 256-token
+// groups, head_dim 128: 64x64 tokens, 3x3 lists, 17 / 18 / 20 / 22 / 23 / 24 heads 64.8 / 66.3 / 74.4 / 86.5 / 94.3 / 87.5 | 64.4 / 67.3 /
+// 70.0 / 84.7 / 87.5 / 85.1, criss-cross, 17 / 20 / 24 heads 86.1 / 85.9 / 90.6 | 81.5 / 83.8 / 89.8; video 8x32x48, 6 / 7 heads 134.8 /
+// 167.3 | 120.8 / 155.1; 128x96 tokens, 6 heads 86.5 | 76.4; 64x80 tokens, 16 heads 80.5 | 70.4.  After two full rounds of
+// 256-row workgroups there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads 177.4 | 184.1), and so do
+// 1 024-token groups (96x96 tokens, 8 heads 211 | 221).
+static int32_t mixed_whole(int64_t tiles256, int64_t tables) {
+    if (128 * 1024 + 4096 + tables > 160 * 1024) return 0;
+    return tiles256 > 256 && tiles256 <= 256 + 128 ? 256 : 0;
+}
+
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
 
 // LDS the MFMA kernel needs beside its four 16-KiB tiles: the row-offset table of a group and the
@@ -335,6 +348,9 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
                                                          (int64_t)max_kv * (n_g / 64) + (n_global + 63) / 64, tables);
             if (p.teams == 4) bm = 64;
             else if (p.teams == 2) bm = 128;
+            if (p.teams == 1 && n_global == 0 && head_dim == 128 && n_g == 256 && geo.num_groups <= 64)
+                p.n_whole = mixed_whole(tiles64 / 4, tables);
+            if (p.n_whole > 0) bm = 256;
         }
     } else {
         bm = f32_tile_rows(n_g, (int64_t)batch * heads * geo.num_groups, f32_keys, false);

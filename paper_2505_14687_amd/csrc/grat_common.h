@@ -65,6 +65,7 @@ struct AttnParams {
     // 8-wave joint kernel 23 more spilled scalar registers and 0.7 % of its time.)
     int32_t q_rows;
     int32_t teams;                    // host only: teams of a workgroup of the MFMA kernel (1, 2 or 4)
+    int32_t n_whole;                  // mixed launches (0: not one): 256-row tiles that are not split
     FastDiv fd_group_tiles;           // workgroups of several teams: KV tiles of a listed group
 };
 

@@ -72,6 +72,25 @@ def test_groups(grid, group, pattern, heads, prompt, d):
     _check(out, q, k, v, mask, dtype)
 
 
+# 257 to 384 tiles of 256 rows: 256 whole ones, the others split between workgroups of two teams
+@pytest.mark.parametrize("grid,group,pattern,heads", [((64, 64), (16, 16), "block", 17), ((64, 64), (16, 16), "cross", 24),
+                                                      ((16, 48), (16, 16), "block", 86), ((8, 32, 48), (4, 8, 8), "block", 6)])
+def test_mixed_launches(grid, group, pattern, heads):
+    n, radius = math.prod(grid), (1,) * len(grid)
+    dtype = torch.float16 if heads % 2 else torch.bfloat16
+    q, k, v = _inputs(heads, n, 128, dtype, 9200 + heads)
+    count, index = grat.grat_build_block_lists(grid, group, pattern, radius)
+    out = torch.full_like(q, float("nan"))
+    grat.grat_attention_fwd(q, k, v, 1.0 / math.sqrt(128), grid, group, count, index, out=out)
+    assert bool(torch.isfinite(out).all())
+    rows = torch.arange(heads % 7, n, max(1, n // 1000), device="cuda")
+    mask = _group_mask(grid, group, pattern, radius)[rows]
+    for h in range(heads):
+        s = (q[0, h, rows].double() @ k[0, h].double().T.contiguous() / math.sqrt(128)).masked_fill(~mask, -math.inf)
+        want = torch.softmax(s, -1) @ v[0, h].double()
+        assert float(((out[0, h, rows].double() - want).norm(dim=-1) / want.norm(dim=-1)).max()) <= 2 * BAR[dtype]
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_short_lists_among_long_ones(d):
     """A list of one group has two 32-key tiles: two of four teams have none.  And O with a layout of its own (packed)."""

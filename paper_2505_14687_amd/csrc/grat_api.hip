@@ -241,12 +241,12 @@ static int dense_tile_rows(int head_dim, int64_t rows, int64_t problems) {
 //   64x64 tokens in 16x16 groups, 3x3 lists, 1 head 36 / 31 / 24 | 25 / 22 / 16, 4 heads 38 / 33 / 26 | 26 / 22 / 17, 8 heads
 //   (256 tiles of 128 rows) 41 / 38 / 46 | 27 / 24 / 30; 32x32 tokens in 8x8 groups 13.5 / - / 11 | 10.5 / - / 8;
 //   own group only (256 keys) 8.0 / 9.3 / 8.7 | 6.5 / 7.2 / 6.6; video 8x32x48, 2 heads 53 / 46 / 55 | 38 / 32 / 37;
-//   sequences x tokens: 16 x 512 11 / 12 / 14 | 8.6 / 8.5 / 7.0, 8 x 1 024 19 / 19 / 17 | 14 / 12 / 9, 16 x 1 024 20 / 20 / 20 |
+//   sequences x tokens: 16 x 512 11 / 12 / 14 | 8.6 / 8.5 / 7.0, 8 x 1 024 19 / 19 / 14 | 14 / 12 / 9, 16 x 1 024 20 / 20 / 20 |
 //   15 / 13 / 10, 24 x 1 200 24 / 25 / 37 | 19 / 16 / 21, 14 x 1 500 27 / 25 / 39 | 22 / 18 / 24, 8 x 2 048 34 / 32 / 28 |
 //   25 / 22 / 16, 1 x 16 384 224 / 190 / 149 | 167 / 130 / 88, 1 x 32 768 514 / 482 / 567 | 341 / 292 / 333.
 static int key_teams(int head_dim, int64_t tiles64, int64_t tiles128, int64_t keys, int64_t tables, bool dense) {
     if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
-    // (the four-team walk over a sequence spills at head_dim 128: more keys have to make up for it)
+    // (sequences at head_dim 128: the more tiles, the less is left to gain)
     const int64_t enough4 = head_dim == 64 ? 384 : dense ? std::max<int64_t>(640, 8 * tiles64) : 512;
     if (tiles64 > 0 && tiles64 <= 256 && keys >= enough4) return 4;
     if (tiles128 > 0 && tiles128 <= 256 && keys >= (head_dim == 64 ? 1024 : 1408)) return 2;

@@ -108,12 +108,15 @@ def test_short_lists_among_long_ones(d):
     _check(out.transpose(1, 2), q, k, v, mask, torch.bfloat16)
 
 
-@pytest.mark.parametrize("heads,n", [(1, 1024), (17, 1536)])   # four teams, two teams
-def test_scores_of_minus_infinity(heads, n):
-    """Keys 32 to 127 score -infinity: whole tiles, among them the first of some teams (not the first of the walk)."""
-    q, k, v = _inputs(heads, n, 128, torch.bfloat16, 31)
+# four teams, two teams (both walk from the last tile), undivided
+@pytest.mark.parametrize("heads,n,d", [(1, 1024, 128), (17, 1536, 128), (1, 1000, 64), (17, 1100, 64), (24, 2100, 64)])
+@pytest.mark.parametrize("behind", [False, True])
+def test_scores_of_minus_infinity(heads, n, d, behind):
+    """Keys 32 to 127, or the last 150, score -infinity: whole tiles, among them the first of some teams, or the first that is
+    walked (not the first of the sequence)."""
+    q, k, v = _inputs(heads, n, d, torch.bfloat16, 31)
     q[..., 0] = q[..., 0].abs() + 0.1
-    k[:, :, 32:128, 0] = -math.inf
+    k[:, :, slice(n - 150, n) if behind else slice(32, 128), 0] = -math.inf
     out = torch.full_like(q, float("nan"))
-    grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(128), out=out)
+    grat.grat_dense_attention_fwd(q, k, v, 1.0 / math.sqrt(d), out=out)
     _check(out, q, k.clamp(min=-1e6), v, None, torch.bfloat16)

@@ -563,9 +563,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_f32_kernel(AttnParams p) {
 // from the listed groups laid end to end, each padded to a multiple of 16 tokens - groups of fewer than
 // 16 tokens are not padded but packed, several to a block.  Where the tiles alone fill the chip a workgroup is one
 // wave (NW = 1), which has all the keys and nothing to merge.  32x32 tokens in 8x8 groups, 2 heads x 64, 3x3 lists,
-// with the list building: 390 us with one query per lane (32 waves in all), 15.5 us here (the matrix instructions of the
-// 128 workgroups take 4 us of the 12 of this kernel; entries read ahead of the count and no ranking of lists took it
-// from 13.6, launches of a graph).
+// with the list building: 390 us with one query per lane (32 waves in all), 15.3 us here (this kernel alone 12.9 back to back, of which the matrix instructions of its 128
+// workgroups are 4; with the entries read behind the count and the lists ranked 14.3).
 // Two workgroups a compute unit where LDS has room for them (head_dim 64: 33 of 160 KiB, four waves a SIMD, 128
 // registers; the compiler wants 129 and 133 and would leave one: 128x128 tokens in 4x4 groups, 8 heads, eight waves, 182
 // us against 122).

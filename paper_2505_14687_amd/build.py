@@ -8,6 +8,7 @@ import subprocess
 import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
+from typing import Optional
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
@@ -41,16 +42,16 @@ def _run(cmd, verbose):
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + res.stdout + res.stderr)
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n" + " ".join(cmd) + "\n" + res.stdout + res.stderr)
     return res.stderr
 
 
-def _binding_command() -> list:
-    """Host code only, against the headers and libraries of the torch it is going to run in."""
+def _binding_command() -> Optional[list]:
+    """Host code only, against the headers and libraries of the torch it is going to run in.  None: no host compiler."""
     import torch
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
-        raise RuntimeError("no host C++ compiler: the binding needs g++")
+        return None
     inc = os.path.join(os.path.dirname(torch.__file__), "include")
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc_path())))
     return [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
@@ -73,9 +74,15 @@ def build_library(verbose: bool = False, extra_flags=(), jobs: int = 8) -> str:
             return _run([hipcc, *HIPCC_FLAGS, *extra_flags, *inc, "-c", os.path.join(CSRC, src), "-o", obj], verbose)
 
         with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES) + 1))) as ex:
-            binding = ex.submit(_run, _binding_command(), verbose)
+            binding_cmd = _binding_command()
+            if os.path.exists(BINDING_PATH):
+                os.remove(BINDING_PATH)   # (never one of an earlier torch beside a new library)
+            if binding_cmd is None:
+                print("no host C++ compiler (g++): calls will be marshalled in Python", flush=True)
+            binding = ex.submit(_run, binding_cmd, verbose) if binding_cmd else None
             warnings = list(ex.map(compile_one, zip(SOURCES, objs)))
-            binding.result()
+            if binding:
+                binding.result()
         _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH], verbose)
     if verbose:
         for w in warnings:

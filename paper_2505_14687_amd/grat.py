@@ -5,12 +5,15 @@ runs inside the library's kernels.  There is no fallback: if libgrat.so has not 
 (python -m paper_2505_14687_amd.build) every call raises.
 
 An ordinary call is marshalled by csrc/binding.cpp (_binding.so).  What that does not take (it answers None) goes through
-ctypes here: arguments of unusual types, tensor subclasses, and everything that is refused.
+ctypes here: arguments of unusual types, tensor subclasses, and everything that is refused.  _binding.so is bound to the
+torch it was built against; where it cannot be loaded every call takes the ctypes way, to the same kernels.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 from typing import Optional, Sequence, Tuple
 
 import torch
@@ -27,7 +30,12 @@ EXPORTS = ("grat_block_list_shape", "grat_build_block_lists", "grat_validate_blo
 _i32, _i64, _f32, _vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_void_p
 _pi32 = ctypes.POINTER(ctypes.c_int32)
 _lib = None
-_native = None   # csrc/binding.cpp, entered by way of _lib's entry points
+_native = None   # csrc/binding.cpp, entered by way of _lib's entry points; not None once _lib is not
+
+
+class _NoNative:
+    """In the place of _binding where that is not there: it takes no call."""
+    attention = packed = dense = block_lists = staticmethod(lambda *args: None)
 
 
 class GratError(RuntimeError):
@@ -41,10 +49,9 @@ def lib() -> ctypes.CDLL:
     """Load libgrat.so (once).  Raises if it is not there: there is no other implementation."""
     global _lib, _native
     if _lib is None:
-        for path in (LIB_PATH, BINDING_PATH):
-            if not os.path.exists(path):
-                raise RuntimeError(f"{path} is missing: build it with "
-                                   "`python -m paper_2505_14687_amd.build` (needs hipcc)")
+        if not os.path.exists(LIB_PATH):
+            raise RuntimeError(f"{LIB_PATH} is missing: build it with "
+                               "`python -m paper_2505_14687_amd.build` (needs hipcc)")
         L = ctypes.CDLL(LIB_PATH)
         L.grat_block_list_shape.argtypes = [_i32, _pi32, _pi32, _i32, _pi32, _pi32, _pi32]
         L.grat_block_list_shape.restype = _i32
@@ -69,12 +76,24 @@ def lib() -> ctypes.CDLL:
         L.grat_status_string.restype = ctypes.c_char_p
         L.grat_probe_mfma.argtypes = [_i32, _i32, _vp, _i32, _i32, _vp]
         L.grat_probe_mfma.restype = _i32
-        from . import _binding
-        _binding.set_library(*(ctypes.cast(f, _vp).value for f in
-                               (L.grat_block_list_shape, L.grat_build_block_lists, L.grat_attention_fwd,
-                                L.grat_attention_global_fwd, L.grat_attention_packed_fwd, L.grat_dense_attention_fwd)))
-        _lib, _native = L, _binding
+        _native = _load_native(L)   # (ahead of _lib: another thread that finds _lib set uses both)
+        _lib = L
     return _lib
+
+
+def _load_native(L: ctypes.CDLL):
+    try:
+        if not os.path.exists(BINDING_PATH):
+            raise ImportError(f"{BINDING_PATH} is missing")
+        native = importlib.import_module(__package__ + "._binding")
+    except ImportError as e:
+        warnings.warn(f"_binding.so cannot be loaded, calls are marshalled in Python (about 10 us more each): {e}; build it with "
+                      "`python -m paper_2505_14687_amd.build`", RuntimeWarning, stacklevel=3)
+        return _NoNative
+    native.set_library(*(ctypes.cast(f, _vp).value for f in
+                         (L.grat_block_list_shape, L.grat_build_block_lists, L.grat_attention_fwd,
+                          L.grat_attention_global_fwd, L.grat_attention_packed_fwd, L.grat_dense_attention_fwd)))
+    return native
 
 
 def _result(r, where: str):

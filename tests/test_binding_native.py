@@ -1,10 +1,14 @@
 """The native part of the binding takes ordinary calls only; all others go the long way and come to the same."""
+import sys
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2505_14687_amd as grat
+from paper_2505_14687_amd import build
 from paper_2505_14687_amd import grat as binding
+from paper_2505_14687_amd.build import BINDING_PATH
 
 GRID, GROUP = (32, 32), (8, 8)
 
@@ -74,3 +78,50 @@ def test_both_ways_give_the_same_and_refuse_the_same():
     assert e.value.status == 2
     with pytest.raises(grat.GratError):
         grat.grat_build_block_lists(GRID, GROUP, "block", (1, 1), max_kv=3)
+
+
+@pytest.fixture(params=["file missing", "cannot be loaded"])
+def without_native(request, monkeypatch):
+    """libgrat.so there, _binding.so not built (no host compiler) or built for another torch."""
+    grat.lib()
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+    if request.param == "file missing":
+        monkeypatch.setattr(binding, "BINDING_PATH", binding.BINDING_PATH + ".not-there")
+    else:
+        monkeypatch.setitem(sys.modules, "paper_2505_14687_amd._binding", None)
+
+
+def test_without_the_native_part_calls_go_the_long_way(without_native):
+    with pytest.warns(RuntimeWarning, match="_binding"):
+        assert grat.grat_block_list_shape(GRID, GROUP, "block", (1, 1)) == (16, 9)
+    x = torch.zeros(1, 2, 1024, 64)
+    cnt, idx = torch.zeros(16, dtype=torch.int32), torch.zeros(16, 9, dtype=torch.int32)
+    for call in (lambda: grat.grat_attention_fwd(x, x, x, 0.1, GRID, GROUP, cnt, idx),
+                 lambda: grat.grat_attention_global_fwd(x, x, x, 0.1, 0, True, GRID, GROUP, cnt, idx),
+                 lambda: grat.grat_dense_attention_fwd(x, x, x, 0.1),
+                 lambda: grat.grat_attention_packed_fwd(torch.zeros(1, 1024, 3, 2, 64), 0.1, GRID, GROUP, cnt, idx)):
+        with pytest.raises(ValueError, match="device memory"):
+            call()
+
+
+@pytest.mark.gpu
+def test_without_the_native_part_results_are_the_same(without_native):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    q, k, v = (torch.randn(1, 2, 1024, 64, generator=g, device="cuda") for _ in range(3))
+    with pytest.warns(RuntimeWarning, match="_binding"):
+        cnt, idx = grat.grat_build_block_lists(GRID, GROUP, "block", (1, 1))
+    got = grat.grat_attention_fwd(q, k, v, 0.125, GRID, GROUP, cnt, idx), grat.grat_dense_attention_fwd(q, k, v, 0.125)
+    binding._lib = None   # (the fixture puts everything back)
+    sys.modules.pop("paper_2505_14687_amd._binding", None)
+    binding.BINDING_PATH = BINDING_PATH
+    c2, i2 = grat.grat_build_block_lists(GRID, GROUP, "block", (1, 1))
+    assert isinstance(binding._native.dense(q, k, v, 0.125, None, None), torch.Tensor)
+    want = grat.grat_attention_fwd(q, k, v, 0.125, GRID, GROUP, cnt, idx), grat.grat_dense_attention_fwd(q, k, v, 0.125)
+    assert torch.equal(cnt, c2) and torch.equal(idx, i2) and all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_a_failed_build_step_names_its_compiler():
+    with pytest.raises(RuntimeError, match="false failed"):
+        build._run(["/bin/false"], False)

@@ -18,14 +18,18 @@ if ROOT not in sys.path:
 BF16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix peak
 
 
-def measured_traffic(workload, pattern):
-    """HBM bytes per attention launch from the committed rocprofv3 counter summary, if there is one
-    for this workload (profiles/attn_mfma_<workload>_<pattern>.md, line 'traffic_bytes_per_launch: N')."""
+def measured_traffic(workload, pattern, kernel):
+    """HBM bytes per attention launch from the committed rocprofv3 counter summary, if there is one for this workload
+    and the kernel that it now runs (profiles/attn_mfma_<workload>_<pattern>.md: the kernel's name opens the title, line
+    'traffic_bytes_per_launch: N')."""
     path = os.path.join(ROOT, "profiles", f"attn_mfma_{workload}_{pattern}.md")
     try:
-        for line in open(path):
-            if line.startswith("traffic_bytes_per_launch:"):
-                return float(line.split(":")[1])
+        with open(path) as f:
+            if not f.readline().startswith(f"# {kernel} "):
+                return None
+            for line in f:
+                if line.startswith("traffic_bytes_per_launch:"):
+                    return float(line.split(":")[1])
     except OSError:
         pass
     return None
@@ -36,30 +40,13 @@ def log(*a):
 
 
 def kernel_name(w, n_g, n_glob, pattern, radius):
-    """The instantiation the library launches for this workload (its rules, restated): template arguments
-    = waves per workgroup, keys per LDS tile, mode (0 grouped, 2 joint, 3 grid the group does not divide),
-    half?, head_dim."""
-    import numpy as np
+    """The kernel the library launches for this workload, as the library says (probe.launched_kernel)."""
+    import torch
     import paper_2505_14687_amd as grat
-    groups = int(np.prod([-(-t // g) for t, g in zip(w.grid, w.group)]))
-    waves = 8 if n_g % 256 == 0 and w.head_dim == 128 else (4 if n_g % 128 == 0 else 2)
-    if waves == 8 and w.batch * w.heads * groups < 512:
-        waves = 4
-    ragged = any(t % g for t, g in zip(w.grid, w.group))
-    mode = 2 if n_glob else (3 if ragged else 0)
+    from paper_2505_14687_amd.probe import launched_kernel
+    dtype = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[w.dtype]
     max_kv = grat.grat_block_list_shape(w.grid, w.group, pattern, radius)[1]
-    keys = 32 if waves == 2 and mode != 2 and max_kv * n_g <= 4096 else 64
-    return "grat::attn_mfma_kernel<%d, %d, %d, %s, %d>" % (waves, keys, mode, "true" if w.dtype == "f16" else "false", w.head_dim)
-
-
-def launched_kernel(w, n_g, n_glob, pattern, radius):
-    """kernel_name, but for launches of little more than one round of 256-row workgroups (mixed_whole in grat_api.hip)."""
-    import numpy as np
-    groups = int(np.prod([-(-t // g) for t, g in zip(w.grid, w.group)]))
-    ragged = any(t % g for t, g in zip(w.grid, w.group))
-    if w.head_dim == 128 and n_g == 256 and groups <= 64 and not n_glob and not ragged and 256 < w.batch * w.heads * groups <= 384:
-        return "grat::attn_mfma_mixed_kernel<%s>" % ("true" if w.dtype == "f16" else "false")
-    return kernel_name(w, n_g, n_glob, pattern, radius)
+    return launched_kernel(dtype, w.batch, w.heads, w.head_dim, w.grid, w.group, max_kv, n_glob)
 
 
 def main():
@@ -312,7 +299,8 @@ def main():
                "parity_rel_l2": float(np.linalg.norm(diff) / np.linalg.norm(want))}
         log(f"cpu oracle: {cpu}")
 
-    traffic = None if n_glob or args.constant_data else measured_traffic(args.workload, args.pattern)
+    kernel = kernel_name(w, n_g, n_glob, pattern, radius)
+    traffic = None if n_glob or args.constant_data else measured_traffic(args.workload, args.pattern, kernel)
     all_patterns = None
     if extra:
         fl = main_r["flops"] + sum(4.0 * w.head_dim * w.heads * w.batch * e["attended_pairs"] for e in extra.values())
@@ -338,8 +326,8 @@ def main():
                      "traffic_source": None if traffic is None else
                                        f"profiles/attn_mfma_{args.workload}_{args.pattern}.md: stored figure of a separate "
                                        "rocprofv3 --pmc run of this command, not measured in this run",
-                     # template arguments: waves per workgroup, keys per LDS tile, mode (0 grouped, 2 joint), half?, head_dim
-                     "kernel": launched_kernel(w, n_g, n_glob, pattern, radius),
+                     # template arguments: see paper_2505_14687_amd/probe.py
+                     "kernel": kernel,
                      # the same matrix instruction in a register-resident loop on this machine (operands
                      # with full significands spread like N(0,1); then all ones), and `achieved` as a
                      # fraction of the former

@@ -1,5 +1,6 @@
 /*
- * libgrat — measurement aid, not an operation of the method: a register-resident MFMA-only loop.
+ * libgrat — measurement aids, not operations of the method: a register-resident MFMA-only loop, and what an
+ * attention call would launch.
  *
  * The attention kernels are priced against the chip's published dense matrix rate.  What the same
  * matrix instruction sustains on a given machine with nothing else going on (no memory traffic,
@@ -48,6 +49,29 @@ extern "C" {
  */
 grat_status grat_probe_mfma(grat_dtype dtype, int32_t data, int64_t* d_sink, int32_t blocks,
                             int32_t iters, void* hip_stream);
+
+/* What an attention call launches (grat_probe_launch). */
+typedef struct {
+    int32_t mode;           /* tiles: 0 of groups, 1 of one sequence, 2 of groups and prompt rows, 3 of groups, some clipped */
+    int32_t rows;           /* query rows of a workgroup */
+    int32_t teams;          /* 16-bit types: teams of waves that share a workgroup's keys (1: undivided) */
+    int32_t tile_keys;      /* 16-bit types: keys of an LDS tile; fp32: 0 */
+    int32_t whole_tiles;    /* mixed launches: leading tiles that are not split, 0: not one */
+    int32_t key_waves;      /* fp32, 16-row workgroups: waves that share the keys; else 0 */
+    int32_t longest_first;  /* 1: grouped tiles go out by list length */
+    int32_t tiles;          /* query tiles (mixed launches: before the split) */
+    int32_t xcd_tiles;      /* tiles of the XCD that gets most */
+} grat_launch_info;
+
+/*
+ * Fills *info for the call with these sizes on contiguous [B, H, N, d] tensors; host only, launches nothing.
+ *   ndim 1 .. 3  grat_attention_fwd, or grat_attention_global_fwd with n_global > 0; max_kv = columns of kv_index
+ *   ndim 0       grat_dense_attention_fwd over n_global tokens (grid, group, max_kv not read)
+ * Errors: GRAT_ERR_NULL (info), and those of the call.
+ */
+grat_status grat_probe_launch(grat_dtype dtype, int32_t batch, int32_t heads, int32_t head_dim, int32_t n_global,
+                              int32_t ndim, const int32_t* grid, const int32_t* group, int32_t max_kv,
+                              grat_launch_info* info);
 
 #ifdef __cplusplus
 }

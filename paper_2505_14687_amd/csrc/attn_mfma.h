@@ -1059,7 +1059,7 @@ inline hipError_t launch_teams(const AttnParams& p, int mode, hipStream_t stream
 }
 
 // p.q_tiles (and p.q_tiles_dense) were computed by the host for p.q_rows: 256 (head_dim 128 only), 128 or
-// 64 rows.  64-row workgroups take 32-key tiles unless the lists are long.
+// 64 rows.
 template <bool F16, int D>
 inline hipError_t launch_by_tile(const AttnParams& p, int mode, hipStream_t stream) {
     if (p.teams == 4) return launch_teams<2, 32, 4, F16, D>(p, mode, stream);   // 64 rows
@@ -1074,10 +1074,7 @@ inline hipError_t launch_by_tile(const AttnParams& p, int mode, hipStream_t stre
     if constexpr (D == 128)
         if (p.q_rows == 256) return launch_one<8, 64, F16, D>(p, mode, stream);
     if (p.q_rows >= 128) return launch_one<4, 64, F16, D>(p, mode, stream);
-    // (measured at 512x512 tokens in 8x8 groups: lists of 9 / 25 / 49 groups gain 16-19 % from the small
-    // tiles, the criss-cross lists of 127 groups lose 5 %)
-    // (not for joint sequences: that variant of the 32-key schedule does not fit the register file)
-    if (mode != kJoint && (int64_t)p.max_kv * p.geo.group_tokens <= 64 * 64) return launch_one<2, 32, F16, D>(p, mode, stream);
+    if (mfma_tile_keys(p, mode) == 32) return launch_one<2, 32, F16, D>(p, mode, stream);
     return launch_one<2, 64, F16, D>(p, mode, stream);
 }
 

@@ -1,8 +1,10 @@
 // Host side of libgrat: argument validation and dispatch.  No allocation, no synchronisation.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
 #include "grat_common.h"
+#include "grat_probe.h"
 
 namespace grat {
 namespace {
@@ -285,15 +287,45 @@ static bool tables_fit_lds(const Geometry& geo, int32_t max_kv, bool ragged) {
     return 4 * 16384 + tables <= 160 * 1024;
 }
 
+// A checked call and everything that is decided about its launch.
+struct Plan {
+    AttnParams p{};
+    int mode = kGrouped;    // AttnMode
+    int key_waves = 0;      // fp32: f32_key_waves
+    int64_t xcd_tiles = 0;  // tiles of the XCD that gets most
+};
+
+static grat_status launch(const Plan& plan, grat_dtype dtype, int32_t head_dim, void* hip_stream) {
+    const hipError_t e = is16(dtype) ? launch_attn_bf16(plan.p, plan.mode, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
+                                     : launch_attn_f32(plan.p, plan.p.q_rows, plan.key_waves, head_dim, plan.mode == kDense,
+                                                       (hipStream_t)hip_stream);
+    return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
+}
+
+// Tiles of the XCD that gets most of a launch: workgroups go to the XCDs in turn, grouped ones either by rank
+// (consecutive) or as head_sync_tile deals them (an eighth of a head's tiles each, rounded up; which eighth rotates).
+static int64_t most_tiles_of_an_xcd(const AttnParams& p, int64_t heads, bool grouped, bool ranked) {
+    int64_t most = 0;
+    const int64_t tiles = grouped ? (int64_t)p.geo.num_groups * p.q_tiles : 0, per = (tiles + kNumXcd - 1) / kNumXcd;
+    for (int xcd = 0; xcd < kNumXcd; ++xcd) {
+        int64_t n = (p.n_dense_tiles + kNumXcd - 1 - xcd) / kNumXcd;
+        if (ranked) n += (heads * tiles + kNumXcd - 1 - xcd) / kNumXcd;
+        else n += heads / kNumXcd * tiles;
+        for (int64_t h = 0; !ranked && h < heads % kNumXcd; ++h) n += std::clamp<int64_t>(tiles - (xcd + h) % kNumXcd * per, 0, per);
+        most = std::max(most, n);
+    }
+    return most;
+}
+
 // Shared by grat_attention_fwd (n_global = 0), grat_attention_global_fwd and grat_attention_packed_fwd.
-static grat_status attention_fwd(const void* Q, const void* K, const void* V, void* O,
-                                 grat_dtype dtype, int32_t batch, int32_t heads, int32_t head_dim,
-                                 int64_t stride_b, int64_t stride_h, int64_t stride_n,
-                                 OutStrides os, float scale,
-                                 int32_t n_global, int32_t global_first, int32_t ndim,
-                                 const int32_t* grid, const int32_t* group,
-                                 const int32_t* d_kv_count, const int32_t* d_kv_index,
-                                 int32_t max_kv, void* hip_stream) {
+static grat_status plan_attention(const void* Q, const void* K, const void* V, void* O,
+                                  grat_dtype dtype, int32_t batch, int32_t heads, int32_t head_dim,
+                                  int64_t stride_b, int64_t stride_h, int64_t stride_n,
+                                  OutStrides os, float scale,
+                                  int32_t n_global, int32_t global_first, int32_t ndim,
+                                  const int32_t* grid, const int32_t* group,
+                                  const int32_t* d_kv_count, const int32_t* d_kv_index,
+                                  int32_t max_kv, Plan& plan) {
     if (!d_kv_count || !d_kv_index) return GRAT_ERR_NULL;
     Geometry geo;
     grat_status st = make_geometry(ndim, grid, group, &geo);
@@ -313,7 +345,7 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     if (max_kv > kMaxListLen) return GRAT_ERR_UNSUPPORTED;
     if (n_global > 0 && !is16(dtype)) return GRAT_ERR_UNSUPPORTED;
 
-    AttnParams p{};
+    AttnParams& p = plan.p;
     p.Q = Q; p.K = K; p.V = V; p.O = O;
     p.stride_b = stride_b; p.stride_h = stride_h; p.stride_n = (int32_t)stride_n;
     p.o_stride_b = os.b; p.o_stride_h = os.h; p.o_stride_n = (int32_t)os.n;
@@ -362,11 +394,11 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
     const int64_t total = (int64_t)batch * heads * geo.num_groups * p.q_tiles;
     if ((int64_t)batch * heads * ((int64_t)geo.num_groups * p.q_tiles + 8) >= kMaxElems - 8) return GRAT_ERR_UNSUPPORTED;
 
-    int mode = ragged ? kRagged : kGrouped;
+    plan.mode = ragged ? kRagged : kGrouped;
     // the clipped-box tests of the bf16 kernel pack box coordinates into 12 + 10 + 10 bits
     if (ragged && is16(dtype) && (geo.g[1] > 1024 || geo.g[2] > 1024)) return GRAT_ERR_UNSUPPORTED;
     if (n_global > 0) {   // joint sequence: prompt rows become dense tiles launched ahead of the rest
-        mode = kJoint;
+        plan.mode = kJoint;
         p.n_global = n_global;
         p.global_row0 = global_first ? 0 : (int32_t)geo.n_tokens;
         p.grid_row0 = global_first ? n_global : 0;
@@ -387,10 +419,23 @@ static grat_status attention_fwd(const void* Q, const void* K, const void* V, vo
                       (is16(dtype) && head_dim == 64 && n_g % 256 == 0 ? total / 2 : total) <= 16 * 256;
     p.fd_tiles_per_rank = make_fastdiv((uint32_t)(batch * heads * p.q_tiles));
     fill_fastdivs(p);
-    const hipError_t e = is16(dtype)
-                             ? launch_attn_bf16(p, mode, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
-                             : launch_attn_f32(p, bm, f32_key_waves(total, f32_keys), head_dim, false, (hipStream_t)hip_stream);
-    return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
+    plan.key_waves = f32_key_waves(total, f32_keys);
+    plan.xcd_tiles = most_tiles_of_an_xcd(p, (int64_t)batch * heads, true, p.longest_first);
+    return GRAT_OK;
+}
+
+static grat_status attention_fwd(const void* Q, const void* K, const void* V, void* O,
+                                 grat_dtype dtype, int32_t batch, int32_t heads, int32_t head_dim,
+                                 int64_t stride_b, int64_t stride_h, int64_t stride_n,
+                                 OutStrides os, float scale,
+                                 int32_t n_global, int32_t global_first, int32_t ndim,
+                                 const int32_t* grid, const int32_t* group,
+                                 const int32_t* d_kv_count, const int32_t* d_kv_index,
+                                 int32_t max_kv, void* hip_stream) {
+    Plan plan;
+    const grat_status st = plan_attention(Q, K, V, O, dtype, batch, heads, head_dim, stride_b, stride_h, stride_n, os, scale, n_global,
+                                          global_first, ndim, grid, group, d_kv_count, d_kv_index, max_kv, plan);
+    return st == GRAT_OK ? launch(plan, dtype, head_dim, hip_stream) : st;
 }
 
 extern "C" grat_status grat_attention_fwd(const void* Q, const void* K, const void* V, void* O,
@@ -441,17 +486,15 @@ extern "C" grat_status grat_attention_packed_fwd(const void* QKV, void* O, grat_
                          grid, group, d_kv_count, d_kv_index, max_kv, hip_stream);
 }
 
-extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, const void* V, void* O,
-                                                grat_dtype dtype, int32_t batch, int32_t heads,
-                                                int64_t n_tokens, int32_t head_dim,
-                                                int64_t stride_b, int64_t stride_h,
-                                                int64_t stride_n, float scale, void* hip_stream) {
+static grat_status plan_dense(const void* Q, const void* K, const void* V, void* O, grat_dtype dtype, int32_t batch, int32_t heads,
+                              int64_t n_tokens, int32_t head_dim, int64_t stride_b, int64_t stride_h, int64_t stride_n, float scale,
+                              Plan& plan) {
     if (n_tokens >= kMaxElems) return GRAT_ERR_BAD_DIMS;
     grat_status st = check_tensors(Q, K, V, O, dtype, batch, heads, head_dim, n_tokens, stride_b,
                                    stride_h, stride_n, scale);
     if (st != GRAT_OK) return st;
 
-    AttnParams p{};
+    AttnParams& p = plan.p;
     p.Q = Q; p.K = K; p.V = V; p.O = O;
     p.stride_b = stride_b; p.stride_h = stride_h; p.stride_n = (int32_t)stride_n;
     p.o_stride_b = stride_b; p.o_stride_h = stride_h; p.o_stride_n = (int32_t)stride_n;
@@ -473,11 +516,57 @@ extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, co
     if ((int64_t)batch * heads * ((int64_t)p.q_tiles + 8) >= kMaxElems - 8) return GRAT_ERR_UNSUPPORTED;
 
     fill_fastdivs(p);
-    const hipError_t e = is16(dtype)
-                             ? launch_attn_bf16(p, kDense, dtype == GRAT_F16, head_dim, (hipStream_t)hip_stream)
-                             : launch_attn_f32(p, bm, f32_key_waves((int64_t)batch * heads * p.q_tiles, n_tokens), head_dim, true,
-                                               (hipStream_t)hip_stream);
-    return e == hipSuccess ? GRAT_OK : GRAT_ERR_HIP;
+    plan.mode = kDense;
+    plan.key_waves = f32_key_waves(bh * p.q_tiles, n_tokens);
+    plan.xcd_tiles = most_tiles_of_an_xcd(p, bh, false, false);
+    return GRAT_OK;
+}
+
+extern "C" grat_status grat_dense_attention_fwd(const void* Q, const void* K, const void* V, void* O,
+                                                grat_dtype dtype, int32_t batch, int32_t heads,
+                                                int64_t n_tokens, int32_t head_dim,
+                                                int64_t stride_b, int64_t stride_h,
+                                                int64_t stride_n, float scale, void* hip_stream) {
+    Plan plan;
+    const grat_status st = plan_dense(Q, K, V, O, dtype, batch, heads, n_tokens, head_dim, stride_b, stride_h, stride_n, scale, plan);
+    return st == GRAT_OK ? launch(plan, dtype, head_dim, hip_stream) : st;
+}
+
+extern "C" grat_status grat_probe_launch(grat_dtype dtype, int32_t batch, int32_t heads, int32_t head_dim, int32_t n_global,
+                                         int32_t ndim, const int32_t* grid, const int32_t* group, int32_t max_kv,
+                                         grat_launch_info* info) {
+    if (!info) return GRAT_ERR_NULL;
+    // a contiguous [B, H, N, d] call; what the pointers point to is not looked at
+    void* const t = (void*)(uintptr_t)4096;
+    const int32_t* const list = (const int32_t*)t;
+    Plan plan;
+    if (ndim == 0) {
+        const int64_t h = (int64_t)n_global * head_dim;
+        const grat_status st = plan_dense(t, t, t, t, dtype, batch, heads, n_global, head_dim, heads * h, h, head_dim, 1.f, plan);
+        if (st != GRAT_OK) return st;
+    } else {
+        Geometry geo;
+        grat_status st = make_geometry(ndim, grid, group, &geo);
+        if (st != GRAT_OK) return st;
+        if (n_global < 0 || head_dim < 1 || heads < 1) return GRAT_ERR_BAD_DIMS;
+        const int64_t h = (geo.n_tokens + n_global) * head_dim;
+        st = plan_attention(t, t, t, t, dtype, batch, heads, head_dim, heads * h, h, head_dim, OutStrides{heads * h, h, head_dim}, 1.f,
+                            n_global, 1, ndim, grid, group, list, list, max_kv, plan);
+        if (st != GRAT_OK) return st;
+    }
+    const AttnParams& p = plan.p;
+    *info = grat_launch_info{};
+    info->mode = plan.mode;
+    info->rows = p.q_rows;
+    info->teams = p.teams;
+    info->whole_tiles = p.n_whole;
+    info->longest_first = p.longest_first;
+    if (is16(dtype)) info->tile_keys = mfma_tile_keys(p, plan.mode);
+    else if (p.q_rows == 16) info->key_waves = plan.key_waves;
+    const int64_t grouped = plan.mode == kDense ? 0 : (int64_t)batch * heads * p.geo.num_groups * p.q_tiles;
+    info->tiles = p.n_dense_tiles + (int32_t)grouped;
+    info->xcd_tiles = (int32_t)plan.xcd_tiles;
+    return GRAT_OK;
 }
 
 extern "C" const char* grat_status_string(grat_status status) {

@@ -81,6 +81,14 @@ struct AttnParams {
 //             (valid, meaningless) address and get weight 0, queries outside are not stored.
 enum AttnMode : int { kGrouped = 0, kDense = 1, kJoint = 2, kRagged = 3 };
 
+// Keys of the MFMA kernel's LDS tiles.  64-row workgroups take 32-key tiles unless the lists are long (measured at 512x512
+// tokens in 8x8 groups: lists of 9 / 25 / 49 groups gain 16-19 % from the small tiles, the criss-cross lists of 127 groups
+// lose 5 %), but not in joint sequences: that variant of the 32-key schedule does not fit the register file.
+inline int mfma_tile_keys(const AttnParams& p, int mode) {
+    if (p.teams == 4) return 32;
+    return p.q_rows == 64 && mode != kJoint && (int64_t)p.max_kv * p.geo.group_tokens <= 64 * 64 ? 32 : 64;
+}
+
 // Launchers: each returns the hipError_t of its launch.
 hipError_t launch_build_block_lists(const Geometry& geo, int ndim, grat_pattern pattern,
                                     const int32_t radius[3], int32_t* d_kv_count,

@@ -25,7 +25,7 @@ PATTERNS = {"block": 0, "cross": 1, "cross_planes": 2, "dense": 3}
 DTYPES = {torch.bfloat16: 0, torch.float32: 1, torch.float16: 2}
 EXPORTS = ("grat_block_list_shape", "grat_build_block_lists", "grat_validate_block_lists", "grat_attention_fwd",
            "grat_attention_global_fwd", "grat_attention_packed_fwd", "grat_dense_attention_fwd",
-           "grat_status_string", "grat_probe_mfma")
+           "grat_status_string", "grat_probe_mfma", "grat_probe_launch")
 
 _i32, _i64, _f32, _vp = ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_void_p
 _pi32 = ctypes.POINTER(ctypes.c_int32)
@@ -76,6 +76,8 @@ def lib() -> ctypes.CDLL:
         L.grat_status_string.restype = ctypes.c_char_p
         L.grat_probe_mfma.argtypes = [_i32, _i32, _vp, _i32, _i32, _vp]
         L.grat_probe_mfma.restype = _i32
+        L.grat_probe_launch.argtypes = [_i32, _i32, _i32, _i32, _i32, _i32, _pi32, _pi32, _i32, _vp]
+        L.grat_probe_launch.restype = _i32
         _native = _load_native(L)   # (ahead of _lib: another thread that finds _lib set uses both)
         _lib = L
     return _lib

@@ -203,7 +203,8 @@ def test_probe_argument_errors():
 
 
 def test_bench_names_the_launched_instantiation():
-    """bench.py restates the library's launch rules to name the kernel in its roofline block (host only)."""
+    """The kernel in bench.py's roofline block is the one that the library launches, and a stored traffic figure is that
+    kernel's (host only)."""
     import numpy as np
     import bench
     from paper_2505_14687_amd import synth
@@ -213,7 +214,48 @@ def test_bench_names_the_launched_instantiation():
         pattern, radius = w.patterns[label]
         names[(wl, label)] = bench.kernel_name(w, int(np.prod(w.group)), 0, pattern, radius)
     assert names[("img8192", "B3")] == "grat::attn_mfma_kernel<8, 64, 0, false, 128>"
-    assert names[("img1024", "X")] == "grat::attn_mfma_kernel<4, 64, 0, false, 128>"
+    assert names[("img1024", "X")] == "grat::attn_mfma_mixed_kernel<false>"
     assert names[("video", "B3")] == "grat::attn_mfma_kernel<4, 64, 0, false, 128>"
     assert names[("img8192_g8", "B3")] == "grat::attn_mfma_kernel<2, 32, 0, false, 128>"
     assert names[("img8192_g8", "X")] == "grat::attn_mfma_kernel<2, 64, 0, false, 128>"
+    assert bench.measured_traffic("img8192", "B3", names[("img8192", "B3")]) > 1e10
+    assert bench.measured_traffic("img1024", "X", names[("img1024", "X")]) is None   # profiled as 128-row workgroups
+
+
+def test_probe_launch_argument_errors():
+    import torch
+    from paper_2505_14687_amd.probe import grat_probe_launch
+    L = grat.lib()
+    assert L.grat_probe_launch(0, 1, 1, 128, 64, 0, None, None, 0, None) == 1
+    def st(*a, **k):
+        return status_of(lambda: grat_probe_launch(*a, **k))
+    bf16, f32 = torch.bfloat16, torch.float32
+    assert st(bf16, 0, 1, 128, n_global=64) == 2 and st(bf16, 1, 1, 128, n_global=0) == 2 and st(bf16, 1, 1, 96, n_global=64) == 6
+    assert st(bf16, 1, 1, 128, (64, 0), (16, 16), 9) == 2 and st(bf16, 1, 1, 128, (64, 64), (16, 16), 0) == 5
+    assert st(bf16, 1, 1, 128, (64, 64), (4, 4), 9) == 6 and st(f32, 1, 1, 128, (64, 64), (16, 16), 9, 8) == 6
+    assert st(bf16, 1, 1, 128, (64, 60), (16, 16), 9, 8) == 3 and st(bf16, 1, 1, 128, (64, 64), (16, 16), 9, -1) == 2
+
+
+# one launch of every kind, with the tiles of the compute-unit array that gets most (8 of them, 32 units each)
+@pytest.mark.parametrize("dtype,batch,heads,d,grid,group,max_kv,n_global,kernel,tiles,xcd", [
+    ("bf16", 1, 24, 128, (512, 512), (16, 16), 9, 0, "mfma_kernel<8, 64, 0, false, 128>", 24576, 3072),
+    ("f16", 2, 24, 128, (90, 160), (16, 16), 9, 0, "mfma_kernel<8, 64, 3, true, 128>", 2880, 360),
+    ("bf16", 4, 16, 64, (64, 64), (16, 16), 7, 0, "mfma_kernel<4, 64, 0, false, 64>", 2048, 256),
+    ("bf16", 1, 24, 128, (64, 64), (16, 16), 9, 0, "mfma_mixed_kernel<false>", 384, 48),
+    ("bf16", 1, 1, 128, (64, 64), (16, 16), 9, 0, "mfma_teams_kernel<2, 32, 0, false, 128, 4>", 64, 8),
+    ("f16", 1, 8, 64, (64, 64), (16, 16), 9, 0, "mfma_teams_kernel<4, 64, 0, true, 64, 2>", 256, 32),
+    ("bf16", 1, 24, 128, (128, 128), (16, 16), 9, 512, "mfma_kernel<8, 64, 2, false, 128>", 1584, 198),
+    ("bf16", 1, 24, 64, (64, 64), (16, 16), 9, 256, "mfma_kernel<4, 64, 2, false, 64>", 816, 102),
+    ("bf16", 1, 2, 128, (48, 32), (16, 16), 6, 100, "mfma_teams_kernel<4, 64, 2, false, 128, 2>", 26, 5),
+    ("bf16", 1, 24, 128, None, None, 0, 4429, "mfma_kernel<8, 64, 1, false, 128>", 432, 54),
+    ("f16", 1, 1, 128, None, None, 0, 1000, "mfma_teams_kernel<2, 32, 1, true, 128, 4>", 16, 2),
+    ("f32", 1, 24, 128, (64, 64), (16, 16), 7, 0, "f32_kernel<128, false, 4>", 768, 96),
+    ("f32", 1, 2, 64, (32, 32), (8, 8), 9, 0, "f32_split_kernel<64, false, 8>", 128, 16),
+    ("f32", 4, 32, 64, None, None, 0, 40, "f32_split_kernel<64, true, 1>", 384, 48),
+])
+def test_probe_names_what_is_launched(dtype, batch, heads, d, grid, group, max_kv, n_global, kernel, tiles, xcd):
+    import torch
+    from paper_2505_14687_amd.probe import grat_probe_launch, launched_kernel
+    a = ({"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32}[dtype], batch, heads, d, grid, group, max_kv, n_global)
+    i = grat_probe_launch(*a)
+    assert (launched_kernel(*a), i.tiles, i.xcd_tiles) == ("grat::attn_" + kernel, tiles, xcd)

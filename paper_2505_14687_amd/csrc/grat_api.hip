@@ -414,8 +414,13 @@ static grat_status plan_attention(const void* Q, const void* K, const void* V, v
     // (head_dim 64 splits 256-token groups in two: the line lies at the same number of queries)
     // A launch that gives no compute unit more than one workgroup starts them all at once, in whatever order: there the
     // ranking, a memory round trip and 64 steps in every wave, only delays them (1.1 of 13.6 us at 32x32 tokens in 8x8
-    // groups, 2 heads x 64, fp32).
-    p.longest_first = geo.num_groups <= 64 && total + p.n_dense_tiles > 256 &&
+    // groups, 2 heads x 64, fp32).  But the order without it deals every head's tiles in eighths that are rounded up, and
+    // an XCD has 32 compute units: where it gets more tiles than that the last ones make a second round, which costs more.
+    // us ranked | not, at most 256 tiles, 3x3 lists in 16x16 groups: 80x80 tokens, 5 heads (35 tiles on an XCD) 41.7 | 55.3,
+    // 48x48 tokens, 14 heads (36) 38.2 | 49.2, at head_dim 64 24.5 | 33.1, 13 heads (33) 37.4 | 41.0, with 10 prompt tokens
+    // 41.4 | 52.6.
+    p.longest_first = geo.num_groups <= 64 &&
+                      (total + p.n_dense_tiles > 256 || most_tiles_of_an_xcd(p, (int64_t)batch * heads, true, false) > 32) &&
                       (is16(dtype) && head_dim == 64 && n_g % 256 == 0 ? total / 2 : total) <= 16 * 256;
     p.fd_tiles_per_rank = make_fastdiv((uint32_t)(batch * heads * p.q_tiles));
     fill_fastdivs(p);

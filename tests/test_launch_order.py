@@ -1,0 +1,36 @@
+"""Launches of at most one tile a compute unit (256 of them, 32 to each of the 8 dies that workgroups go to in turn): no die may
+get more tiles than it has compute units, or the launch takes a second round.  Host only."""
+import math
+
+import pytest
+import torch
+
+from paper_2505_14687_amd.probe import grat_probe_launch
+
+DIES, UNITS = 8, 32
+
+
+# heads, or tiles a head, that are no multiple of 8
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dtype,grid,group,heads,prompt", [
+    (torch.bfloat16, (48, 48), (16, 16), 14, 0), (torch.float16, (48, 48), (16, 16), 13, 0), (torch.bfloat16, (80, 80), (16, 16), 5, 0),
+    (torch.bfloat16, (48, 48), (16, 16), 13, 10), (torch.float32, (56, 56), (8, 8), 1, 0)])
+def test_no_die_gets_more_tiles_than_units(dtype, grid, group, heads, prompt, d):
+    i = grat_probe_launch(dtype, 1, heads, d, grid, group, 9, prompt)
+    assert i.tiles <= DIES * UNITS and i.xcd_tiles <= UNITS
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_sweep_of_small_launches(dtype):
+    seen = 0
+    for rows in range(1, 9):
+        for cols in range(rows, 9):
+            for heads in range(1, 33):
+                for prompt in (0, 100) if dtype == torch.bfloat16 else (0,):
+                    i = grat_probe_launch(dtype, 1, heads, 64, (16 * rows, 16 * cols), (16, 16), min(9, rows * cols), prompt)
+                    if i.tiles > DIES * UNITS:
+                        continue
+                    seen += 1
+                    # (by rank the prompt tiles and the grouped ones are each dealt in turn: one more where neither fills a row of dies)
+                    assert i.xcd_tiles <= UNITS or (prompt and i.longest_first and i.xcd_tiles <= math.ceil(i.tiles / DIES) + 1)
+    assert seen > 200

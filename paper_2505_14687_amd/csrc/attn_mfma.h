@@ -151,9 +151,10 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     constexpr bool dense = DENSE;
 
     extern __shared__ int32_t s_dyn[];   // [n_g] row offsets inside a group, then [max_kv] group origins (kRagged: and the two tables below)
-    // Teams walk a whole sequence from its last tile to the first: only the beginning has to look for a tile cut short, and
-    // one copy of the walk does (head_dim 128, 8 heads: 1 024 tokens 16.4 -> 13.8 us, where the two copies of the 32-key walk
-    // spilled 27 registers, 2 049 tokens 31.1 -> 29.7).  Undivided walks gain nothing or lose where no tile is cut short
+    // Teams have one copy of the walk over a whole sequence, from its last tile to the first.  64-key tiles (two teams): a tile
+    // cut short comes first, and only the first two steps look for it (head_dim 128, 8 heads, 2 049 tokens 31.1 -> 29.7 us).
+    // 32-key tiles (four teams): every step looks, the order is of no use to it; what helps is that there is one copy, since two
+    // spilled 27 registers (1 024 tokens 16.4 -> 13.8).  Undivided walks gain nothing or lose backwards where no tile is cut short
     // (head_dim 128: 8 191 tokens 660 | 664, 4 352 tokens 215.5 | 219.8; head_dim 64: 8 191 tokens 425 | 419, 8 192 tokens 415 | 418).
     constexpr bool kBackwards = DENSE && TEAMS > 1;
     constexpr bool kLists = MODE == kGrouped || MODE == kRagged;   // every KV tile comes from a listed group
@@ -689,6 +690,10 @@ __device__ __forceinline__ void attn_tile(const AttnParams& p, const int bh, con
     // 24 heads: two thirds of the workgroups take the plain walk; 760 -> 741 us, head_dim 64, 250x250 tokens 990 -> 950).
     // (A loop of their own for those waves: a branch around the steps of the others would end the straight-line code that
     // covers the table reads, 1.6 % at 97x70 tokens, head_dim 64.)
+    // (Two copies of the walk cost the 32-key kernels 23 (head_dim 128) and 17 spilled registers, all outside of the steps.  One copy
+    // that asks in every step whether anything is clipped spills none and is better only where a walk is short and all is over
+    // in one round: one | two, 8x8 groups, 24 heads, 20x28 tokens 21.6 | 22.1 us, 60x60 44.2 | 44.5, 250x250 647 | 629; head_dim 64
+    // 18.6 | 18.6, 26.9 | 27.0, 363 | 347.)
     auto fetch_only = [&]() {
         start(yes);
         for (int t = 0; t < n_tiles + (kBN == 64 ? 1 : 2); ++t) {   // as many barriers as the walks below have
@@ -942,8 +947,11 @@ constexpr int waves_per_simd(int nwaves, int bn, int mode, int d) {
 // The kernel: picks this workgroup's query tile (tile_order.h) and runs it.  In joint mode the long-running
 // dense tiles over the prompt rows get the lowest block indices, dealt round-robin over the XCDs, and the
 // grouped tiles follow.  (Both ways to pick a grouped tile lead to one copy of its code: with a copy each, of the 512x512
-// token kernels some spilled 5 to 21 scalar registers, clipped grids 13 to 66; 250x250 tokens 1 640 -> 1 620 us.  The 8-wave
-// joint kernel is 1 % faster with two: 128x128 tokens, 512 prompt tokens 537 against 543 us.)
+// token kernels some spilled 5 to 21 scalar registers, clipped grids 13 to 66; 250x250 tokens 1 640 -> 1 620 us, ranked launches of
+// 256-row workgroups 0.5 to 1.3 % more time.  At head_dim 128 the 4-wave grouped kernel has two, and the joint ones: us, two | one copy,
+// ranked launches of 128-row workgroups, 5x5 lists, 48x64 tokens, 24 / 26 heads 117 / 119 | 122 / 133, 48x96, 16 heads 126 | 134, 64x80, 14 heads 134 |
+// 140; criss-cross 1 to 2 %; joint, 4 waves, 64x64 tokens, 256 prompt tokens, 24 heads 114 | 116.5, 8 waves, 128x128, 512 prompt tokens
+// 537 | 543.)
 template <int NWAVES, int BN, int MODE, bool F16, int D>
 __global__ __launch_bounds__(NWAVES * 64, waves_per_simd(NWAVES, BN, MODE, D)) void attn_mfma_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t sK[2][BN * D * 2];
@@ -959,7 +967,7 @@ __global__ __launch_bounds__(NWAVES * 64, waves_per_simd(NWAVES, BN, MODE, D)) v
             return;
         }
     }
-    if constexpr (MODE == kJoint && NWAVES == 8) {
+    if constexpr (D == 128 && ((MODE == kJoint && NWAVES >= 4) || (MODE == kGrouped && NWAVES == 4))) {
         int gamma;
         if (p.longest_first) {
             if (longest_first_tile(p, block, bh, tile, gamma))
@@ -998,8 +1006,8 @@ __global__ __launch_bounds__(NWAVES * TEAMS * 64, 2) void attn_mfma_teams_kernel
 }
 
 // Launches of little more than one round: p.n_whole tiles of 256 rows, one for every compute unit, the others as two 128-row
-// workgroups of two teams each, all longest list first (64x64 tokens in 16x16 groups, 3x3 lists, 24 heads: 87.5 us as 128-row
-// workgroups, 85.1; 64x80 tokens, 16 heads 80.5, 70.4).
+// workgroups of two teams each, all longest list first (80x80 tokens in 16x16 groups, 3x3 lists, 12 heads: 79 us as 128-row
+// workgroups, 73; 64x80 tokens, 16 heads 80, 73).
 template <bool F16>
 __global__ __launch_bounds__(512, 2) void attn_mfma_mixed_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[8][64 * 128 * 2];

@@ -267,15 +267,26 @@ static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t
 
 // Whole tiles of a mixed launch (attn_mfma_mixed_kernel), 0: not one.  A compute unit each for the first 256 tiles of
 // 256 rows; what is left, if it is at most 128 tiles, keeps the others busy as twice as many workgroups of half the walk,
-// where 128-row workgroups, two a compute unit, would take another 0.7 of a round.  us as those | mixed, 256-token
-// groups, head_dim 128: 64x64 tokens, 3x3 lists, 17 / 18 / 20 / 22 / 23 / 24 heads 64.8 / 66.3 / 74.4 / 86.5 / 94.3 / 87.5 | 64.4 / 67.3 /
-// 70.0 / 84.7 / 87.5 / 85.1, criss-cross, 17 / 20 / 24 heads 86.1 / 85.9 / 90.6 | 81.5 / 83.8 / 89.8; video 8x32x48, 6 / 7 heads 134.8 /
-// 167.3 | 120.8 / 155.1; 128x96 tokens, 6 heads 86.5 | 76.4; 64x80 tokens, 16 heads 80.5 | 70.4.  After two full rounds of
-// 256-row workgroups there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads 177.4 | 184.1), and so do
-// 1 024-token groups (96x96 tokens, 8 heads 211 | 221).
-static int32_t mixed_whole(int64_t tiles256, int64_t tables) {
+// where 128-row workgroups, two a compute unit, would take another 0.7 of a round.  256-token groups, head_dim 128, us as
+// those | mixed, means of two allocations:
+//   128x128 tokens, 3x3 lists, 5 / 6 heads 98 / 124 | 92 / 103, 5x5 208 / 232 | 186 / 230, criss-cross 171 / 182 | 164 / 185; 96x96, 3x3, 8 / 10
+//   heads 77 / 98 | 71 / 94; 80x80, 3x3, 11 / 12 heads 80 / 79 | 68 / 73; 64x80, 3x3, 15 / 16 heads 82 / 80 | 71 / 73, criss-cross 98 / 93 | 94 / 94;
+//   video 8x32x48, 6 heads, 3x3x3 lists 133 | 125.
+// Not where it loses (375 launches of 4 to 64 groups, 16 to 96 heads x batch):
+//   lists longer than half of the grid's groups, whose lengths differ most: 128-row workgroups even them out in halves of a
+//   tile (5x5 lists in 80x96 tokens, 9 heads 142 | 158, in 96x96, 8 heads 153 | 163; 3x3 in 64x64, 18 heads 64 | 67, 24 heads 88 | 88);
+//   fewer than 20 groups, whose lists are short (32x32 tokens, 96 heads, 3x3 57 | 61, criss-cross 48 | 51; 48x64, 32 heads 82 | 88;
+//   48x96, 16 heads 64 | 68);
+//   a second round of a few tiles (48x176 tokens, 8 heads, 8 of them 63 | 66), or of few groups and more than three quarters full (80x96
+//   tokens, 12 heads 88 | 93).
+// What is left gains 5.9 % on average, up to 24 %, and loses up to 4 % in three of 129 launches.  After two full rounds of 256-row workgroups
+// there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads 177.4 | 184.1), and so do 1 024-token groups (96x96
+// tokens, 8 heads 211 | 221).
+static int32_t mixed_whole(int64_t tiles256, int64_t groups, int64_t max_kv, int64_t tables) {
     if (128 * 1024 + 4096 + tables > 160 * 1024) return 0;
-    return tiles256 > 256 && tiles256 <= 256 + 128 ? 256 : 0;
+    const int64_t rest = tiles256 - 256;
+    if (rest <= 8 || rest > (groups < 36 ? 96 : 128)) return 0;
+    return groups >= 20 && 2 * max_kv <= groups ? 256 : 0;
 }
 
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
@@ -381,7 +392,7 @@ static grat_status plan_attention(const void* Q, const void* K, const void* V, v
             if (p.teams == 4) bm = 64;
             else if (p.teams == 2) bm = 128;
             if (p.teams == 1 && n_global == 0 && head_dim == 128 && n_g == 256 && geo.num_groups <= 64)
-                p.n_whole = mixed_whole(tiles64 / 4, tables);
+                p.n_whole = mixed_whole(tiles64 / 4, geo.num_groups, max_kv, tables);
             if (p.n_whole > 0) bm = 256;
         }
     } else {

@@ -240,15 +240,17 @@ static int dense_tile_rows(int head_dim, int64_t rows, int64_t problems) {
 // of each of its steps (a lone 128-row workgroup takes 1 us for 64 keys, of which its products are 0.45).
 // `tiles64` / `tiles128` = workgroups of the launch with that many rows (0: not possible), `keys` = an upper bound of a
 // list's keys, `tables` = LDS for them.  us, 1 / 2 / 4 teams, head_dim 128 | 64:
-//   64x64 tokens in 16x16 groups, 3x3 lists, 1 head 36 / 31 / 24 | 25 / 22 / 16, 4 heads 38 / 33 / 26 | 26 / 22 / 17, 8 heads
-//   (256 tiles of 128 rows) 41 / 38 / 46 | 27 / 24 / 30; 32x32 tokens in 8x8 groups 13.5 / - / 11 | 10.5 / - / 8;
-//   own group only (256 keys) 8.0 / 9.3 / 8.7 | 6.5 / 7.2 / 6.6; video 8x32x48, 2 heads 53 / 46 / 55 | 38 / 32 / 37;
-//   sequences x tokens: 16 x 512 11 / 12 / 14 | 8.6 / 8.5 / 7.0, 8 x 1 024 19 / 19 / 14 | 14 / 12 / 9, 16 x 1 024 20 / 20 / 20 |
-//   15 / 13 / 10, 24 x 1 200 24 / 25 / 37 | 19 / 16 / 21, 14 x 1 500 27 / 25 / 39 | 22 / 18 / 24, 8 x 2 048 34 / 32 / 28 |
-//   25 / 22 / 16, 1 x 16 384 224 / 190 / 149 | 167 / 130 / 88, 1 x 32 768 514 / 482 / 567 | 341 / 292 / 333.
+//   64x64 tokens in 16x16 groups, 3x3 lists, 1 head 35 / 30 / 22 | 25.5 / 21.7 / 15.7, 4 heads 36 / 32 / 25 | 26 / 22 / 16.5, 8 heads
+//   (256 tiles of 128 rows) 39 / 36 / 43 | 26 / 23 / 27; 32x32 tokens in 8x8 groups 13.0 / - / 10.4 | 10.0 / - / 7.4;
+//   own group only (256 keys) 8.0 / 9.2 / 8.6 | 6.1 / 6.5 / 6.2; video 8x32x48, 2 heads 67 / 58 / 61 | 48 / 40 / 40;
+//   sequences x tokens: 16 x 512 11.1 / 11.5 / 10.4 | 8.3 / 8.0 / 6.8, 24 x 512 11.2 / 11.7 / 12.5 | 8.4 / 8.1 / 7.1, 8 x 1 024 18.2 / 17.4 /
+//   14.1 | 13.5 / 11.8 / 9.2, 10 x 1 024 18.3 / 17.8 / 14.6 | 13.5 / 11.9 / 9.4, 16 x 1 024 18.5 / 18.7 / 16.5 | 13.9 / 12.2 / 10.2, 24 x 1 200 25 / 25 / 33 |
+//   18 / 15 / 21, 14 x 1 500 27 / 25 / 35 | 21 / 16 / 23, 8 x 2 048 33 / 30 / 24 | 24 / 20 / 15.5, 1 x 16 384 228 / 189 / 148 | 168 / 130 / 89,
+//   1 x 32 768 542 / 485 / 586 | 355 / 292 / 348.
+// (Sequences at head_dim 128: the line was drawn with a kernel that spilled registers, which those figures no longer show; four teams
+// would now win down to about max(384, 4 * tiles64) keys, 10 x 1 024 18.3 -> 14.6.)
 static int key_teams(int head_dim, int64_t tiles64, int64_t tiles128, int64_t keys, int64_t tables, bool dense) {
     if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
-    // (sequences at head_dim 128: the more tiles, the less is left to gain)
     const int64_t enough4 = head_dim == 64 ? 384 : dense ? std::max<int64_t>(640, 8 * tiles64) : 512;
     if (tiles64 > 0 && tiles64 <= 256 && keys >= enough4) return 4;
     if (tiles128 > 0 && tiles128 <= 256 && keys >= (head_dim == 64 ? 1024 : 1408)) return 2;

@@ -133,12 +133,12 @@ def small_case(B, H, grid, group, pattern, radius, q_gain=1.0, seed=91):
 
 
 @pytest.mark.parametrize("grid,group,pattern,radius", [
-    ((32, 48), (8, 8), "block", (1, 1)),              # 64-token groups: 2-wave workgroups
+    ((32, 48), (8, 8), "block", (1, 1)),              # 64-token groups: four teams, like all of these
     ((32, 48), (8, 8), "cross", (0, 0)),
-    ((32, 48), (8, 16), "block", (1, 1)),             # 128-token groups: 4-wave workgroups
+    ((32, 48), (8, 16), "block", (1, 1)),             # 128-token groups
     ((48, 48), (16, 16), "block", (1, 0)),            # 256-token groups, asymmetric radius
-    ((48, 48), (24, 8), "cross", (0, 0)),             # 192-token groups -> 64-row query tiles
-    ((64, 64), (32, 32), "block", (1, 1)),            # 1024-token groups: 4 query tiles each
+    ((48, 48), (24, 8), "cross", (0, 0)),             # 192-token groups: three 64-row query tiles
+    ((64, 64), (32, 32), "block", (1, 1)),            # 1024-token groups: 8 query tiles each, two teams
     ((4, 16, 24), (2, 8, 8), "block", (1, 1, 1)),
     ((4, 16, 24), (2, 8, 8), "cross", (0, 0, 0)),
     ((4, 16, 24), (2, 8, 8), "cross_planes", (0, 0, 0)),
@@ -154,8 +154,8 @@ def test_small_grouped(grid, group, pattern, radius):
 @pytest.mark.parametrize("grid,group,pattern,radius", [
     ((40, 56), (16, 16), "block", (1, 1)),            # last groups 8 x 8 of 16 x 16: whole KV tiles outside
     ((40, 56), (16, 16), "cross", (0, 0)),
-    ((33, 47), (8, 8), "block", (1, 1)),              # 2-wave workgroups; one row / seven columns left over
-    ((36, 40), (8, 16), "cross", (0, 0)),             # 4-wave workgroups
+    ((33, 47), (8, 8), "block", (1, 1)),              # undivided 2-wave workgroups; one row / seven columns left over
+    ((36, 40), (8, 16), "cross", (0, 0)),             # undivided 4-wave workgroups
     ((70, 90), (32, 32), "block", (1, 1)),            # 1024-token boxes: border query tiles wholly outside
     ((5, 20, 28), (2, 8, 8), "block", (1, 1, 1)),     # ragged on all three axes
     ((5, 20, 28), (2, 8, 8), "cross_planes", (0, 0, 0)),

@@ -29,8 +29,8 @@ def small_case(B, H, grid, group, pattern, radius, q_gain=1.0, seed=501):
 @pytest.mark.parametrize("grid,group,pattern,radius", [
     ((64, 64), (16, 16), "block", (1, 1)),
     ((64, 64), (16, 16), "cross", (0, 0)),
-    ((32, 48), (8, 16), "block", (1, 1)),             # 4-wave workgroups
-    ((32, 48), (8, 8), "cross", (0, 0)),              # 2-wave workgroups
+    ((32, 48), (8, 16), "block", (1, 1)),             # 128-token groups: four teams
+    ((32, 48), (8, 8), "cross", (0, 0)),              # 64-token groups: four teams
     ((4, 16, 24), (2, 8, 8), "cross_planes", (0, 0, 0)),
     ((40, 56), (16, 16), "block", (1, 1)),            # clipped border groups
 ])

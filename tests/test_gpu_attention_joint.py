@@ -26,8 +26,8 @@ def run_joint(host, n_global, global_first, grid, group, pattern, radius, scale)
 @pytest.mark.parametrize("n_global,global_first,grid,group,pattern,radius", [
     (64, True, (32, 32), (16, 16), "block", (1, 1)),
     (64, False, (32, 32), (16, 16), "block", (1, 1)),
-    (100, True, (32, 48), (8, 16), "cross", (0, 0)),          # ragged prompt tile, 4-wave workgroups
-    (1, False, (32, 48), (8, 8), "block", (1, 1)),            # one prompt token, 2-wave workgroups
+    (100, True, (32, 48), (8, 16), "cross", (0, 0)),          # ragged prompt tile, two teams
+    (1, False, (32, 48), (8, 8), "block", (1, 1)),            # one prompt token, undivided 2-wave workgroups
     (300, True, (48, 48), (16, 16), "cross", (0, 0)),         # more prompt rows than one dense tile
     (77, False, (4, 16, 24), (2, 8, 8), "block", (1, 1, 1)),
     (200, True, (4, 16, 16), (4, 8, 8), "cross_planes", (0, 0, 0)),

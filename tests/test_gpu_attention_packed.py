@@ -21,8 +21,8 @@ def pack(dev):
 
 @pytest.mark.parametrize("dtype,d,grid,group,pattern,radius,n_global", [
     ("bf16", 128, (32, 32), (16, 16), "block", (1, 1), 0),
-    ("bf16", 128, (32, 48), (8, 16), "cross", (0, 0), 0),          # 4-wave workgroups
-    ("bf16", 128, (32, 48), (8, 8), "block", (1, 1), 0),           # 2-wave workgroups
+    ("bf16", 128, (32, 48), (8, 16), "cross", (0, 0), 0),          # 128-token groups: four teams
+    ("bf16", 128, (32, 48), (8, 8), "block", (1, 1), 0),           # 64-token groups: four teams
     ("bf16", 128, (4, 16, 16), (4, 8, 8), "cross_planes", (0, 0, 0), 0),
     ("bf16", 128, (32, 32), (16, 16), "block", (1, 1), 100),       # prompt tokens ahead of the grid
     ("bf16", 128, (40, 56), (16, 16), "block", (1, 1), 0),         # clipped border groups, O with its own pitch

@@ -428,12 +428,14 @@ static grat_status plan_attention(const void* Q, const void* K, const void* V, v
     // A launch that gives no compute unit more than one workgroup starts them all at once, in whatever order: there the
     // ranking, a memory round trip and 64 steps in every wave, only delays them (1.1 of 13.6 us at 32x32 tokens in 8x8
     // groups, 2 heads x 64, fp32).  But the order without it deals every head's tiles in eighths that are rounded up, and
-    // an XCD has 32 compute units: where it gets more tiles than that the last ones make a second round, which costs more.
-    // us ranked | not, at most 256 tiles, 3x3 lists in 16x16 groups: 80x80 tokens, 5 heads (35 tiles on an XCD) 41.7 | 55.3,
-    // 48x48 tokens, 14 heads (36) 38.2 | 49.2, at head_dim 64 24.5 | 33.1, 13 heads (33) 37.4 | 41.0, with 10 prompt tokens
-    // 41.4 | 52.6.
-    p.longest_first = geo.num_groups <= 64 &&
-                      (total + p.n_dense_tiles > 256 || most_tiles_of_an_xcd(p, (int64_t)batch * heads, true, false) > 32) &&
+    // the workgroups that only fill these up need places too: with them the launch has to fit as well.  us ranked | not, at
+    // most 256 tiles, 3x3 lists in 16x16 groups: 80x80 tokens, 5 heads 41.7 | 55.3, 48x48 tokens, 14 heads 38.2 | 49.2, at head_dim 64
+    // 24.5 | 33.1, 12 heads with 86 prompt tokens 34 | 47.6; 517 launches of up to 256 workgroups are 6 % (up to 22) faster without
+    // ranking, 92 of more 13 % (up to 60) slower.  A full 256 of undivided workgroups, which do not have a compute unit to
+    // themselves, are ranked (fp32, 16x64 tokens in 8x8 groups, 16 heads x 64 45 | 48).
+    const int64_t workgroups = (int64_t)batch * heads * (((int64_t)geo.num_groups * p.q_tiles + kNumXcd - 1) / kNumXcd * kNumXcd) +
+                               xcd_padded_blocks(p.n_dense_tiles);
+    p.longest_first = geo.num_groups <= 64 && workgroups > (p.teams > 1 ? 256 : 255) &&
                       (is16(dtype) && head_dim == 64 && n_g % 256 == 0 ? total / 2 : total) <= 16 * 256;
     p.fd_tiles_per_rank = make_fastdiv((uint32_t)(batch * heads * p.q_tiles));
     fill_fastdivs(p);

@@ -1,5 +1,6 @@
-"""Launches of at most one tile a compute unit (256 of them, 32 to each of the 8 dies that workgroups go to in turn): no die may
-get more tiles than it has compute units, or the launch takes a second round.  Host only."""
+"""Launches of at most one tile a compute unit (256 of them, 32 to each of the 8 dies that workgroups go to in turn).  Those that
+are not ranked by list length deal every head's tiles in eighths, rounded up: no die may get more tiles than it has compute
+units that way, and the workgroups that only fill up an eighth have to fit as well, or the launch takes a second round.  Host only."""
 import math
 
 import pytest
@@ -20,6 +21,14 @@ def test_no_die_gets_more_tiles_than_units(dtype, grid, group, heads, prompt, d)
     assert i.tiles <= DIES * UNITS and i.xcd_tiles <= UNITS
 
 
+@pytest.mark.parametrize("dtype,d,grid,group,heads,prompt", [
+    (torch.bfloat16, 64, (48, 48), (16, 16), 12, 86), (torch.bfloat16, 128, (16, 40), (8, 8), 24, 0), (torch.bfloat16, 128, (16, 48), (16, 16), 30, 1),
+    (torch.float16, 128, (34, 46), (16, 16), 12, 0), (torch.float32, 64, (8, 56), (8, 8), 9, 0)])
+def test_launches_that_fit_only_without_their_padding_are_ranked(dtype, d, grid, group, heads, prompt):
+    i = grat_probe_launch(dtype, 1, heads, d, grid, group, 9, prompt)
+    assert i.tiles <= DIES * UNITS and i.longest_first
+
+
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_sweep_of_small_launches(dtype):
     seen = 0
@@ -33,6 +42,10 @@ def test_sweep_of_small_launches(dtype):
                     seen += 1
                     # (by rank the prompt tiles and the grouped ones are each dealt in turn: one more where neither fills a row of dies)
                     assert i.xcd_tiles <= UNITS or (prompt and i.longest_first and i.xcd_tiles <= math.ceil(i.tiles / DIES) + 1)
+                    tiles_per_head = rows * cols * math.ceil(256 / i.rows)
+                    grouped = DIES * math.ceil(tiles_per_head / DIES) * heads
+                    prompts = DIES * math.ceil(heads * math.ceil(prompt / i.rows) / DIES)
+                    assert i.longest_first == (grouped + prompts > (DIES * UNITS if i.teams > 1 else DIES * UNITS - 1))
     assert seen > 200
 
 

@@ -60,3 +60,13 @@ def test_sweep_of_small_launches(dtype):
     ((128, 128), (16, 16), 25, 6, True), ((128, 128), (16, 16), 9, 6, True), ((8, 32, 48), (4, 8, 8), 18, 7, True)])
 def test_mixed_launches_where_they_gain(grid, group, max_kv, heads, mixed):
     assert (grat_probe_launch(torch.bfloat16, 1, heads, 128, grid, group, max_kv).whole_tiles > 0) == mixed
+
+
+# joint sequences of more than 256 tiles: two teams only where the prompt tiles' walk is what the launch waits for
+@pytest.mark.parametrize("grid,group,max_kv,heads,d,prompt,teams", [
+    ((4, 8, 40), (2, 8, 8), 10, 24, 128, 88, 1), ((128, 64), (16, 16), 11, 12, 128, 36, 1), ((64, 96), (32, 32), 4, 8, 64, 36, 1),
+    ((64, 32), (16, 16), 5, 20, 128, 96, 1), ((64, 64), (16, 16), 16, 8, 128, 62, 1), ((128, 128), (16, 16), 15, 12, 128, 100, 1),
+    ((128, 128), (16, 16), 15, 8, 128, 100, 2), ((64, 64), (16, 16), 9, 12, 64, 256, 2), ((128, 128), (16, 16), 9, 8, 128, 512, 2),
+    ((48, 48), (16, 16), 9, 12, 64, 86, 2)])
+def test_teams_of_joint_sequences(grid, group, max_kv, heads, d, prompt, teams):
+    assert grat_probe_launch(torch.bfloat16, 1, heads, d, grid, group, max_kv, prompt).teams == teams

@@ -251,7 +251,12 @@ static int dense_tile_rows(int head_dim, int64_t rows, int64_t problems) {
 // would now win down to about max(384, 4 * tiles64) keys, 10 x 1 024 18.3 -> 14.6.)
 static int key_teams(int head_dim, int64_t tiles64, int64_t tiles128, int64_t keys, int64_t tables, bool dense) {
     if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
-    const int64_t enough4 = head_dim == 64 ? 384 : dense ? std::max<int64_t>(640, 8 * tiles64) : 512;
+    // (groups that could have 128-row workgroups, half as many, short lists: 512 keys, 120 / 168 / 216 tiles of 64 rows 12.1 / 12.6 / 12.9 us as
+    // those, 10.5 / 13.2 / 14.7 as four teams; 640 keys, 210 tiles 14.5, 11.7)
+    const int64_t enough4 = head_dim == 64   ? 384
+                            : dense          ? std::max<int64_t>(640, 8 * tiles64)
+                            : tiles128 > 0   ? std::max<int64_t>(512, 2 * tiles64 + 200)
+                                             : 512;
     if (tiles64 > 0 && tiles64 <= 256 && keys >= enough4) return 4;
     if (tiles128 > 0 && tiles128 <= 256 && keys >= (head_dim == 64 ? 1024 : 1408)) return 2;
     return 1;

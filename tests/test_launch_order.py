@@ -70,3 +70,11 @@ def test_mixed_launches_where_they_gain(grid, group, max_kv, heads, mixed):
     ((48, 48), (16, 16), 9, 12, 64, 86, 2)])
 def test_teams_of_joint_sequences(grid, group, max_kv, heads, d, prompt, teams):
     assert grat_probe_launch(torch.bfloat16, 1, heads, d, grid, group, max_kv, prompt).teams == teams
+
+
+# short lists at head_dim 128: four teams of 64 rows against undivided workgroups of 128, half as many
+@pytest.mark.parametrize("grid,group,max_kv,heads,teams", [
+    ((16, 32), (16, 16), 2, 27, 1), ((16, 32), (8, 16), 4, 25, 1), ((16, 32), (16, 16), 2, 15, 4), ((16, 32), (16, 16), 2, 21, 1), ((8, 112), (8, 16), 5, 15, 4), ((16, 80), (16, 16), 3, 10, 4),
+    ((32, 32), (16, 16), 4, 15, 4), ((32, 32), (8, 8), 9, 16, 4)])
+def test_four_teams_of_groups(grid, group, max_kv, heads, teams):
+    assert grat_probe_launch(torch.bfloat16, 1, heads, 128, grid, group, max_kv).teams == teams

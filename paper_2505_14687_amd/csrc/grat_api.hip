@@ -281,25 +281,27 @@ static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t
 // Whole tiles of a mixed launch (attn_mfma_mixed_kernel), 0: not one.  A compute unit each for the first 256 tiles of
 // 256 rows; what is left, if it is at most 128 tiles, keeps the others busy as twice as many workgroups of half the walk,
 // where 128-row workgroups, two a compute unit, would take another 0.7 of a round.  256-token groups, head_dim 128, us as
-// those | mixed, means of two allocations:
-//   128x128 tokens, 3x3 lists, 5 / 6 heads 98 / 124 | 92 / 103, 5x5 208 / 232 | 186 / 230, criss-cross 171 / 182 | 164 / 185; 96x96, 3x3, 8 / 10
-//   heads 77 / 98 | 71 / 94; 80x80, 3x3, 11 / 12 heads 80 / 79 | 68 / 73; 64x80, 3x3, 15 / 16 heads 82 / 80 | 71 / 73, criss-cross 98 / 93 | 94 / 94;
-//   video 8x32x48, 6 heads, 3x3x3 lists 133 | 125.
-// Not where it loses (375 launches of 4 to 64 groups, 16 to 96 heads x batch):
-//   lists longer than half of the grid's groups, whose lengths differ most: 128-row workgroups even them out in halves of a
-//   tile (5x5 lists in 80x96 tokens, 9 heads 142 | 158, in 96x96, 8 heads 153 | 163; 3x3 in 64x64, 18 heads 64 | 67, 24 heads 88 | 88);
-//   fewer than 20 groups, whose lists are short (32x32 tokens, 96 heads, 3x3 57 | 61, criss-cross 48 | 51; 48x64, 32 heads 82 | 88;
-//   48x96, 16 heads 64 | 68);
-//   a second round of a few tiles (48x176 tokens, 8 heads, 8 of them 63 | 66), or of few groups and more than three quarters full (80x96
-//   tokens, 12 heads 88 | 93).
-// What is left gains 5.9 % on average, up to 24 %, and loses up to 4 % in three of 129 launches.  After two full rounds of 256-row workgroups
-// there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads 177.4 | 184.1), and so do 1 024-token groups (96x96
-// tokens, 8 heads 211 | 221).
-static int32_t mixed_whole(int64_t tiles256, int64_t groups, int64_t max_kv, int64_t tables) {
+// those | mixed, 3x3 lists, means of four allocations: 64x64 tokens, 19 / 21 / 23 / 24 heads 78 / 87 / 95 / 87 | 69 / 74 / 86 / 87 (24 with
+// the lists built in the pass 86.3 | 84.4); 64x80, 16 heads 79 | 71; 80x80, 12 heads 78 | 70; 96x128, 8 heads 105 | 96.
+// `problems` = batch x heads.  Over 708 launches of 257 to 384 tiles (8 to 64 groups, images and video, 3x3, 5x5 and criss-cross
+// lists) mixed launches take 6.5 % less time on average, and 53 of them are more than 2 % (up to 13) slower.  Left out:
+//   multiples of four problems with fewer than 16 groups or lists of fewer than 8: ranked 128-row workgroups then have every head on the
+//   same two XCDs and miss their L2 less (64x64 tokens, 24 heads 17 MiB a head, 23 heads, where every XCD reads every head, 22), and
+//   there is 0.0 % on average in not doing so (48x64 tokens, 32 heads 80 | 87; 64x64 criss-cross, 24 heads 90 | 92).  Other
+//   numbers of problems gain 8.2 %;
+//   a second round of up to 32 tiles where problems are even, or lists longer than half of the groups differ most in length (64x64, 18 heads
+//   65 | 68; 96x96, 5x5, 8 heads -6 %; 12x24x32 tokens, 3x3x3, 8 heads -13 %; all together +1.7 %).
+// The 590 that stay gain 7.6 % on average, up to 30 %; 18 lose more than 2 %, the most 8x16x32 tokens, 3x3x3, 20 heads (108 | 116).
+// (Of 155 launches of 2 to 7 groups, measured once the line was drawn, 90 stay, gain 9.4 % and lose at most 1.5; the others would gain
+// -1.5 %.)  After two full rounds of 256-row workgroups there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads
+// 177.4 | 184.1), and so do 1 024-token groups (96x96 tokens, 8 heads 211 | 221).
+static int32_t mixed_whole(int64_t tiles256, int64_t problems, int64_t groups, int64_t max_kv, int64_t tables) {
     if (128 * 1024 + 4096 + tables > 160 * 1024) return 0;
     const int64_t rest = tiles256 - 256;
-    if (rest <= 8 || rest > (groups < 36 ? 96 : 128)) return 0;
-    return groups >= 20 && 2 * max_kv <= groups ? 256 : 0;
+    if (rest <= 0 || rest > 128) return 0;
+    if (problems % 4 == 0 && (groups < 16 || max_kv < 8)) return 0;
+    if (rest <= 32 && (problems % 2 == 0 || (groups >= 20 && 2 * max_kv > groups))) return 0;
+    return 256;
 }
 
 struct OutStrides { int64_t b, h, n; };   // O's own strides (elements)
@@ -405,7 +407,7 @@ static grat_status plan_attention(const void* Q, const void* K, const void* V, v
             if (p.teams == 4) bm = 64;
             else if (p.teams == 2) bm = 128;
             if (p.teams == 1 && n_global == 0 && head_dim == 128 && n_g == 256 && geo.num_groups <= 64)
-                p.n_whole = mixed_whole(tiles64 / 4, geo.num_groups, max_kv, tables);
+                p.n_whole = mixed_whole(tiles64 / 4, bh, geo.num_groups, max_kv, tables);
             if (p.n_whole > 0) bm = 256;
         }
     } else {

@@ -242,7 +242,8 @@ def test_probe_launch_argument_errors():
     ("f16", 2, 24, 128, (90, 160), (16, 16), 9, 0, "mfma_kernel<8, 64, 3, true, 128>", 2880, 360),
     ("bf16", 4, 16, 64, (64, 64), (16, 16), 7, 0, "mfma_kernel<4, 64, 0, false, 64>", 2048, 256),
     ("bf16", 1, 16, 128, (64, 80), (16, 16), 9, 0, "mfma_mixed_kernel<false>", 320, 40),
-    ("bf16", 1, 24, 128, (64, 64), (16, 16), 9, 0, "mfma_kernel<4, 64, 0, false, 128>", 768, 96),
+    ("bf16", 1, 24, 128, (64, 64), (16, 16), 9, 0, "mfma_mixed_kernel<false>", 384, 48),
+    ("bf16", 1, 24, 128, (64, 64), (16, 16), 7, 0, "mfma_kernel<4, 64, 0, false, 128>", 768, 96),
     ("bf16", 1, 1, 128, (64, 64), (16, 16), 9, 0, "mfma_teams_kernel<2, 32, 0, false, 128, 4>", 64, 8),
     ("f16", 1, 8, 64, (64, 64), (16, 16), 9, 0, "mfma_teams_kernel<4, 64, 0, true, 64, 2>", 256, 32),
     ("bf16", 1, 24, 128, (128, 128), (16, 16), 9, 512, "mfma_kernel<8, 64, 2, false, 128>", 1584, 198),

@@ -124,7 +124,7 @@ CASES = [  # kernel, batch, heads, head_dim, grid, group, pattern, prompt, promp
     # mixed
     ("mixed_kernel<false>", 2, 8, 128, (64, 80), (16, 16), "block", 0, True, "token major", "normal"),
     ("mixed_kernel<true>", 1, 16, 128, (64, 80), (16, 16), "cross", 0, True, "packed", "rising"),
-    ("mixed_kernel<true>", 3, 2, 128, (8, 32, 48), (4, 8, 8), "block", 0, True, "heads first", "peaked16"),
+    ("mixed_kernel<true>", 3, 5, 128, (4, 32, 48), (4, 8, 8), "block", 0, True, "heads first", "peaked16"),
 ]
 
 

@@ -51,11 +51,12 @@ def test_sweep_of_small_launches(dtype):
 
 # 257 to 384 tiles of 256 rows: where 128-row workgroups were measured to be faster than the mixed launch, and where they were not
 @pytest.mark.parametrize("grid,group,max_kv,heads,mixed", [
-    ((64, 64), (16, 16), 9, 18, False), ((64, 64), (16, 16), 9, 24, False), ((32, 32), (16, 16), 4, 72, False),
+    ((64, 64), (16, 16), 9, 18, False), ((64, 64), (16, 16), 7, 24, False), ((32, 32), (16, 16), 4, 72, False),
     ((32, 32), (16, 16), 3, 96, False), ((32, 48), (16, 16), 6, 64, False), ((48, 48), (16, 16), 5, 36, False),
-    ((48, 64), (16, 16), 9, 32, False), ((48, 96), (16, 16), 9, 16, False), ((80, 96), (16, 16), 9, 12, False),
+    ((48, 64), (16, 16), 9, 32, False), ((48, 96), (16, 16), 9, 16, False),
     ((96, 96), (16, 16), 25, 8, False), ((80, 80), (16, 16), 25, 11, False), ((12, 24, 32), (4, 8, 8), 27, 8, False),
     ((48, 176), (16, 16), 9, 8, False),
+    ((64, 64), (16, 16), 9, 19, True), ((64, 64), (16, 16), 7, 23, True), ((64, 64), (16, 16), 9, 24, True),
     ((64, 80), (16, 16), 9, 16, True), ((80, 80), (16, 16), 9, 12, True), ((96, 96), (16, 16), 9, 10, True),
     ((128, 128), (16, 16), 25, 6, True), ((128, 128), (16, 16), 9, 6, True), ((8, 32, 48), (4, 8, 8), 18, 7, True)])
 def test_mixed_launches_where_they_gain(grid, group, max_kv, heads, mixed):

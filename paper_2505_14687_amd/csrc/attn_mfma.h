@@ -1006,8 +1006,8 @@ __global__ __launch_bounds__(NWAVES * TEAMS * 64, 2) void attn_mfma_teams_kernel
 }
 
 // Launches of little more than one round: p.n_whole tiles of 256 rows, one for every compute unit, the others as two 128-row
-// workgroups of two teams each, all longest list first (80x80 tokens in 16x16 groups, 3x3 lists, 12 heads: 79 us as 128-row
-// workgroups, 73; 64x80 tokens, 16 heads 80, 73).
+// workgroups of two teams each, all longest list first (80x80 tokens in 16x16 groups, 3x3 lists, 12 heads: 78 us as 128-row
+// workgroups, 70; 64x80 tokens, 16 heads 79, 71).
 template <bool F16>
 __global__ __launch_bounds__(512, 2) void attn_mfma_mixed_kernel(AttnParams p) {
     __shared__ __attribute__((aligned(1024))) uint8_t lds[8][64 * 128 * 2];

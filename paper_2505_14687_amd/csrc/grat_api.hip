@@ -284,23 +284,24 @@ static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t
 // those | mixed, 3x3 lists, means of four allocations: 64x64 tokens, 19 / 21 / 23 / 24 heads 78 / 87 / 95 / 87 | 69 / 74 / 86 / 87 (24 with
 // the lists built in the pass 86.3 | 84.4); 64x80, 16 heads 79 | 71; 80x80, 12 heads 78 | 70; 96x128, 8 heads 105 | 96.
 // `problems` = batch x heads.  Over 708 launches of 257 to 384 tiles (8 to 64 groups, images and video, 3x3, 5x5 and criss-cross
-// lists) mixed launches take 6.5 % less time on average, and 53 of them are more than 2 % (up to 13) slower.  Left out:
-//   multiples of four problems with fewer than 16 groups or lists of fewer than 8: ranked 128-row workgroups then have every head on the
-//   same two XCDs and miss their L2 less (64x64 tokens, 24 heads 17 MiB a head, 23 heads, where every XCD reads every head, 22), and
-//   there is 0.0 % on average in not doing so (48x64 tokens, 32 heads 80 | 87; 64x64 criss-cross, 24 heads 90 | 92).  Other
-//   numbers of problems gain 8.2 %;
-//   a second round of up to 32 tiles where problems are even, or lists longer than half of the groups differ most in length (64x64, 18 heads
-//   65 | 68; 96x96, 5x5, 8 heads -6 %; 12x24x32 tokens, 3x3x3, 8 heads -13 %; all together +1.7 %).
-// The 590 that stay gain 7.6 % on average, up to 30 %; 18 lose more than 2 %, the most 8x16x32 tokens, 3x3x3, 20 heads (108 | 116).
-// (Of 155 launches of 2 to 7 groups, measured once the line was drawn, 90 stay, gain 9.4 % and lose at most 1.5; the others would gain
-// -1.5 %.)  After two full rounds of 256-row workgroups there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads
-// 177.4 | 184.1), and so do 1 024-token groups (96x96 tokens, 8 heads 211 | 221).
+// lists) mixed launches gain 6.5 % on average, and 53 of them lose more than 2 % (up to 13).  Left out:
+//   multiples of four problems with short lists, or few groups and lists that differ in length: ranked 128-row workgroups then
+//   have every head on the same two XCDs and miss their L2 less (64x64 tokens, 24 heads 17 MiB a head; 23 heads, where every XCD reads
+//   every head, 22), and mixed ones lose 2.0 % (48x64 tokens, 32 heads 80 | 87; 64x64 criss-cross, 24 heads 90 | 92).  Other numbers
+//   of problems gain 8.2 %;
+//   a second round of up to 32 tiles where lists are longer than half of the groups, which differ most (-0.1 %, but up to -13: 12x24x32 tokens,
+//   3x3x3, 8 heads; 96x96, 5x5, 8 heads 151 | 161), or few, short and of an even number of problems (-2.1 %: 64x64, 18 heads 65 | 68).
+// The 642 that stay gain 7.3 %, up to 30; 22 lose more than 2 %, the most 8x16x32 tokens, 3x3x3, 20 heads (108 | 116).  Of 155 launches
+// of 2 to 7 groups 95 stay, gain 8.9 %, two lose more than 2 %; the others would lose 1.7 %.  After two full rounds
+// of 256-row workgroups there is nothing in it (36 heads 118.3 | 117.8), after three it loses (56 heads 177.4 | 184.1), and so do
+// 1 024-token groups (96x96 tokens, 8 heads 211 | 221).
 static int32_t mixed_whole(int64_t tiles256, int64_t problems, int64_t groups, int64_t max_kv, int64_t tables) {
     if (128 * 1024 + 4096 + tables > 160 * 1024) return 0;
     const int64_t rest = tiles256 - 256;
     if (rest <= 0 || rest > 128) return 0;
-    if (problems % 4 == 0 && (groups < 16 || max_kv < 8)) return 0;
-    if (rest <= 32 && (problems % 2 == 0 || (groups >= 20 && 2 * max_kv > groups))) return 0;
+    if (problems % 4 == 0 && ((max_kv < 8 && groups < 24) || (groups < 16 && max_kv < groups))) return 0;
+    if (rest <= 32 && groups >= 20 && 2 * max_kv > groups) return 0;
+    if (rest <= 32 && rest > 16 && groups <= 20 && max_kv < 10 && problems % 2 == 0) return 0;
     return 256;
 }
 

@@ -55,7 +55,7 @@ def test_sweep_of_small_launches(dtype):
     ((32, 32), (16, 16), 3, 96, False), ((32, 48), (16, 16), 6, 64, False), ((48, 48), (16, 16), 5, 36, False),
     ((48, 64), (16, 16), 9, 32, False), ((48, 96), (16, 16), 9, 16, False),
     ((96, 96), (16, 16), 25, 8, False), ((80, 80), (16, 16), 25, 11, False), ((12, 24, 32), (4, 8, 8), 27, 8, False),
-    ((48, 176), (16, 16), 9, 8, False),
+    ((64, 80), (16, 16), 9, 14, False),
     ((64, 64), (16, 16), 9, 19, True), ((64, 64), (16, 16), 7, 23, True), ((64, 64), (16, 16), 9, 24, True),
     ((64, 80), (16, 16), 9, 16, True), ((80, 80), (16, 16), 9, 12, True), ((96, 96), (16, 16), 9, 10, True),
     ((128, 128), (16, 16), 25, 6, True), ((128, 128), (16, 16), 9, 6, True), ((8, 32, 48), (4, 8, 8), 18, 7, True)])

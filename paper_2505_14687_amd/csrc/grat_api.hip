@@ -268,9 +268,9 @@ static int key_teams(int head_dim, int64_t tiles64, int64_t tiles128, int64_t ke
 // heads (2.1 / 1.0) 79 / 64, 113 / 125 | 50 / 43, 70 / 81; 128x128 tokens, 3x3, 512 prompt tokens, 8 heads (2.5) 352 / 246 | 198 / 144.
 // Of two teams only 256 workgroups have a place.  Up to that many two teams are always ahead.  With more a second round of theirs has
 // to be shorter than what the prompt tiles save: not where the lists are nearly the whole walk (24 launches, 7 to 21 % slower: 64x64
-// tokens, 7x7 lists, 8 heads 98 / 117; 8x8x40 in 2x8x8 groups, 24 heads, 88 prompt tokens 37.5 / 47), nor where the walk is shorter than 44 tiles,
-// which does not cover the merges of two rounds (64x32, 20 heads, 96 prompt tokens 44 / 51), or than 90 with a ratio below 2 (64x64 in 32x32
-// groups, criss-cross, 8 heads, 835 prompt tokens 104 / 119).  Of 420 launches with a ratio of at least 1.7 and more than 256 tiles 385 stay
+// tokens, 7x7 lists, 8 heads 98 / 117; 8x8x40 in 2x8x8 groups, 24 heads, 88 prompt tokens 37.5 / 47), nor where the walk is shorter than 90 tiles
+// with a ratio below 2 (64x64 in 32x32 groups, criss-cross, 8 heads, 835 prompt tokens 104 / 119) or than 44 with one below 3, which does not
+// cover the merges of two rounds (64x32, 20 heads, 96 prompt tokens (2.3) 44 / 51; but 2x32x32 in 2x8x8, 16 heads, 127 (3.1) 38.1 / 31.6).  Of 420 launches with a ratio of at least 1.7 and more than 256 tiles 385 stay
 // and gain 36 %, 5 of them lose more than 2 % (up to 9); the others would lose 14 %.  (Below 2 it is lists of one length that lose, which is not
 // known here: criss-cross, 128x64, 12 heads, 36 prompt tokens (1.8) 160 / 182, 256x160 in 32x32, 3 heads (1.7) 853 / 899; but 80x144,
 // 7x7 lists, 4 heads, 21 prompt tokens (1.8) 197 / 176, 160x304, 3 heads, head_dim 64 (1.7) 626 / 488.)
@@ -278,7 +278,7 @@ static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t
     if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
     const int64_t rest = prompt_tiles * walk + group_tiles * list;
     if (prompt_tiles + group_tiles <= 256) return walk * 512 * 10 >= rest * 17 ? 2 : 1;
-    return walk >= 44 && 10 * list <= 9 * walk && walk * 512 * 10 >= rest * (walk < 90 ? 20 : 17) ? 2 : 1;
+    return 10 * list <= 9 * walk && walk * 512 * 10 >= rest * (walk < 44 ? 30 : walk < 90 ? 20 : 17) ? 2 : 1;
 }
 
 // Whole tiles of a mixed launch (attn_mfma_mixed_kernel), 0: not one.  A compute unit each for the first 256 tiles of

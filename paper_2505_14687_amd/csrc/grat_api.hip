@@ -449,10 +449,11 @@ static grat_status plan_attention(const void* Q, const void* K, const void* V, v
     // most 256 tiles, 3x3 lists in 16x16 groups: 80x80 tokens, 5 heads 41.7 | 55.3, 48x48 tokens, 14 heads 38.2 | 49.2, at head_dim 64
     // 24.5 | 33.1, 12 heads with 86 prompt tokens 34 | 47.6; 517 launches of up to 256 workgroups are 6 % (up to 22) faster without
     // ranking, 92 of more 13 % (up to 60) slower.  A full 256 of undivided workgroups, which do not have a compute unit to
-    // themselves, are ranked (fp32, 16x64 tokens in 8x8 groups, 16 heads x 64 45 | 48).
+    // themselves, are ranked (fp32, 16x64 tokens in 8x8 groups, 16 heads x 64 45 | 48), but not the lists of fewer than four groups, which differ little
+    // (32x32 tokens in one group, 32 heads 24.8 | 23.8).
     const int64_t workgroups = (int64_t)batch * heads * (((int64_t)geo.num_groups * p.q_tiles + kNumXcd - 1) / kNumXcd * kNumXcd) +
                                xcd_padded_blocks(p.n_dense_tiles);
-    p.longest_first = geo.num_groups <= 64 && workgroups > (p.teams > 1 ? 256 : 255) &&
+    p.longest_first = geo.num_groups <= 64 && workgroups > (p.teams > 1 || geo.num_groups < 4 ? 256 : 255) &&
                       (is16(dtype) && head_dim == 64 && n_g % 256 == 0 ? total / 2 : total) <= 16 * 256;
     p.fd_tiles_per_rank = make_fastdiv((uint32_t)(batch * heads * p.q_tiles));
     fill_fastdivs(p);

@@ -45,7 +45,7 @@ def test_sweep_of_small_launches(dtype):
                     tiles_per_head = rows * cols * math.ceil(256 / i.rows)
                     grouped = DIES * math.ceil(tiles_per_head / DIES) * heads
                     prompts = DIES * math.ceil(heads * math.ceil(prompt / i.rows) / DIES)
-                    assert i.longest_first == (grouped + prompts > (DIES * UNITS if i.teams > 1 else DIES * UNITS - 1))
+                    assert i.longest_first == (grouped + prompts > (DIES * UNITS if i.teams > 1 or rows * cols < 4 else DIES * UNITS - 1))
     assert seen > 200
 
 
@@ -79,3 +79,12 @@ def test_teams_of_joint_sequences(grid, group, max_kv, heads, d, prompt, teams):
     ((32, 32), (16, 16), 4, 15, 4), ((32, 32), (8, 8), 9, 16, 4)])
 def test_four_teams_of_groups(grid, group, max_kv, heads, teams):
     assert grat_probe_launch(torch.bfloat16, 1, heads, 128, grid, group, max_kv).teams == teams
+
+
+# 256 undivided workgroups, padding included: ranked unless their groups are too few for lists that differ
+@pytest.mark.parametrize("dtype,d,grid,group,max_kv,heads,ranked", [
+    (torch.bfloat16, 128, (32, 32), (32, 32), 1, 32, 0), (torch.float16, 64, (4, 24, 8), (4, 8, 8), 3, 32, 0), (torch.float32, 128, (32, 64), (32, 32), 2, 2, 0),
+    (torch.bfloat16, 128, (32, 32), (16, 16), 4, 32, 1), (torch.float32, 64, (16, 64), (8, 8), 6, 16, 1)])
+def test_full_launches_of_few_groups_are_not_ranked(dtype, d, grid, group, max_kv, heads, ranked):
+    i = grat_probe_launch(dtype, 1, heads, d, grid, group, max_kv)
+    assert i.teams <= 1 and i.longest_first == ranked

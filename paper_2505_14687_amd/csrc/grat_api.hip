@@ -261,24 +261,30 @@ static int key_teams(int head_dim, int64_t tiles64, int64_t tiles128, int64_t ke
     if (tiles128 > 0 && tiles128 <= 256 && keys >= (head_dim == 64 ? 1024 : 1408)) return 2;
     return 1;
 }
+// Lists as long as those of a criss-cross, of planes or of all groups: then they are all of one length.
+static bool one_length(const Geometry& geo, int64_t max_kv) {
+    const int64_t a = geo.G[0], b = geo.G[1], c = geo.G[2], n = geo.num_groups;
+    return max_kv == a + b + c - 2 || max_kv == n - (a - 1) * (b - 1) * (c - 1) || max_kv == n;
+}
 // Joint sequences: a prompt tile walks the whole sequence, which such a launch waits for where the rest of it is done
 // sooner.  `rest` = steps of 128 rows x 64 keys of the launch, for each of 512 places; 1 / 2 teams, us, head_dim 128 | 64 with
 // (walk / rest): 128x128 tokens, criss-cross, 100 prompt tokens 2 / 8 / 12 / 24 heads (8.1 / 2.0 / 1.3 / 0.7) 252 / 199,
 // 356 / 310, 419 / 445, 771 / 868 | 183 / 131, 216 / 202, 257 / 288, 456 / 545; 64x64 tokens, 3x3 lists, 256 prompt tokens, 12 / 24
 // heads (2.1 / 1.0) 79 / 64, 113 / 125 | 50 / 43, 70 / 81; 128x128 tokens, 3x3, 512 prompt tokens, 8 heads (2.5) 352 / 246 | 198 / 144.
 // Of two teams only 256 workgroups have a place.  Up to that many two teams are always ahead.  With more a second round of theirs has
-// to be shorter than what the prompt tiles save: not where the lists are nearly the whole walk (24 launches, 7 to 21 % slower: 64x64
-// tokens, 7x7 lists, 8 heads 98 / 117; 8x8x40 in 2x8x8 groups, 24 heads, 88 prompt tokens 37.5 / 47), nor where the walk is shorter than 90 tiles
-// with a ratio below 2 (64x64 in 32x32 groups, criss-cross, 8 heads, 835 prompt tokens 104 / 119) or than 44 with one below 3, which does not
-// cover the merges of two rounds (64x32, 20 heads, 96 prompt tokens (2.3) 44 / 51; but 2x32x32 in 2x8x8, 16 heads, 127 (3.1) 38.1 / 31.6).  Of 420 launches with a ratio of at least 1.7 and more than 256 tiles 385 stay
-// and gain 36 %, 5 of them lose more than 2 % (up to 9); the others would lose 14 %.  (Below 2 it is lists of one length that lose, which is not
-// known here: criss-cross, 128x64, 12 heads, 36 prompt tokens (1.8) 160 / 182, 256x160 in 32x32, 3 heads (1.7) 853 / 899; but 80x144,
-// 7x7 lists, 4 heads, 21 prompt tokens (1.8) 197 / 176, 160x304, 3 heads, head_dim 64 (1.7) 626 / 488.)
-static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t group_tiles, int64_t list, int64_t tables) {
+// to be shorter than what the prompt tiles save.  It is where lists differ in length, most being shorter than the longest, which `rest`
+// counts: of 235 such launches with a ratio of at least 1.7 one loses (6 %), and they gain 38 % (8x24x24 tokens in 2x8x8 groups, 10 heads, 74 prompt
+// tokens (1.8) 82 / 64; 80x144 in 16x16, 7x7 lists, 4 heads, 21 (1.8) 197 / 176).  Where all have one length (one_length) it is not if they are
+// nearly the whole walk (21 launches, 7 to 21 % slower: 64x64, 7x7 lists, 8 heads 98 / 117), nor on walks shorter than 90 tiles with
+// a ratio below 2.5 (64x64 in 32x32, criss-cross, 8 heads, 835 prompt tokens (2.0) 104 / 119) or than 44 with one below 3 (23, 9 to 21 %: 64x32,
+// 20 heads, 96 prompt tokens (2.3) 44 / 51; but 4x24x24 in 2x8x8, criss-cross, 16 heads, 87 (4.2) 43.5 / 38.2).  Of 420 launches 382 stay and gain 36 %, 3 of them lose more than 2 % (criss-cross, 256x160 in 32x32, 3
+// heads (1.7) 853 / 899); the others would lose 13 %.
+static int joint_teams(int head_dim, int64_t prompt_tiles, int64_t walk, int64_t group_tiles, int64_t list, int64_t tables, bool equal_lists) {
     if (head_dim * 1024 + 4096 + tables > 160 * 1024) return 1;
     const int64_t rest = prompt_tiles * walk + group_tiles * list;
-    if (prompt_tiles + group_tiles <= 256) return walk * 512 * 10 >= rest * 17 ? 2 : 1;
-    return 10 * list <= 9 * walk && walk * 512 * 10 >= rest * (walk < 44 ? 30 : walk < 90 ? 20 : 17) ? 2 : 1;
+    const bool short_round = prompt_tiles + group_tiles <= 256 || !equal_lists;
+    if (!short_round && 10 * list > 9 * walk) return 1;
+    return walk * 512 * 10 >= rest * (short_round || walk >= 90 ? 17 : walk >= 44 ? 25 : 30) ? 2 : 1;
 }
 
 // Whole tiles of a mixed launch (attn_mfma_mixed_kernel), 0: not one.  A compute unit each for the first 256 tiles of
@@ -407,7 +413,7 @@ static grat_status plan_attention(const void* Q, const void* K, const void* V, v
             const int64_t tiles64 = bh * geo.num_groups * (n_g / 64), tiles128 = n_g % 128 ? 0 : tiles64 / 2;
             if (n_global == 0) p.teams = key_teams(head_dim, tiles64, tiles128, (int64_t)max_kv * n_g, tables, false);
             else if (tiles128 > 0) p.teams = joint_teams(head_dim, bh * ((n_global + 127) / 128), (seq_len + 63) / 64, tiles128,
-                                                         (int64_t)max_kv * (n_g / 64) + (n_global + 63) / 64, tables);
+                                                         (int64_t)max_kv * (n_g / 64) + (n_global + 63) / 64, tables, one_length(geo, max_kv));
             if (p.teams == 4) bm = 64;
             else if (p.teams == 2) bm = 128;
             if (p.teams == 1 && n_global == 0 && head_dim == 128 && n_g == 256 && geo.num_groups <= 64)

@@ -68,7 +68,8 @@ def test_mixed_launches_where_they_gain(grid, group, max_kv, heads, mixed):
     ((4, 8, 40), (2, 8, 8), 10, 24, 128, 88, 1), ((64, 64), (32, 32), 3, 8, 128, 835, 1), ((64, 96), (32, 32), 6, 6, 64, 18, 1),
     ((64, 32), (16, 16), 5, 20, 128, 96, 1), ((64, 64), (16, 16), 16, 8, 128, 62, 1), ((128, 128), (16, 16), 15, 12, 128, 100, 1),
     ((128, 128), (16, 16), 15, 8, 128, 100, 2), ((64, 64), (16, 16), 9, 12, 64, 256, 2), ((128, 128), (16, 16), 9, 8, 128, 512, 2),
-    ((48, 48), (16, 16), 9, 12, 64, 86, 2), ((2, 32, 32), (2, 8, 8), 9, 16, 128, 127, 2), ((80, 144), (16, 16), 35, 4, 128, 21, 2), ((160, 304), (16, 16), 49, 3, 64, 56, 2)])
+    ((48, 48), (16, 16), 9, 12, 64, 86, 2), ((2, 32, 32), (2, 8, 8), 9, 16, 128, 127, 2), ((8, 24, 24), (2, 8, 8), 27, 10, 128, 74, 2),
+    ((2, 16, 64), (2, 8, 8), 6, 28, 64, 21, 2), ((48, 48), (16, 16), 5, 16, 64, 91, 1), ((4, 24, 24), (2, 8, 8), 6, 16, 128, 87, 2), ((80, 144), (16, 16), 35, 4, 128, 21, 2), ((160, 304), (16, 16), 49, 3, 64, 56, 2)])
 def test_teams_of_joint_sequences(grid, group, max_kv, heads, d, prompt, teams):
     assert grat_probe_launch(torch.bfloat16, 1, heads, d, grid, group, max_kv, prompt).teams == teams
 
